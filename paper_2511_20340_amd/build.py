@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecformer.so")
-SOURCES = ["api.hip", "attention.hip", "gemm.hip", "elementwise.hip", "accept.hip"]
+SOURCES = ["api.hip", "attention.hip", "gemm.hip", "gemm_f32.hip", "elementwise.hip", "accept.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-result"]

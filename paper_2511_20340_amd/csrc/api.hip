@@ -48,7 +48,7 @@ size_t esize(int dtype) { return dtype == SF_BF16 ? 2 : 4; }
 // (B*(max_k+1) rows) and draft-slot (B*k rows) uses; draft and verify run back to back on one
 // stream, so they share it.
 struct Arena {
-  size_t h, hb, a, qkv, qr, ao, gu, act, table, order, part_o, part_ml, pmax, pidx, logits;  // shared
+  size_t h, hb, a, qkv, qr, ao, act, table, order, part_o, part_ml, pmax, pidx, logits;  // shared
   size_t f4, x, kvc, xl, s0, s0b;                                        // draft only
   size_t x_last, id_last, q1, qr1, ao1, len_m1, zeros, kc2, vc2;         // draft, two-stage wiring
   size_t gemm_ws, gemm_ws_bytes, dev_err;
@@ -78,7 +78,6 @@ Arena plan(const sf_ctx *c, int B, int k, int cap) {
   a.qkv = take(M * (nq + 2 * nkv) * es);
   a.qr = take(M * nq * es);
   a.ao = take(M * nq * es);
-  a.gu = take(m.dtype == SF_F32 ? M * 2 * F * sizeof(float) : 0);  // bf16 gates in the GEMM epilogue
   a.act = take(M * F * es);
   a.table = take((Mx + Ms) * (m.head_dim / 2) * sizeof(float2));  // block rows, then the draft's slot rows
   a.order = take((size_t)B * sizeof(int32_t));
@@ -159,8 +158,9 @@ struct Run {
 };
 #define LAUNCH(cls, expr) r.launch(cls, [&] { return (expr); })
 
-// optional extras of one linear launch (bf16 mode)
+// optional extras of one linear launch (bf16 mode; the hooked copies and the norm's gains in fp32 mode)
 struct GemmExtra {
+  const void *gain_f32 = nullptr;  // fp32 mode: RMSNorm of the input rows (with the launch's norm_eps)
   int res_f32 = 0;               // residual (and, with out_f32, y) are rows of the float residual stream
   void *y2 = nullptr;            // bf16 copy of y
   void *hooks = nullptr;         // hooked copies of the block rows
@@ -178,9 +178,12 @@ void gemm(Run &r, int dtype, const void *x, const void *w, const void *bias, con
   g.plan_M = r.plan_rows;
   g.tile = r.c->tune_tile; g.split = r.c->tune_split;
   g.fused_norm = fused_norm; g.norm_eps = norm_eps;
+  if (ex) {
+    g.hooks = ex->hooks; g.hook_mask = ex->hook_mask; g.hook_q = ex->hook_q; g.hook_qmax = ex->hook_qmax;
+    if (dtype != SF_BF16) g.gain_f32 = ex->gain_f32;
+  }
   if (ex && dtype == SF_BF16) {
-    g.res_f32 = ex->res_f32; g.y2 = ex->y2; g.hooks = ex->hooks; g.hook_mask = ex->hook_mask; g.hook_q = ex->hook_q;
-    g.hook_qmax = ex->hook_qmax; g.am_val = ex->am_val; g.am_idx = ex->am_idx; g.am_stride = ex->am_stride;
+    g.res_f32 = ex->res_f32; g.y2 = ex->y2; g.am_val = ex->am_val; g.am_idx = ex->am_idx; g.am_stride = ex->am_stride;
     g.am_parts_out = ex->am_parts_out;
   }
   LAUNCH(K_GEMM, dtype == SF_BF16 ? launch_gemm_bf16(g, r.s) : launch_gemm_f32(g, r.s));
@@ -188,9 +191,11 @@ void gemm(Run &r, int dtype, const void *x, const void *w, const void *bias, con
 
 // LM head + arg-max: ids[row] = argmax_v (a . lm_head^T)[row][v].  bf16: the linear kernel's epilogue leaves
 // per-column-tile partials and the logits are stored only when `logits` is given; fp32: the logits are
-// materialised (in `logits`, else in `scratch_logits`) and scanned in segments.
+// materialised (in `logits`, else in `scratch_logits`) and scanned in segments; gain_f32: a norm of the rows of a
+// that the fp32 linear kernel applies itself.
 void lm_head_argmax(Run &r, const sf_model_cfg &m, const void *a, const void *lm_head, float *logits,
-                    float *scratch_logits, float *pmax, int32_t *pidx, int32_t *ids, int M) {
+                    float *scratch_logits, float *pmax, int32_t *pidx, int32_t *ids, int M,
+                    const void *gain_f32 = nullptr) {
   if (m.dtype == SF_BF16) {
     GemmExtra ex;
     int parts = 0;  // column tiles of the launch's tile shape: the partials it writes per row
@@ -199,22 +204,20 @@ void lm_head_argmax(Run &r, const sf_model_cfg &m, const void *a, const void *lm
     LAUNCH(K_ACCEPT, launch_argmax_final(pmax, pidx, M, parts, ex.am_stride, ids, r.s));
   } else {
     float *lg = logits ? logits : scratch_logits;
-    gemm(r, m.dtype, a, lm_head, nullptr, nullptr, lg, M, m.vocab, m.d_model, 1);
+    GemmExtra ex;
+    ex.gain_f32 = gain_f32;
+    gemm(r, m.dtype, a, lm_head, nullptr, nullptr, lg, M, m.vocab, m.d_model, 1, 0, 0, m.rms_eps, &ex);
     LAUNCH(K_ARGMAX, launch_argmax_partial(lg, M, m.vocab, pmax, pidx, r.s));
     LAUNCH(K_ACCEPT, launch_argmax_final(pmax, pidx, M, ARGMAX_SEGS, ARGMAX_SEGS, ids, r.s));
   }
 }
 
-// act[M][F] = silu(a . Wg^T) * (a . Wu^T): one kernel in bf16 mode (weight packed with glu = 1), GEMM to
-// fp32 + gating kernel in fp32 mode
-void swiglu_in(Run &r, int dtype, const void *a, const void *w_gate_up, float *gu, void *act, int M, int F, int K,
-               int fused_norm = 0, float norm_eps = 0.f) {
-  if (dtype == SF_BF16) {
-    gemm(r, dtype, a, w_gate_up, nullptr, nullptr, act, M, 2 * F, K, 0, 1, fused_norm, norm_eps);
-  } else {
-    gemm(r, dtype, a, w_gate_up, nullptr, nullptr, gu, M, 2 * F, K, 1);
-    LAUNCH(K_SILU, launch_silu_mul(gu, act, M, F, dtype, r.s));
-  }
+// act[M][F] = silu(a . Wg^T) * (a . Wu^T) in one kernel (bf16: weight packed with glu = 1)
+void swiglu_in(Run &r, int dtype, const void *a, const void *w_gate_up, void *act, int M, int F, int K,
+               int fused_norm = 0, float norm_eps = 0.f, const void *gain_f32 = nullptr) {
+  GemmExtra ex;
+  ex.gain_f32 = gain_f32;
+  gemm(r, dtype, a, w_gate_up, nullptr, nullptr, act, M, 2 * F, K, 0, 1, fused_norm, norm_eps, &ex);
 }
 
 void norm(Run &r, const sf_model_cfg &m, const void *x, const void *gain, void *y, int M, int n_gain = 1,
@@ -224,29 +227,23 @@ void norm(Run &r, const sf_model_cfg &m, const void *x, const void *gain, void *
   LAUNCH(K_NORM, launch_rmsnorm(n, m.dtype, r.s));
 }
 
-// y = RMSNorm(x; gain) . w^T.  bf16: ONE kernel -- w was packed with the gain folded into its columns,
-// the linear kernel takes the raw rows, sums their squares while staging them and scales its
-// accumulators by the row factor.  fp32: the norm kernel into `tmp`, then the linear kernel.
+// y = RMSNorm(x; gain) . w^T, one kernel.  bf16: w was packed with the gain folded into its columns, the linear
+// kernel takes the raw rows, sums their squares while staging them and scales its accumulators by the row
+// factor.  fp32: the linear kernel multiplies the rows by the gain as they arrive.
 // x: the rows in fp32 mode; xb: their bf16 copy in bf16 mode (rows of the residual stream are kept as float
 // plus a bf16 copy for exactly this use).
-void norm_gemm(Run &r, const sf_model_cfg &m, const void *x, const void *xb, const void *gain, void *tmp,
-               const void *w, void *y, int M, int N, int K, int out_f32) {
-  if (m.dtype == SF_BF16) {
-    gemm(r, m.dtype, xb, w, nullptr, nullptr, y, M, N, K, out_f32, 0, 1, m.rms_eps);
-  } else {
-    norm(r, m, x, gain, tmp, M);
-    gemm(r, m.dtype, tmp, w, nullptr, nullptr, y, M, N, K, out_f32);
-  }
+void norm_gemm(Run &r, const sf_model_cfg &m, const void *x, const void *xb, const void *gain, const void *w, void *y,
+               int M, int N, int K, int out_f32) {
+  GemmExtra ex;
+  ex.gain_f32 = gain;
+  const bool bf = m.dtype == SF_BF16;
+  gemm(r, m.dtype, bf ? xb : x, w, nullptr, nullptr, y, M, N, K, out_f32, 0, bf ? 1 : 0, m.rms_eps, &ex);
 }
 
-void norm_swiglu_in(Run &r, const sf_model_cfg &m, const void *x, const void *xb, const void *gain, void *tmp,
-                    const void *w_gate_up, float *gu, void *act, int M, int F, int K) {
-  if (m.dtype == SF_BF16) {
-    swiglu_in(r, m.dtype, xb, w_gate_up, gu, act, M, F, K, 1, m.rms_eps);
-  } else {
-    norm(r, m, x, gain, tmp, M);
-    swiglu_in(r, m.dtype, tmp, w_gate_up, gu, act, M, F, K);
-  }
+void norm_swiglu_in(Run &r, const sf_model_cfg &m, const void *x, const void *xb, const void *gain,
+                    const void *w_gate_up, void *act, int M, int F, int K) {
+  const bool bf = m.dtype == SF_BF16;
+  swiglu_in(r, m.dtype, bf ? xb : x, w_gate_up, act, M, F, K, bf ? 1 : 0, m.rms_eps, gain);
 }
 
 void attention(Run &r, const sf_model_cfg &m, const void *q, const void *kc, const void *vc, const int32_t *kv_len,
@@ -372,7 +369,6 @@ sf_status sf_verify_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_t
   float *h = (float *)(ws + A.h);                                    // the residual stream
   void *hb = m.dtype == SF_BF16 ? (void *)(ws + A.hb) : (void *)h;   // bf16: its copy for the matrix products
   void *a = ws + A.a, *qkv = ws + A.qkv, *qr = ws + A.qr, *ao = ws + A.ao, *act = ws + A.act;
-  float *gu = (float *)(ws + A.gu);
   const int d = m.d_model, F = m.d_ffn, L = m.n_layers;
   const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
   const bool bf = m.dtype == SF_BF16;
@@ -403,7 +399,7 @@ sf_status sf_verify_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_t
   const size_t lb = kv_layer_bytes(m, B, cap);
   for (int l = 0; l < L && r.st == SF_OK; ++l) {
     void *kc = (char *)st->tk + l * lb, *vc = (char *)st->tv + l * lb;
-    norm_gemm(r, m, h, hb, c->attn_norm[l], a, c->wqkv[l], qkv, M, nq + 2 * nkv, d, 0);
+    norm_gemm(r, m, h, hb, c->attn_norm[l], c->wqkv[l], qkv, M, nq + 2 * nkv, d, 0);
     ra.kc = kc; ra.vc = vc;
     // bf16: the attention kernel rotates Q and K and appends the block's K, V rows itself
     if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
@@ -413,18 +409,15 @@ sf_status sf_verify_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_t
     GemmExtra ex;
     ex.res_f32 = 1; ex.y2 = hb;
     gemm(r, m.dtype, ao, c->wo[l], nullptr, h, h, M, d, nq, 1, 0, 0, 0.f, &ex);
-    norm_swiglu_in(r, m, h, hb, c->ffn_norm[l], a, c->w_gate_up[l], gu, act, M, F, d);
+    norm_swiglu_in(r, m, h, hb, c->ffn_norm[l], c->w_gate_up[l], act, M, F, d);
     const int mask = hook_mask_of(l + 1);  // the stream after this layer is hooked state(s) `mask`
     if (mask) { ex.hooks = st->hooks; ex.hook_mask = mask; ex.hook_q = q; ex.hook_qmax = qm; }
     gemm(r, m.dtype, act, c->w_down[l], nullptr, h, h, M, d, F, 1, 0, 0, 0.f, &ex);
-    if (!bf)
-      for (int g = 1; g < 4; ++g)
-        if (mask >> g & 1) LAUNCH(K_EMBED_HOOK, launch_hook_copy(h, st->hooks, B, q, qm, d, g, m.dtype, r.s));
   }
   // the LM head serves two norms (this one and the draft's), so no gain is folded into it
-  norm(r, m, h, c->tw.final_norm, a, M, 1, 0, 1, 1, nullptr, 1);
-  lm_head_argmax(r, m, a, c->tw.lm_head, logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
-                 (int32_t *)(ws + A.pidx), target_ids, M);
+  if (bf) norm(r, m, h, c->tw.final_norm, a, M, 1, 0, 1, 1, nullptr, 1);
+  lm_head_argmax(r, m, bf ? a : h, c->tw.lm_head, logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
+                 (int32_t *)(ws + A.pidx), target_ids, M, c->tw.final_norm);
   if (r.st == SF_OK) { c->verified_state = st->kv_len; c->verified_k = k; }
   return r.st;
 }
@@ -451,7 +444,6 @@ sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, 
   void *f4 = ws + A.f4, *x = ws + A.x, *kvc = ws + A.kvc, *xl = ws + A.xl;
   float *s0 = (float *)(ws + A.s0);                                    // the slot layer's residual stream
   void *s0b = bf ? (void *)(ws + A.s0b) : (void *)s0;                  // bf16: its copy for the matrix products
-  float *gu = (float *)(ws + A.gu);
   float *part_o = (float *)(ws + A.part_o), *part_ml = (float *)(ws + A.part_ml);
   const int d = m.d_model, F = m.d_ffn;
   const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
@@ -463,7 +455,7 @@ sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, 
   gemm(r, m.dtype, f4, w.w_ds, nullptr, nullptr, x, Mh, d, 4 * d, 0);
   // K and V rows of wqkv start after the nq query rows (a whole number of packed 32-row blocks)
   const size_t kv_off = bf ? packed_weight_bytes(nq, d, m.dtype) : (size_t)nq * d * es;
-  norm_gemm(r, m, x, x, w.attn_norm, a, (const char *)w.wqkv + kv_off, kvc, Mh, 2 * nkv, d, 0);
+  norm_gemm(r, m, x, x, w.attn_norm, (const char *)w.wqkv + kv_off, kvc, Mh, 2 * nkv, d, 0);
   RopeArgs ra{};
   ra.qkv = kvc; ra.q_out = nullptr; ra.kc = st->dk; ra.vc = st->dv; ra.kv_len = st->kv_len; ra.n_new = st->n_new;
   ra.table = (float2 *)(ws + A.table);
@@ -492,7 +484,7 @@ sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, 
     float *id_last = (float *)(ws + A.id_last);
     int32_t *len_m1 = (int32_t *)(ws + A.len_m1);
     LAUNCH(K_EMBED_HOOK, launch_gather_last(x, x_last, st->n_new, st->kv_len, len_m1, B, qm, d, m.dtype, r.s));
-    norm_gemm(r, m, x_last, x_last, w.attn_norm, a, w.wqkv, q1, B, nq, d, 0);  // the nq query rows lead wqkv
+    norm_gemm(r, m, x_last, x_last, w.attn_norm, w.wqkv, q1, B, nq, d, 0);  // the nq query rows lead wqkv
     RopeArgs rq{};
     rq.qkv = q1; rq.q_out = qr1; rq.kc = nullptr; rq.vc = nullptr; rq.kv_len = len_m1; rq.n_new = nullptr;
     rq.table = ra.table; rq.B = B; rq.n_q = 1; rq.Hq = m.n_q_heads; rq.Hkv = 0; rq.hd = m.head_dim; rq.cap = cap;
@@ -511,7 +503,7 @@ sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, 
   ex.y2 = s0b;
   gemm(r, m.dtype, xl, w.w_pos, w.b_pos, nullptr, s0, B, k * d, d, 1, 0, 0, 0.f, &ex);
   // one attention + SwiGLU layer over the slots
-  norm_gemm(r, m, s0, s0b, norm_s, a, wqkv_s, qkv, Ms, nq + 2 * nkv, d, 0);
+  norm_gemm(r, m, s0, s0b, norm_s, wqkv_s, qkv, Ms, nq + 2 * nkv, d, 0);
   ra.qkv = qkv; ra.q_out = qr; ra.kc = (void *)kc_s; ra.vc = (void *)vc_s; ra.kv_len = len_s; ra.n_new = nullptr;
   ra.n_q = k; ra.cap = cap_s; ra.kv_only = 0; ra.pos_mode = 0; ra.table = slot_table;
   if (two_stage) LAUNCH(K_ROPE, launch_rope_table(ra, r.s));  // slots at positions 0..k-1 of their own tile
@@ -521,12 +513,12 @@ sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, 
             ra.table);
   ex.res_f32 = 1;
   gemm(r, m.dtype, ao, wo_s, nullptr, s0, s0, Ms, d, nq, 1, 0, 0, 0.f, &ex);
-  norm_swiglu_in(r, m, s0, s0b, w.ffn_norm, a, w.w_gate_up, gu, act, Ms, F, d);
+  norm_swiglu_in(r, m, s0, s0b, w.ffn_norm, w.w_gate_up, act, Ms, F, d);
   ex.y2 = nullptr;
   gemm(r, m.dtype, act, w.w_down, nullptr, s0, s0, Ms, d, F, 1, 0, 0, 0.f, &ex);
-  norm(r, m, s0, w.out_norm, a, Ms, 1, 0, 1, 1, nullptr, 1);
-  lm_head_argmax(r, m, a, c->tw.lm_head, draft_logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
-                 (int32_t *)(ws + A.pidx), draft_tokens, Ms);
+  if (bf) norm(r, m, s0, w.out_norm, a, Ms, 1, 0, 1, 1, nullptr, 1);
+  lm_head_argmax(r, m, bf ? a : s0, c->tw.lm_head, draft_logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
+                 (int32_t *)(ws + A.pidx), draft_tokens, Ms, w.out_norm);
   return r.st;
 }
 
@@ -721,7 +713,7 @@ sf_status sf_op_linear_swiglu(const sf_ctx *c, const void *x, const void *w_gate
   if (!bf && (!workspace || workspace_bytes < gu_bytes)) return SF_ECAPACITY;
   Run r{c, (hipStream_t)stream};
   if (bf && workspace && workspace_bytes >= lin) { r.gemm_ws = workspace; r.gemm_ws_bytes = workspace_bytes; }
-  swiglu_in(r, c->tc.dtype, x, w_gate_up, (float *)workspace, act, M, F, K);
+  swiglu_in(r, c->tc.dtype, x, w_gate_up, act, M, F, K);
   return r.st;
 }
 

@@ -337,82 +337,71 @@ __global__ __launch_bounds__(HD / 4) void attn_combine_kernel(
   *reinterpret_cast<uint2 *>(O + (((size_t)b * n_q + i) * Hq + hq) * HD + c4) = pk;
 }
 
-// fp32 path (small models): plain cache layout, one workgroup per (sequence, query head).
-// Keys are processed in chunks of CK with a workgroup-wide online softmax.
+// fp32 path (small models): plain cache layout, one workgroup per (query head, block row, sequence).
+// Keys are processed in chunks of CK with a workgroup-wide online softmax.  A pair of lanes scores one key (its
+// features in alternating groups of four), so 128 keys are scored at once; for the weighted sum of the values
+// the threads form hd/4 columns of four features times 256/(hd/4) key groups, which meet in LDS at the end.  At 64 keys everything is latency: one workgroup per row keeps
+// every chain short (4 sequences x 4 heads x 5 rows: 36 us with one workgroup per head walking all rows).
 constexpr int CK = 512;
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ Q, const float *__restrict__ Kc,
                                                        const float *__restrict__ Vc,
                                                        const int32_t *__restrict__ kv_len, float *__restrict__ O,
                                                        int n_q, int Hq, int Hkv, int hd, int cap, int mode,
                                                        float scale) {
-  extern __shared__ float sm[];
-  // sm: q[n_q][hd] | sc[n_q][CK] | red[256] | m[n_q] | l[n_q] | alpha[n_q]
-  float *sq = sm, *sc = sq + n_q * hd, *red = sc + n_q * CK, *sm_m = red + 256, *sm_l = sm_m + n_q,
-        *sm_a = sm_l + n_q;
-  const int hq = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  __shared__ float sq[256], sc[CK], red[8];
+  __shared__ f32x4 so[256];
+  const int hq = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = hq / (Hq / Hkv);
-  const int len = min(kv_len[b], cap - n_q), total = len + n_q;
+  const int len = min(kv_len[b], cap - n_q), total = len + (mode == SF_MASK_BIDIR ? n_q : i + 1);
   const float *K = Kc + ((size_t)b * Hkv + g) * (size_t)cap * hd;
   const float *V = Vc + ((size_t)b * Hkv + g) * (size_t)cap * hd;
-  for (int x = tid; x < n_q * hd; x += 256) sq[x] = Q[(((size_t)b * n_q + x / hd) * Hq + hq) * hd + x % hd];
-  if (tid < n_q) { sm_m[tid] = NEG_INF; sm_l[tid] = 0.f; }
-  // each thread owns up to 2 (row, feature) outputs per 256-stride sweep
-  float oacc[8];
-#pragma unroll
-  for (int x = 0; x < 8; ++x) oacc[x] = 0.f;
+  const size_t row = (((size_t)b * n_q + i) * Hq + hq) * hd;
+  if (tid < hd) sq[tid] = Q[row + tid];
   __syncthreads();
+  const int cols = hd / 4, groups = 256 / cols, col = tid % cols, grp = tid / cols;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  float m_run = NEG_INF, l_run = 0.f;
   for (int p0 = 0; p0 < total; p0 += CK) {
     const int nk = min(CK, total - p0);
-    for (int x = tid; x < n_q * nk; x += 256) {
-      const int i = x / nk, p = p0 + x % nk;
-      const int j = p - len;
-      const bool vis = j < 0 || (mode == SF_MASK_BIDIR || j <= i);
-      float s = NEG_INF;
-      if (vis) {
-        s = 0.f;
-        const float *kr = K + (size_t)p * hd;
-        for (int e = 0; e < hd; ++e) s += sq[i * hd + e] * kr[e];
-        s *= scale;
+    float mx = NEG_INF;
+    for (int x = tid >> 1; x < nk; x += 128) {
+      const float *kr = K + (size_t)(p0 + x) * hd + (tid & 1) * 4, *qr = sq + (tid & 1) * 4;
+      float s = 0.f;
+      for (int e = 0; e < hd; e += 8) {
+        const f32x4 k4 = *reinterpret_cast<const f32x4 *>(kr + e), q4 = *reinterpret_cast<const f32x4 *>(qr + e);
+        s += k4[0] * q4[0] + k4[1] * q4[1] + k4[2] * q4[2] + k4[3] * q4[3];
       }
-      sc[i * CK + x % nk] = s;
+      s = (s + __shfl_xor(s, 1)) * scale;
+      if ((tid & 1) == 0) sc[x] = s;
+      mx = fmaxf(mx, s);
     }
+    for (int w = 32; w; w >>= 1) mx = fmaxf(mx, __shfl_xor(mx, w));
+    if (lane == 0) red[wave] = mx;
     __syncthreads();
-    // per-row max and sum: wave w handles rows w, w+4, ...
-    const int lane = tid & 63, wave = tid >> 6;
-    for (int i = wave; i < n_q; i += 4) {
-      float mx = NEG_INF;
-      for (int x = lane; x < nk; x += 64) mx = fmaxf(mx, sc[i * CK + x]);
-      for (int o = 32; o; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-      const float m_new = fmaxf(sm_m[i], mx);
-      const float m_use = m_new == NEG_INF ? 0.f : m_new;
-      float sum = 0.f;
-      for (int x = lane; x < nk; x += 64) {
-        const float p = expf(sc[i * CK + x] - m_use);
-        sc[i * CK + x] = p;
-        sum += p;
-      }
-      for (int o = 32; o; o >>= 1) sum += __shfl_xor(sum, o);
-      if (lane == 0) {
-        const float a = expf(sm_m[i] - m_use);
-        sm_a[i] = a;
-        sm_l[i] = sm_l[i] * a + sum;
-        sm_m[i] = m_new;
-      }
+    const float m_new = fmaxf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), m_run);
+    float sum = 0.f;
+    for (int x = tid; x < nk; x += 256) {
+      const float p = expf(sc[x] - m_new);
+      sc[x] = p;
+      sum += p;
     }
+    for (int w = 32; w; w >>= 1) sum += __shfl_xor(sum, w);
+    if (lane == 0) red[4 + wave] = sum;
     __syncthreads();
-    int slot = 0;
-    for (int x = tid; x < n_q * hd; x += 256, ++slot) {
-      const int i = x / hd, e = x % hd;
-      float o = oacc[slot] * sm_a[i];
-      for (int kk = 0; kk < nk; ++kk) o += sc[i * CK + kk] * V[(size_t)(p0 + kk) * hd + e];
-      oacc[slot] = o;
-    }
-    __syncthreads();
+    const float alpha = expf(m_run - m_new);
+    l_run = l_run * alpha + ((red[4] + red[5]) + (red[6] + red[7]));
+    m_run = m_new;
+    o *= alpha;
+    if (grp < groups)
+      for (int x = grp; x < nk; x += groups)
+        o += sc[x] * *reinterpret_cast<const f32x4 *>(V + (size_t)(p0 + x) * hd + col * 4);
+    __syncthreads();  // sc and red are written again
   }
-  int slot = 0;
-  for (int x = tid; x < n_q * hd; x += 256, ++slot) {
-    const int i = x / hd, e = x % hd;
-    O[(((size_t)b * n_q + i) * Hq + hq) * hd + e] = oacc[slot] / sm_l[i];
+  so[tid] = o;
+  __syncthreads();
+  if (tid < cols) {
+    for (int x = 1; x < groups; ++x) o += so[x * cols + tid];
+    *reinterpret_cast<f32x4 *>(O + row + tid * 4) = o / l_run;
   }
 }
 
@@ -490,17 +479,9 @@ hipError_t launch_attention_combine(const AttnArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t s) {
-  const size_t lds = ((size_t)a.n_q * a.hd + (size_t)a.n_q * CK + 256 + 3 * a.n_q) * sizeof(float);
-  dim3 grid(a.Hq, a.B);
-  static bool attr_done = false;
-  if (!attr_done) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(attn_f32_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                        64 * 1024);
-    attr_done = true;
-  }
-  attn_f32_kernel<<<grid, 256, lds, s>>>((const float *)a.q, (const float *)a.kc, (const float *)a.vc, a.kv_len,
-                                         (float *)a.out, a.n_q, a.Hq, a.Hkv, a.hd, a.cap, a.mode,
-                                         1.f / sqrtf((float)a.hd));
+  attn_f32_kernel<<<dim3(a.Hq, a.n_q, a.B), 256, 0, s>>>((const float *)a.q, (const float *)a.kc, (const float *)a.vc,
+                                                         a.kv_len, (float *)a.out, a.n_q, a.Hq, a.Hkv, a.hd, a.cap,
+                                                         a.mode, 1.f / sqrtf((float)a.hd));
   return hipGetLastError();
 }
 

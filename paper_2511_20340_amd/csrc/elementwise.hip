@@ -260,15 +260,6 @@ __global__ __launch_bounds__(256) void gather_last_kernel(const T *__restrict__ 
   if (threadIdx.x == 0) len_m1[b] = max(kv_len[b] - 1, 0);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void hook_copy_kernel(const float *__restrict__ H, T *__restrict__ hooks, int q,
-                                                        int q_max, int d, int group) {
-  const int row = blockIdx.x, b = row / q, i = row % q;
-  const float *h = H + (size_t)row * d;
-  T *hk = hooks + (((size_t)b * q_max + i) * 4 + group) * d;
-  for (int e = threadIdx.x; e < d; e += 256) Elem<T>::st(hk + e, h[e]);
-}
-
 // plain [B][Hkv][cap][hd] <-> tiled (bf16) / plain (fp32: straight copy)
 template <typename T>
 __global__ void kv_convert_kernel(const T *__restrict__ src, T *__restrict__ dst, int is_v, int to_tiled,
@@ -361,13 +352,6 @@ hipError_t launch_gather_last(const void *x, void *out, const int32_t *n_new, co
     gather_last_kernel<bf16_t><<<B, 256, 0, s>>>((const bf16_t *)x, (bf16_t *)out, n_new, kv_len, len_m1, q, d);
   else
     gather_last_kernel<float><<<B, 256, 0, s>>>((const float *)x, (float *)out, n_new, kv_len, len_m1, q, d);
-  return hipGetLastError();
-}
-
-hipError_t launch_hook_copy(const float *h, void *hooks, int B, int q, int q_max, int d, int group, int dtype,
-                            hipStream_t s) {
-  if (dtype == SF_BF16) hook_copy_kernel<bf16_t><<<B * q, 256, 0, s>>>(h, (bf16_t *)hooks, q, q_max, d, group);
-  else hook_copy_kernel<float><<<B * q, 256, 0, s>>>(h, (float *)hooks, q, q_max, d, group);
   return hipGetLastError();
 }
 

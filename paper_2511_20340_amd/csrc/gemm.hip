@@ -23,8 +23,6 @@
 // Workgroup ids are remapped so that all M-tiles of one weight column block (and K split) run on the
 // same XCD (its L2 then serves the weight units to every M-tile after one HBM read), and those units are
 // dealt evenly over the eight XCDs.
-//
-// fp32 path: plain SIMT tiling on row-major weights for the small fp32 configuration.
 #include "sf_internal.h"
 
 #include <algorithm>
@@ -812,46 +810,6 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
   return best;
 }
 
-// fp32: 64x64 tile, 16 wide k slices, each thread a 4x4 micro-tile
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W,
-                                                       const float *__restrict__ bias, const float *residual,
-                                                       float *Y, int M, int N, int K) {
-  __shared__ float sA[16][65], sW[16][65];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int x = tid; x < 64 * 16; x += 256) {
-      const int r = x >> 4, kk = x & 15;
-      sA[kk][r] = (m0 + r < M && k0 + kk < K) ? A[(size_t)(m0 + r) * K + k0 + kk] : 0.f;
-      sW[kk][r] = (n0 + r < N && k0 + kk < K) ? W[(size_t)(n0 + r) * K + k0 + kk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], wv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = sA[kk][ty * 4 + i]; wv[i] = sW[kk][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int jn = 0; jn < 4; ++jn) acc[i][jn] += av[i] * wv[jn];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int jn = 0; jn < 4; ++jn) {
-      const int r = m0 + ty * 4 + i, c = n0 + tx * 4 + jn;
-      if (r < M && c < N) {
-        float v = acc[i][jn] + (bias ? bias[c] : 0.f);
-        if (residual) v += residual[(size_t)r * N + c];
-        Y[(size_t)r * N + c] = v;
-      }
-    }
-}
-
 }  // namespace
 
 // Called when weights are bound (outside any stream capture): the attribute calls of the tall tiles are
@@ -905,13 +863,6 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s) {
     if (c.tile <= 0) c.tile = c.split == h.split ? h.tile : pick(a.M, a.N, a.K, a.ws ? a.ws_bytes : 0, c.split).tile;
   }
   return dispatch(c.tile, a, s, c.split, 0);
-}
-
-hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
-  dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
-  gemm_f32_kernel<<<grid, 256, 0, s>>>((const float *)a.x, (const float *)a.w, (const float *)a.bias,
-                                       (const float *)a.residual, (float *)a.y, a.M, a.N, a.K);
-  return hipGetLastError();
 }
 
 }  // namespace sf

@@ -94,7 +94,7 @@ struct GemmArgs {
   void *y;
   int M, N, K;
   int out_f32;
-  int glu;          // bf16 only: w packed with glu=1, y = silu(gate) * up as elem [M][N/2]
+  int glu;          // y = silu(gate) * up as elem [M][N/2]; bf16: w packed with glu=1, fp32: w = [gate; up]
   void *ws;         // split-K tickets (first GEMM_TICKET_BYTES, zero between launches) + partial tiles
   size_t ws_bytes;  // 0: no split-K
   // bf16 kernel choice; 0 = heuristic.  plan_M: the row count the split factor is chosen for (the
@@ -104,11 +104,13 @@ struct GemmArgs {
   // folded into w's columns at pack time; the kernel supplies the row factor 1/sqrt(mean(x^2)+eps)
   int fused_norm = 0;
   float norm_eps = 0.f;
+  // fp32 only: the gain vector [K] of an RMSNorm applied to the rows of x on their way in (with norm_eps)
+  const void *gain_f32 = nullptr;
   // bf16 only, the residual stream: residual (and with out_f32 the output) is float [M][N]; y2, when
   // set, receives a bf16 copy of the output (what the next norm + linear pair multiplies with)
   int res_f32 = 0;
   void *y2 = nullptr;
-  // bf16 only: the output rows are block rows (b, i) = (row / hook_q, row % hook_q); their bf16 copy also
+  // the output rows are block rows (b, i) = (row / hook_q, row % hook_q); their copy in the model dtype also
   // goes to hooks[b][i][g][:] ([B][hook_qmax][4][N]) for every group g in hook_mask
   void *hooks = nullptr;
   int hook_mask = 0, hook_q = 1, hook_qmax = 1;
@@ -190,8 +192,6 @@ hipError_t launch_embed(const void *embed, const int32_t *pending, const int32_t
 // out[b] = x[b*q + n_new[b]-1] (zero row when n_new[b]==0); len_m1[b] = max(kv_len[b]-1, 0)
 hipError_t launch_gather_last(const void *x, void *out, const int32_t *n_new, const int32_t *kv_len, int32_t *len_m1,
                               int B, int q, int d, int dtype, hipStream_t s);
-hipError_t launch_hook_copy(const float *h, void *hooks, int B, int q, int q_max, int d, int group, int dtype,
-                            hipStream_t s);
 hipError_t launch_kv_convert(const void *src, void *dst, int is_v, int to_tiled, int B, int Hkv, int cap, int hd,
                              int dtype, hipStream_t s);
 
