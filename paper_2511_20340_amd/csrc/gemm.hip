@@ -49,6 +49,7 @@ struct Epilogue {
   int32_t *am_idx;       // ... and its column
   int hook_mask, hook_q, hook_qmax, am_stride;
   int out_f32, res_f32, glu;
+  int vec;               // every pointer above is 16-byte aligned
 };
 
 // f(integral_constant<0>) ... f(integral_constant<N-1>): a loop whose index is a compile-time constant in
@@ -74,6 +75,51 @@ __device__ __forceinline__ float half_wave_max(float v) {
   return fmaxf(v, __shfl_xor(v, 16));
 }
 
+// 8 consecutive elements as floats; vec: every pointer of the launch is 16-byte aligned
+__device__ __forceinline__ void load8(const bf16_t *p, float (&v)[8], int vec) {
+  if (vec) {
+    const u32x4 w = *reinterpret_cast<const u32x4 *>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[2 * i] = __uint_as_float(w[i] << 16); v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
+  } else {
+    for (int i = 0; i < 8; ++i) v[i] = bf2f(p[i]);
+  }
+}
+__device__ __forceinline__ void load8(const float *p, float (&v)[8], int vec) {
+  if (vec) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const f32x4 q = *reinterpret_cast<const f32x4 *>(p + j * 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
+    }
+  } else {
+    for (int i = 0; i < 8; ++i) v[i] = p[i];
+  }
+}
+__device__ __forceinline__ void store8(bf16_t *p, const float (&v)[8], int vec) {
+  if (vec) {
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = pack2bf(v[2 * i], v[2 * i + 1]);
+    *reinterpret_cast<u32x4 *>(p) = w;
+  } else {
+    for (int i = 0; i < 8; ++i) p[i] = f2bf(v[i]);
+  }
+}
+__device__ __forceinline__ void store8(float *p, const float (&v)[8], int vec) {
+  if (vec) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(p + j * 4) = f32x4{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
+  } else {
+    for (int i = 0; i < 8; ++i) p[i] = v[i];
+  }
+}
+
+// Row length (floats) of the LDS piece a wave turns a 32x32 tile in: rows stay 16-byte aligned, and the two rows
+// four apart that one store instruction writes land in different halves of the 64 banks.
+constexpr int TURN_STRIDE = 40;
+
 // What every bf16 kernel variant does once a workgroup holds its accumulators: the split-K hand-over
 // (partials, ticket, ordered sum in the last workgroup to arrive) and the output epilogue.
 //
@@ -83,7 +129,7 @@ __device__ __forceinline__ float half_wave_max(float v) {
 // is applied to the accumulators here.  With split-K the per-split sums travel next to the partial
 // tiles and are added in split order too.
 //
-// scratch: LDS the main loop no longer needs, at least NW * BM * 8 bytes (arg-max partials).
+// scratch: LDS the main loop no longer needs, at least NW * BM * 8 (arg-max partials) and NW * 128 * TURN_STRIDE bytes.
 template <int TM, int TN, int NW = 4>
 __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogue &e, int M, int N, int tiles_m,
                                             int split_k, float *__restrict__ partial,
@@ -169,30 +215,6 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
       }
   }
 
-  if (e.glu) {
-    // SwiGLU epilogue.  The weight was packed with gate and up rows interleaved 16 by 16, so a
-    // 32-column tile holds gate features f..f+15 in columns 0-15 and the matching up features in
-    // columns 16-31: lane ln < 16 fetches its partner's value and writes silu(gate) * up.
-    const int F = N >> 1;
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b) {
-        const int col = (nb0 + b) * 16 + (ln & 15);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float mine = acc[a][b][v];
-          const float other = __shfl_xor(mine, 16);
-          const int row = m0 + a * 32 + c_row(v, lh);
-          if ((ln & 16) == 0 && col < F && row < M) {
-            const float r = mine / (1.0f + __expf(-mine)) * other;
-            reinterpret_cast<bf16_t *>(e.y)[(size_t)row * F + col] = f2bf(r);
-          }
-        }
-      }
-    return;
-  }
-
   if (e.am_val) {
     // Arg-max partials of this workgroup's column tile: per row the largest accumulator and the lowest
     // column that holds it.  Columns past N and NaN never take part.
@@ -240,74 +262,110 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
     if (!e.y) return;
   }
 
-  // epilogue: lane holds column ln, rows c_row(v, lh) of every 32x32 tile.  y may be the residual
-  // buffer itself, and the residual loads are the only latency left at this point: the residual values
-  // of a group of 32x32 tiles are requested before the group's first store -- one exposed round trip per
-  // group.  A wave with up to five tiles forms one group; taller ones go five tiles at a time (their
-  // residual values would not fit the register file at once).
-  auto load_residual = [&](int a, int b, float (&res)[16]) __attribute__((always_inline)) {
-    const int col = min((nb0 + b) * 32 + ln, N - 1);
+  // Output.  A lane holds one column of 16 rows of every 32x32 tile; stored from there, an element is a 2- or
+  // 4-byte store of its own, and those stores cost more than the K loop of a short layer (160 x 2048 x 512 on
+  // 160-row tiles: 20.1 us, 9.6 us this way).  So each wave turns its tiles through a private piece of LDS, one
+  // after the other, and lane l then holds 16 consecutive columns of row l / 2: residual, output and copies move in
+  // 16-byte units.
+  __syncthreads();  // the other waves are done with the LDS this one is about to write
+  float *turn = reinterpret_cast<float *>(scratch) + wave * (32 * TURN_STRIDE);
+  const int t_row = lane >> 1, t_col = (lane & 1) * 16;
+  auto transpose = [&](const f32x16 &c, int col0, float (&v)[16], int step) __attribute__((always_inline)) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = min(m0 + a * 32 + c_row(v, lh), M - 1);
-      const size_t o = (size_t)row * N + col;
-      res[v] = e.res_f32 ? reinterpret_cast<const float *>(e.residual)[o]
-                         : bf2f(reinterpret_cast<const bf16_t *>(e.residual)[o]);
+    for (int i = 0; i < 16; ++i) turn[c_row(i, lh) * TURN_STRIDE + ln] = c[i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const f32x4 q = *reinterpret_cast<const f32x4 *>(turn + t_row * TURN_STRIDE + col0 + (j >> 1) * step + (j & 1) * 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  if (e.glu) {
+    // SwiGLU.  The weight was packed with gate and up rows interleaved 16 by 16: columns 0-15 of a tile are gate
+    // features f..f+15, columns 16-31 the matching up features.  Lane l takes 8 features of both.
+    const int F = N >> 1;
+    static_for<TM * TN>([&](auto i_c) {
+      constexpr int a = decltype(i_c)::value / TN, b = decltype(i_c)::value % TN;
+      const int col = (nb0 + b) * 16 + (lane & 1) * 8, row = m0 + a * 32 + t_row;
+      float v[16];
+      transpose(acc[a][b], (lane & 1) * 8, v, 16);
+      float r[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] = v[i] / (1.0f + __expf(-v[i])) * v[8 + i];
+      if (row < M && col < F) store8(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * F + col, r, e.vec);
+    });
+    return;
+  }
+
+  // The residual values of a group of tiles are requested before the group's first store (y may be the residual
+  // buffer itself): one exposed round trip per group.  A wave with up to five tiles forms one group, taller ones
+  // go five tiles at a time.
+  auto load_residual = [&](int a, int b, float (&res)[16]) __attribute__((always_inline)) {
+    const int row = min(m0 + a * 32 + t_row, M - 1);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const size_t o = (size_t)row * N + min((nb0 + b) * 32 + t_col + j * 8, N - 8);
+      float(&dst)[8] = reinterpret_cast<float(&)[8]>(res[j * 8]);
+      if (e.res_f32) load8(reinterpret_cast<const float *>(e.residual) + o, dst, e.vec);
+      else load8(reinterpret_cast<const bf16_t *>(e.residual) + o, dst, e.vec);
     }
   };
   auto store_tile = [&](int a, int b, const f32x16 &c, const float (&res)[16]) __attribute__((always_inline)) {
-    const int col = (nb0 + b) * 32 + ln;
-    if (col >= N) return;
-    const float bv = e.bias ? bf2f(e.bias[col]) : 0.f;
+    float v[16];
+    transpose(c, t_col, v, 8);
+    const int row = m0 + a * 32 + t_row;
+    if (row >= M) return;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = m0 + a * 32 + c_row(v, lh);
-      if (row >= M) continue;
-      float r = c[v] + bv;
+    for (int j = 0; j < 2; ++j) {
+      const int col = (nb0 + b) * 32 + t_col + j * 8;
+      if (col >= N) continue;
+      float r[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] = v[j * 8 + i];
+      if (e.bias) {
+        float bv[8];
+        load8(e.bias + col, bv, e.vec);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] += bv[i];
+      }
+      if (e.residual) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] += res[j * 8 + i];
+      }
       const size_t o = (size_t)row * N + col;
-      if (e.residual) r += res[v];
-      if (e.out_f32) reinterpret_cast<float *>(e.y)[o] = r;
-      else reinterpret_cast<bf16_t *>(e.y)[o] = f2bf(r);
-      if (e.y2) e.y2[o] = f2bf(r);
+      if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec);
+      else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec);
+      if (e.y2) store8(e.y2 + o, r, e.vec);
       if (e.hooks) {
         const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
 #pragma unroll
         for (int g = 1; g < 4; ++g)
-          if (e.hook_mask >> g & 1) e.hooks[(hrow + g) * N + col] = f2bf(r);
+          if (e.hook_mask >> g & 1) store8(e.hooks + (hrow + g) * N + col, r, e.vec);
       }
     }
   };
-  if constexpr (TM * TN <= 5) {
-    float res[TM][TN][16];
+  // constant tile indices whatever the size of the body: an unroll pragma gives up beyond a size threshold, and a
+  // run-time index into the accumulators would move them out of registers
+  constexpr int AG = TN >= 5 ? 1 : (TM < 5 / TN ? TM : 5 / TN), GROUPS = (TM + AG - 1) / AG;
+  static_for<GROUPS>([&](auto g_c) {
+    constexpr int a0 = decltype(g_c)::value * AG, a1 = a0 + AG < TM ? a0 + AG : TM;
+    float res[AG][TN][16];
     if (e.residual) {
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) load_residual(a, b, res[a][b]);
-    }
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b) store_tile(a, b, acc[a][b], res[a][b]);
-  } else {
-    // constant tile indices whatever the size of the body: an unroll pragma gives up beyond a size
-    // threshold, and a run-time index into the accumulators would move them out of registers
-    constexpr int AG = TN >= 5 ? 1 : 5 / TN, GROUPS = (TM + AG - 1) / AG;
-    static_for<GROUPS>([&](auto g_c) {
-      constexpr int a0 = decltype(g_c)::value * AG, a1 = a0 + AG < TM ? a0 + AG : TM;
-      float res[AG][TN][16];
-      if (e.residual) {
-#pragma unroll
-        for (int a = a0; a < a1; ++a)
-#pragma unroll
-          for (int b = 0; b < TN; ++b) load_residual(a, b, res[a - a0][b]);
-      }
 #pragma unroll
       for (int a = a0; a < a1; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b) store_tile(a, b, acc[a][b], res[a - a0][b]);
-    });
-  }
+        for (int b = 0; b < TN; ++b) load_residual(a, b, res[a - a0][b]);
+    }
+#pragma unroll
+    for (int a = a0; a < a1; ++a)
+#pragma unroll
+      for (int b = 0; b < TN; ++b) store_tile(a, b, acc[a][b], res[a - a0][b]);
+  });
 }
 
 // The bf16 kernel.  TM 32-row activation blocks x TN weight row blocks per wave, NW waves, ring
@@ -576,12 +634,20 @@ bool plan_fits(const Plan &p, int BM, const void *ws, size_t ws_bytes) {
          p.ticket_bytes <= GEMM_TICKET_BYTES && ssq_bytes <= GEMM_SSQ_BYTES;
 }
 
+// Dynamic LDS of a workgroup: the activation double buffer (+ the fused norm's row sums), later the epilogue's
+// transposition pieces.
+template <int TM, int NW>
+constexpr size_t lds_bytes(bool norm) {
+  constexpr size_t loop = (size_t)2 * TM * 32 * LDK * sizeof(bf16_t), turn = (size_t)NW * 32 * TURN_STRIDE * sizeof(float);
+  const size_t need = loop + (norm ? (size_t)TM * 32 * sizeof(float) : 0);
+  return need > turn ? need : turn;
+}
+
 // A tile whose activation double buffer exceeds the 64 KiB of dynamic LDS a kernel gets by default has the
 // limit of both its kernels (with and without the fused norm) raised, once per device.
 template <int TM, int TN, int R, int OCC, int NW, int PIPE = 0, int PIPE_NORM = PIPE>
 hipError_t ensure_lds() {
-  constexpr int BM = TM * 32;
-  constexpr int cap = 2 * BM * LDK * (int)sizeof(bf16_t) + BM * (int)sizeof(float);
+  constexpr int cap = (int)lds_bytes<TM, NW>(true);
   if (cap <= 64 * 1024) return hipSuccess;
   static bool raised[64] = {};
   int dev = 0;
@@ -605,7 +671,7 @@ hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split, int mode) {
   if (!plan_fits(p, BM, a.ws, a.ws_bytes)) return hipErrorInvalidValue;
   if (mode == 1) return hipSuccess;
   const int groups = (p.tiles_n * p.split_k + XCDS - 1) / XCDS;  // (column tile, K split) units per XCD
-  size_t lds = (size_t)2 * BM * LDK * sizeof(bf16_t);
+  const size_t lds = lds_bytes<TM, NW>(a.fused_norm != 0);
   unsigned *tickets = (unsigned *)a.ws;
   float *ssq_part = a.ws ? (float *)((char *)a.ws + GEMM_TICKET_BYTES) : nullptr;
   float *partial = a.ws ? (float *)((char *)a.ws + GEMM_TICKET_BYTES + GEMM_SSQ_BYTES) : nullptr;
@@ -614,8 +680,8 @@ hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split, int mode) {
   if (a.am_val && a.am_parts_out) *a.am_parts_out = p.tiles_n;
   static_assert((size_t)2 * BM * LDK * sizeof(bf16_t) >= (size_t)NW * BM * 8, "arg-max partials fit the activation tile");
   const Epilogue e{(const bf16_t *)a.bias, a.residual, a.y, (bf16_t *)a.y2, (bf16_t *)a.hooks, a.am_val, a.am_idx,
-                   a.hook_mask, a.hook_q, a.hook_qmax, a.am_stride, a.out_f32, a.res_f32, a.glu};
-  if (a.fused_norm) lds += (size_t)BM * sizeof(float);
+                   a.hook_mask, a.hook_q, a.hook_qmax, a.am_stride, a.out_f32, a.res_f32, a.glu,
+                   (((uintptr_t)a.bias | (uintptr_t)a.residual | (uintptr_t)a.y | (uintptr_t)a.y2 | (uintptr_t)a.hooks) & 15) == 0};
   if (lds > 64 * 1024) {
     const hipError_t err = ensure_lds<TM, TN, R, OCC, NW, PIPE, PIPE_NORM>();
     if (err != hipSuccess) return err;
