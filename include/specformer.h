@@ -236,9 +236,8 @@ sf_status sf_pack_weight(const sf_ctx *ctx, const void *w, void *packed, int32_t
 /* y[M][N] = x[M][K] . w[N][K]^T (+ bias[N]) (+ residual[M][N]); x, bias, residual: dev elem; w: packed;
  * fp32 accumulation; y: dev elem, or float when out_f32 != 0.  K % 8 == 0, N % 8 == 0.
  * residual may alias y.  workspace (dev, 256-byte aligned, may be NULL): lets skinny shapes split the
- * K dimension over several workgroups; its first 64 KiB are ticket counters that must be ZERO before
- * the first use and are left zero by every launch (the same holds for sf_state.workspace, which the
- * caller zero-fills once after allocating it).  sf_linear_workspace_bytes gives the size to pass. */
+ * K dimension over several workgroups (their partial sums; nothing is kept in it between calls).
+ * sf_linear_workspace_bytes gives the size to pass. */
 size_t sf_linear_workspace_bytes(const sf_ctx *ctx, int32_t M);
 sf_status sf_op_linear(const sf_ctx *ctx, const void *x, const void *w, const void *bias,
                        const void *residual, void *y, int32_t M, int32_t N, int32_t K, int32_t out_f32,

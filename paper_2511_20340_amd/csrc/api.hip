@@ -66,11 +66,10 @@ Arena plan(const sf_ctx *c, int B, int k, int cap) {
   Arena a;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += up(bytes); return o; };
-  // first, at an offset that does not depend on k: the split-K ticket counters must stay zero
-  // between calls, so no other buffer of any call shape may ever overlap them
   a.gemm_ws_bytes = m.dtype == SF_BF16 ? gemm_workspace_bytes((int)Mx) : 0;
   a.gemm_ws = take(a.gemm_ws_bytes);
-  a.zeros = take((size_t)B * sizeof(int32_t));  // likewise never written: the empty prefix of a slot-only attention
+  // at offsets that do not depend on k, so that no other buffer of any call shape ever overlaps them:
+  a.zeros = take((size_t)B * sizeof(int32_t));  // never written: the empty prefix of a slot-only attention
   a.dev_err = take(sizeof(int32_t));            // sticky SF_DEVERR_* bits, read and cleared by sf_check_state
   a.h = take(M * d * sizeof(float));  // the residual stream
   a.hb = take(m.dtype == SF_BF16 ? M * d * es : 0);

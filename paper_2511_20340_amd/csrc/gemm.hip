@@ -15,10 +15,9 @@
 // unconditional and issued in the order of use, so the compiler's vmcnt waits only ever cover the
 // slice that is needed next.
 //
-// Parallelism for small N*M: the K dimension is split over `split_k` workgroups per tile.  Each
-// leaves its fp32 partial tile in the workspace and takes a ticket; the last one to arrive adds
-// the partials in split order (deterministic), applies the epilogue and resets the ticket, so one
-// launch does everything and the counters stay zero between launches.
+// Parallelism for small N*M: the K dimension is split over `split_k` workgroups per tile.  Each leaves its fp32
+// partial tile in the workspace; a second, elementwise launch (split_finish_kernel) adds the partials in split
+// order (deterministic) and applies the epilogue with the whole chip.
 //
 // Workgroup ids are remapped so that all M-tiles of one weight column block (and K split) run on the
 // same XCD (its L2 then serves the weight units to every M-tile after one HBM read), and those units are
@@ -116,104 +115,82 @@ __device__ __forceinline__ void store8(float *p, const float (&v)[8], int vec) {
   }
 }
 
+// 8 finished columns of an output row: y, its bf16 copy, the hooked copies
+__device__ __forceinline__ void store_row8(const Epilogue &e, int row, int col, int N, const float (&r)[8]) {
+  const size_t o = (size_t)row * N + col;
+  if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec);
+  else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec);
+  if (e.y2) store8(e.y2 + o, r, e.vec);
+  if (e.hooks) {
+    const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
+#pragma unroll
+    for (int g = 1; g < 4; ++g)
+      if (e.hook_mask >> g & 1) store8(e.hooks + (hrow + g) * N + col, r, e.vec);
+  }
+}
+
 // Row length (floats) of the LDS piece a wave turns a 32x32 tile in: rows stay 16-byte aligned, and the two rows
 // four apart that one store instruction writes land in different halves of the 64 banks.
 constexpr int TURN_STRIDE = 40;
 
-// What every bf16 kernel variant does once a workgroup holds its accumulators: the split-K hand-over
-// (partials, ticket, ordered sum in the last workgroup to arrive) and the output epilogue.
+// What every bf16 kernel variant does once a workgroup holds its accumulators.
 //
 // Fused RMSNorm (sS != nullptr): the weight was packed with the norm's gain vector folded into its
 // columns, the main loop ran on the raw activations and left each row's sum of squares over this
 // workgroup's K range in sS[BM]; the row factor 1/sqrt(mean(x^2)+eps) commutes with the K sum and
-// is applied to the accumulators here.  With split-K the per-split sums travel next to the partial
-// tiles and are added in split order too.
+// is applied to the finished tiles here.
+//
+// Split K (split_k > 1): partial tile and row sums go to the workspace as rows of [split][M][N] and [split][M], and
+// split_finish_kernel does the rest.
 //
 // scratch: LDS the main loop no longer needs, at least NW * BM * 8 (arg-max partials) and NW * 128 * TURN_STRIDE bytes.
 template <int TM, int TN, int NW = 4>
-__device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogue &e, int M, int N, int tiles_m,
-                                            int split_k, float *__restrict__ partial,
-                                            unsigned *__restrict__ tickets, int tm, int tn, int ks, int m0,
-                                            int nb0, unsigned &s_ticket, void *scratch, float *sS = nullptr,
-                                            float *__restrict__ ssq_part = nullptr, int K = 1, float eps = 0.f) {
+__device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogue &e, int M, int N, int split_k,
+                                            float *__restrict__ partial, int tn, int ks, int m0, int nb0,
+                                            void *scratch, float *sS = nullptr, float *__restrict__ ssq_part = nullptr,
+                                            int K = 1, float eps = 0.f) {
   constexpr int BM = TM * 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ln = lane & 31, lh = lane >> 5;
+
+  // A lane holds one column of 16 rows of every 32x32 tile; stored from there, an element is a 2- or 4-byte store
+  // of its own, and those stores cost more than the K loop of a short layer (160 x 2048 x 512 on 160-row tiles:
+  // 20.1 us, 11.1 us this way).  So each wave turns its tiles through a private piece of LDS, one after the other,
+  // and lane l then holds 16 consecutive columns of row l / 2: residual, output and copies move in 16-byte units.
+  float *turn = reinterpret_cast<float *>(scratch) + wave * (32 * TURN_STRIDE);
+  const int t_row = lane >> 1, t_col = (lane & 1) * 16;
+  auto transpose = [&](const f32x16 &c, int col0, float (&v)[16], int step) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);  // tile by tile: overlapping them would cost registers the tall tiles lack
+#pragma unroll
+    for (int i = 0; i < 16; ++i) turn[c_row(i, lh) * TURN_STRIDE + ln] = c[i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const f32x4 q = *reinterpret_cast<const f32x4 *>(turn + t_row * TURN_STRIDE + col0 + (j >> 1) * step + (j & 1) * 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+
   if (split_k > 1) {
-    // Partial tiles in register order: [tile][split][wave][TM][TN][reg][lane], written and read with
-    // agent-scope atomic accesses only (write-through stores, loads that bypass the caches), so no
-    // cache-wide write-back or invalidate is needed for them.  Hand-over: every wave waits until its
-    // stores are acknowledged and releases at workgroup scope, the workgroup meets at a barrier, and one
-    // thread takes the tile's ticket with a release read-modify-write at agent scope; the thread that
-    // draws the last ticket follows it with an acquire fence at agent scope.  That chain (workgroup
-    // release -> barrier -> agent release ticket ... last ticket -> agent acquire fence -> barrier)
-    // orders every split's stores before the loads of the workgroup that finishes the tile.
-    const size_t tile = (size_t)tn * tiles_m + tm;
-    constexpr size_t PER_WAVE = (size_t)TM * TN * 64 * 16;
-    float *mine = partial + ((tile * split_k + ks) * NW + wave) * PER_WAVE;
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          __hip_atomic_store(mine + ((a * TN + b) * 16 + v) * 64 + lane, acc[a][b][v], __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-    if (sS && tid < BM)
-      __hip_atomic_store(ssq_part + (tile * split_k + ks) * BM + tid, sS[tid], __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_s_waitcnt(0);  // all counters: this wave's write-through stores have been acknowledged
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __syncthreads();
-    if (tid == 0) {
-      s_ticket = __hip_atomic_fetch_add(&tickets[tile], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      // only the workgroup that draws the last ticket reads other workgroups' data: it alone acquires
-      if (s_ticket == (unsigned)(split_k - 1)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-    __syncthreads();
-    if (s_ticket != (unsigned)(split_k - 1)) return;  // not the last split of this tile
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-    for (int s = 0; s < split_k; ++s) {  // fixed order: the sum does not depend on arrival order
-      const float *p = partial + ((tile * split_k + s) * NW + wave) * PER_WAVE;
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            acc[a][b][v] += __hip_atomic_load(p + ((a * TN + b) * 16 + v) * 64 + lane, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (sS) {
-      if (tid < BM) {
-        float t = 0.f;
-        for (int s = 0; s < split_k; ++s)
-          t += __hip_atomic_load(ssq_part + (tile * split_k + s) * BM + tid, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-        sS[tid] = t;
-      }
-      __syncthreads();
-    }
-    if (tid == 0) __hip_atomic_store(&tickets[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (sS && tn == 0 && tid < BM && m0 + tid < M) ssq_part[(size_t)ks * M + m0 + tid] = sS[tid];
+    __syncthreads();  // the other waves are done with the LDS this one is about to write
+    static_for<TM * TN>([&](auto i_c) {
+      constexpr int a = decltype(i_c)::value / TN, b = decltype(i_c)::value % TN;
+      float v[16];
+      transpose(acc[a][b], t_col, v, 8);
+      const int row = m0 + a * 32 + t_row, col = (nb0 + b) * 32 + t_col;
+      float *o = partial + ((size_t)ks * M + row) * N + col;
+      if (row < M && col < N) store8(o, reinterpret_cast<const float(&)[8]>(v[0]), 1);
+      if (row < M && col + 8 < N) store8(o + 8, reinterpret_cast<const float(&)[8]>(v[8]), 1);
+    });
+    return;
   }
 
-  if (sS) {
-    if (tid < BM) sS[tid] = 1.0f / sqrtf(sS[tid] / (float)K + eps);  // one row factor per row, once
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float rinv = sS[a * 32 + c_row(v, lh)];
-#pragma unroll
-        for (int b = 0; b < TN; ++b) acc[a][b][v] *= rinv;
-      }
-  }
+  if (sS && tid < BM) sS[tid] = 1.0f / sqrtf(sS[tid] / (float)K + eps);  // one row factor per row, once
 
   if (e.am_val) {
     // Arg-max partials of this workgroup's column tile: per row the largest accumulator and the lowest
@@ -262,29 +239,13 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
     if (!e.y) return;
   }
 
-  // Output.  A lane holds one column of 16 rows of every 32x32 tile; stored from there, an element is a 2- or
-  // 4-byte store of its own, and those stores cost more than the K loop of a short layer (160 x 2048 x 512 on
-  // 160-row tiles: 20.1 us, 9.6 us this way).  So each wave turns its tiles through a private piece of LDS, one
-  // after the other, and lane l then holds 16 consecutive columns of row l / 2: residual, output and copies move in
-  // 16-byte units.
-  __syncthreads();  // the other waves are done with the LDS this one is about to write
-  float *turn = reinterpret_cast<float *>(scratch) + wave * (32 * TURN_STRIDE);
-  const int t_row = lane >> 1, t_col = (lane & 1) * 16;
-  auto transpose = [&](const f32x16 &c, int col0, float (&v)[16], int step) __attribute__((always_inline)) {
+  __syncthreads();  // row factors are in place; the other waves are done with the LDS this one is about to write
+  auto scale_row = [&](int a, float (&v)[16]) __attribute__((always_inline)) {
+    if (!sS) return;
+    const float f = sS[a * 32 + t_row];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) turn[c_row(i, lh) * TURN_STRIDE + ln] = c[i];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f32x4 q = *reinterpret_cast<const f32x4 *>(turn + t_row * TURN_STRIDE + col0 + (j >> 1) * step + (j & 1) * 4);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    for (int i = 0; i < 16; ++i) v[i] *= f;
   };
-
   if (e.glu) {
     // SwiGLU.  The weight was packed with gate and up rows interleaved 16 by 16: columns 0-15 of a tile are gate
     // features f..f+15, columns 16-31 the matching up features.  Lane l takes 8 features of both.
@@ -294,6 +255,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
       const int col = (nb0 + b) * 16 + (lane & 1) * 8, row = m0 + a * 32 + t_row;
       float v[16];
       transpose(acc[a][b], (lane & 1) * 8, v, 16);
+      scale_row(a, v);
       float r[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) r[i] = v[i] / (1.0f + __expf(-v[i])) * v[8 + i];
@@ -304,7 +266,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
 
   // The residual values of a group of tiles are requested before the group's first store (y may be the residual
   // buffer itself): one exposed round trip per group.  A wave with up to five tiles forms one group, taller ones
-  // go five tiles at a time.
+  // go five, the tallest (no registers to spare) two tiles at a time.
   auto load_residual = [&](int a, int b, float (&res)[16]) __attribute__((always_inline)) {
     const int row = min(m0 + a * 32 + t_row, M - 1);
 #pragma unroll
@@ -318,6 +280,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   auto store_tile = [&](int a, int b, const f32x16 &c, const float (&res)[16]) __attribute__((always_inline)) {
     float v[16];
     transpose(c, t_col, v, 8);
+    scale_row(a, v);
     const int row = m0 + a * 32 + t_row;
     if (row >= M) return;
 #pragma unroll
@@ -337,21 +300,13 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
 #pragma unroll
         for (int i = 0; i < 8; ++i) r[i] += res[j * 8 + i];
       }
-      const size_t o = (size_t)row * N + col;
-      if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec);
-      else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec);
-      if (e.y2) store8(e.y2 + o, r, e.vec);
-      if (e.hooks) {
-        const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
-#pragma unroll
-        for (int g = 1; g < 4; ++g)
-          if (e.hook_mask >> g & 1) store8(e.hooks + (hrow + g) * N + col, r, e.vec);
-      }
+      store_row8(e, row, col, N, r);
     }
   };
   // constant tile indices whatever the size of the body: an unroll pragma gives up beyond a size threshold, and a
   // run-time index into the accumulators would move them out of registers
-  constexpr int AG = TN >= 5 ? 1 : (TM < 5 / TN ? TM : 5 / TN), GROUPS = (TM + AG - 1) / AG;
+  constexpr int MOST = TM * TN > 7 ? 2 : 5;  // tiles per group
+  constexpr int AG = TN >= MOST ? 1 : (TM < MOST / TN ? TM : MOST / TN), GROUPS = (TM + AG - 1) / AG;
   static_for<GROUPS>([&](auto g_c) {
     constexpr int a0 = decltype(g_c)::value * AG, a1 = a0 + AG < TM ? a0 + AG : TM;
     float res[AG][TN][16];
@@ -368,6 +323,18 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   });
 }
 
+// Dynamic LDS of a workgroup: the activation double buffer, later the epilogue's transposition pieces (+ the fused
+// norm's row sums behind them).
+template <int TM, int NW>
+constexpr size_t lds_loop_bytes() {
+  constexpr size_t loop = (size_t)2 * TM * 32 * LDK * sizeof(bf16_t), turn = (size_t)NW * 32 * TURN_STRIDE * sizeof(float);
+  return loop > turn ? loop : turn;
+}
+template <int TM, int NW>
+constexpr size_t lds_bytes(bool norm) {
+  return lds_loop_bytes<TM, NW>() + (norm ? (size_t)TM * 32 * sizeof(float) : 0);
+}
+
 // The bf16 kernel.  TM 32-row activation blocks x TN weight row blocks per wave, NW waves, ring
 // depth R.  Slot indices are compile-time after unrolling by R; the loop runs whole rounds of R
 // slices, and slices past the workgroup's K range contribute zeros.
@@ -375,17 +342,15 @@ template <int TM, int TN, int R, int OCC, int NW, int NORM, int PIPE = 0>
 __global__ __launch_bounds__(64 * NW, OCC) void gemm_ring_kernel(const bf16_t *__restrict__ A,
                                                         const uint4 *__restrict__ Wp, const Epilogue e, int M,
                                                         int N, int K, int tiles_m, int tiles_n, int split_k,
-                                                        int kt_per_split, float *__restrict__ partial,
-                                                        unsigned *__restrict__ tickets, float eps,
+                                                        int kt_per_split, float *__restrict__ partial, float eps,
                                                         float *__restrict__ ssq_part) {
   static_assert(R >= 2, "the slot after the current one holds the next activation chunk");
   constexpr int BM = TM * 32;
   constexpr int NT = 64 * NW;              // threads
   constexpr int CH = TM * 256;             // 16-byte activation chunks per K slice
   constexpr int CPT = (CH + NT - 1) / NT;  // chunks per thread
-  // [2][BM][LDK] activations; NORM: then float sS[BM], the rows' sums of squares
+  // [2][BM][LDK] activations (later the transposition pieces); NORM: then float sS[BM], the rows' sums of squares
   extern __shared__ __attribute__((aligned(16))) bf16_t sA[];
-  __shared__ unsigned s_ticket;
 
   // Consecutive workgroup ids go to consecutive XCDs.  The M-tiles of one (column tile, K split) unit read
   // the same weight bytes: they get consecutive slots of ONE XCD, and the units are dealt round-robin over
@@ -404,7 +369,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void gemm_ring_kernel(const bf16_t *_
   const int nb0 = (tn * NW + wave) * TN;
   const int KT = (K + BK - 1) / BK;
   const int kt0 = ks * kt_per_split, kt1 = min(KT, kt0 + kt_per_split);
-  float *sS = reinterpret_cast<float *>(sA + 2 * BM * LDK);
+  float *sS = reinterpret_cast<float *>(reinterpret_cast<char *>(sA) + lds_loop_bytes<TM, NW>());
   float ssq[CPT];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) ssq[c] = 0.f;
@@ -570,8 +535,67 @@ __global__ __launch_bounds__(64 * NW, OCC) void gemm_ring_kernel(const bf16_t *_
     }
     __syncthreads();
   }
-  gemm_finish<TM, TN, NW>(acc, e, M, N, tiles_m, split_k, partial, tickets, tm, tn, ks, m0, nb0, s_ticket, sA,
-                          NORM ? sS : nullptr, ssq_part, K, eps);
+  gemm_finish<TM, TN, NW>(acc, e, M, N, split_k, partial, tn, ks, m0, nb0, sA, NORM ? sS : nullptr, ssq_part, K, eps);
+}
+
+// The second launch of a layer whose K is split: adds a row's partials in split order, applies the fused norm's row
+// factor and the epilogue.  One thread per 8 output columns of a row; partials are read once, whole lines, by every
+// compute unit.  The alternative, one launch in which the last workgroup of a tile to arrive adds the tile's partials
+// behind write-through stores and an agent-scope ticket, costs 8 us at 5 MB of partials and 20 us at 21 MB where
+// this launch costs 5 and 15: 160 x 2048 x 2048 in 4 splits 15.8 -> 13.8 us, 5 x 4096 x 14336 in 8 splits
+// 32.3 -> 26.9 us, 160 x 2048 x 4096 in 8 splits 31.2 -> 20.0 us.
+__global__ __launch_bounds__(256) void split_finish_kernel(const float *__restrict__ partial,
+                                                           const float *__restrict__ ssq_part, const Epilogue e,
+                                                           int split, int M, int N, int K, float eps) {
+  const int cols8 = (e.glu ? N / 2 : N) / 8;
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= M * cols8) return;
+  const int row = idx / cols8, col = (idx - row * cols8) * 8;
+  const float *p = partial + (size_t)row * N + (e.glu ? (col >> 4) * 32 + (col & 15) : col);
+  const size_t step = (size_t)M * N;
+  float r[8], up[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = up[i] = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < split; ++s) {
+    float q[8];
+    load8(p + s * step, q, 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] += q[i];
+    if (e.glu) {
+      load8(p + s * step + 16, q, 1);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) up[i] += q[i];
+    }
+  }
+  if (ssq_part) {
+    float t = 0.f;
+    for (int s = 0; s < split; ++s) t += ssq_part[(size_t)s * M + row];
+    const float rinv = 1.0f / sqrtf(t / (float)K + eps);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { r[i] *= rinv; up[i] *= rinv; }
+  }
+  if (e.glu) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = r[i] / (1.0f + __expf(-r[i])) * up[i];
+    store8(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * (N >> 1) + col, r, e.vec);
+    return;
+  }
+  const size_t o = (size_t)row * N + col;
+  if (e.bias) {
+    float bv[8];
+    load8(e.bias + col, bv, e.vec);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] += bv[i];
+  }
+  if (e.residual) {
+    float res[8];
+    if (e.res_f32) load8(reinterpret_cast<const float *>(e.residual) + o, res, e.vec);
+    else load8(reinterpret_cast<const bf16_t *>(e.residual) + o, res, e.vec);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] += res[i];
+  }
+  store_row8(e, row, col, N, r);
 }
 
 // row-major [N][K] -> packed units; one thread per 16-byte operand register
@@ -607,7 +631,7 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 
 struct Plan {
   int tiles_m, tiles_n, split_k, kt_per_split;
-  size_t partial_bytes, ticket_bytes;
+  size_t partial_bytes;
 };
 
 // split_k workgroups share a tile's K range.  The partition depends on K and split only -- never on
@@ -622,25 +646,14 @@ Plan make_plan(int M, int N, int K, int BM, int BN, int split) {
   p.kt_per_split = (KT + s - 1) / s;
   p.split_k = (KT + p.kt_per_split - 1) / p.kt_per_split;
   p.partial_bytes = p.split_k > 1 ? (size_t)tiles * p.split_k * BM * BN * sizeof(float) : 0;
-  p.ticket_bytes = p.split_k > 1 ? (size_t)tiles * sizeof(unsigned) : 0;
   return p;
 }
 
-// workspace: [tickets][row sums of squares of the fused norm][partial tiles]
+// workspace: [row sums of squares of the fused norm][partial tiles]
 bool plan_fits(const Plan &p, int BM, const void *ws, size_t ws_bytes) {
   if (p.split_k == 1) return true;
-  const size_t ssq_bytes = (size_t)p.tiles_m * p.tiles_n * p.split_k * BM * sizeof(float);
-  return ws && ws_bytes >= GEMM_TICKET_BYTES + GEMM_SSQ_BYTES + p.partial_bytes &&
-         p.ticket_bytes <= GEMM_TICKET_BYTES && ssq_bytes <= GEMM_SSQ_BYTES;
-}
-
-// Dynamic LDS of a workgroup: the activation double buffer (+ the fused norm's row sums), later the epilogue's
-// transposition pieces.
-template <int TM, int NW>
-constexpr size_t lds_bytes(bool norm) {
-  constexpr size_t loop = (size_t)2 * TM * 32 * LDK * sizeof(bf16_t), turn = (size_t)NW * 32 * TURN_STRIDE * sizeof(float);
-  const size_t need = loop + (norm ? (size_t)TM * 32 * sizeof(float) : 0);
-  return need > turn ? need : turn;
+  const size_t ssq_bytes = (size_t)p.tiles_m * p.split_k * BM * sizeof(float);
+  return ws && ws_bytes >= GEMM_SSQ_BYTES + p.partial_bytes && ssq_bytes <= GEMM_SSQ_BYTES;
 }
 
 // A tile whose activation double buffer exceeds the 64 KiB of dynamic LDS a kernel gets by default has the
@@ -672,11 +685,10 @@ hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split, int mode) {
   if (mode == 1) return hipSuccess;
   const int groups = (p.tiles_n * p.split_k + XCDS - 1) / XCDS;  // (column tile, K split) units per XCD
   const size_t lds = lds_bytes<TM, NW>(a.fused_norm != 0);
-  unsigned *tickets = (unsigned *)a.ws;
-  float *ssq_part = a.ws ? (float *)((char *)a.ws + GEMM_TICKET_BYTES) : nullptr;
-  float *partial = a.ws ? (float *)((char *)a.ws + GEMM_TICKET_BYTES + GEMM_SSQ_BYTES) : nullptr;
+  float *ssq_part = p.split_k > 1 ? (float *)a.ws : nullptr;
+  float *partial = p.split_k > 1 ? (float *)((char *)a.ws + GEMM_SSQ_BYTES) : nullptr;
   const dim3 grid(groups * XCDS * p.tiles_m), block(64 * NW);
-  if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n)) return hipErrorInvalidValue;
+  if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;
   if (a.am_val && a.am_parts_out) *a.am_parts_out = p.tiles_n;
   static_assert((size_t)2 * BM * LDK * sizeof(bf16_t) >= (size_t)NW * BM * 8, "arg-max partials fit the activation tile");
   const Epilogue e{(const bf16_t *)a.bias, a.residual, a.y, (bf16_t *)a.y2, (bf16_t *)a.hooks, a.am_val, a.am_idx,
@@ -689,11 +701,16 @@ hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split, int mode) {
   if (a.fused_norm) {
     gemm_ring_kernel<TM, TN, R, OCC, NW, 1, PIPE_NORM><<<grid, block, lds, s>>>(
         (const bf16_t *)a.x, (const uint4 *)a.w, e, a.M, a.N, a.K, p.tiles_m, p.tiles_n, p.split_k, p.kt_per_split,
-        partial, tickets, a.norm_eps, ssq_part);
+        partial, a.norm_eps, ssq_part);
   } else {
     gemm_ring_kernel<TM, TN, R, OCC, NW, 0, PIPE><<<grid, block, lds, s>>>(
         (const bf16_t *)a.x, (const uint4 *)a.w, e, a.M, a.N, a.K, p.tiles_m, p.tiles_n, p.split_k, p.kt_per_split,
-        partial, tickets, 0.f, nullptr);
+        partial, 0.f, nullptr);
+  }
+  if (p.split_k > 1) {
+    const int units = a.M * ((a.glu ? a.N / 2 : a.N) / 8);
+    split_finish_kernel<<<(units + 255) / 256, 256, 0, s>>>(partial, a.fused_norm ? ssq_part : nullptr, e, p.split_k,
+                                                            a.M, a.N, a.K, a.norm_eps);
   }
   return hipGetLastError();
 }
@@ -904,7 +921,7 @@ bool gemm_config_fits(const GemmConfig &c, const GemmArgs &a) {
 
 size_t gemm_workspace_bytes(int M_max) {
   (void)M_max;
-  return GEMM_TICKET_BYTES + GEMM_SSQ_BYTES + GEMM_PARTIAL_BYTES;
+  return GEMM_SSQ_BYTES + GEMM_PARTIAL_BYTES;
 }
 
 size_t packed_weight_bytes(int N, int K, int dtype) {

@@ -95,7 +95,7 @@ struct GemmArgs {
   int M, N, K;
   int out_f32;
   int glu;          // y = silu(gate) * up as elem [M][N/2]; bf16: w packed with glu=1, fp32: w = [gate; up]
-  void *ws;         // split-K tickets (first GEMM_TICKET_BYTES, zero between launches) + partial tiles
+  void *ws;         // split-K partials: row sums of squares (first GEMM_SSQ_BYTES) and tiles
   size_t ws_bytes;  // 0: no split-K
   // bf16 kernel choice; 0 = heuristic.  plan_M: the row count the split factor is chosen for (the
   // largest M this weight is used with), so that every M gets the same K partition; 0 = M.
@@ -127,7 +127,6 @@ inline int gemm_argmax_parts(int N) { return (N + 127) / 128; }
 struct GemmConfig {
   int tile, split;
 };
-constexpr size_t GEMM_TICKET_BYTES = 64 * 1024;
 constexpr size_t GEMM_PARTIAL_BYTES = 96u * 1024 * 1024;
 constexpr size_t GEMM_SSQ_BYTES = 1024 * 1024;  // split-K: per-split row sums of squares of the fused norm
 size_t gemm_workspace_bytes(int M_max);

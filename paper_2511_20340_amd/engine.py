@@ -286,12 +286,12 @@ class Engine:
         return out
 
     def linear_workspace(self, M):
-        """(pointer, bytes) of a zero-filled split-K workspace, cached per engine."""
+        """(pointer, bytes) of a split-K workspace, cached per engine."""
         nb = self.lib.sf_linear_workspace_bytes(self.ctx, M)
         if nb == 0:
             return None, 0
         if getattr(self, "_lin_ws", None) is None or self._lin_ws.numel() < nb + 256:
-            self._lin_ws = torch.zeros(nb + 256, dtype=torch.uint8, device=self.dev)
+            self._lin_ws = torch.empty(nb + 256, dtype=torch.uint8, device=self.dev)
         p = self._lin_ws.data_ptr() + (-self._lin_ws.data_ptr()) % 256
         return C.c_void_p(p), nb
 
