@@ -19,13 +19,6 @@ namespace {
 constexpr int WAVES = 4;
 constexpr float NEG_INF = -__builtin_huge_valf();
 
-// one 16-byte operand unit; ONCE: no other workgroup reads it, so the caches need not keep it
-template <int ONCE>
-__device__ __forceinline__ uint4 load_unit(const uint4 *p) {
-  if constexpr (ONCE) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)));
-  return *p;
-}
-
 // FUSE = 1 (the target's layers): Q is the raw output of the QKV projection, rows [q | k | v].  The
 // workgroup first rotates the block's new K rows that fall into its own tiles (RoPE, cos/sin from
 // `table`) and appends them and the V rows to the cache, then rotates its Q rows in registers (a

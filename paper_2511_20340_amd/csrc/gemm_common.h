@@ -1,0 +1,117 @@
+// What the kernels of the bf16 linear layers and their host code share: the epilogue's arguments, row input / output,
+// the K partition.
+#pragma once
+#include "sf_internal.h"
+
+namespace sf {
+
+constexpr int BK = 64;
+constexpr int LDK = 72;  // padded LDS row length in bf16 elements (144 B)
+constexpr int XCDS = 8;
+
+// Where a workgroup's finished accumulators go.
+struct Epilogue {
+  const bf16_t *bias;    // [N] or null
+  const void *residual;  // [M][N] bf16, or float when res_f32; may alias y
+  void *y;               // [M][N] bf16, or float when out_f32; null: not stored (arg-max partials only)
+  bf16_t *y2;            // optional bf16 copy of y
+  bf16_t *hooks;         // optional: bf16 copies of block row (r / hook_q, r % hook_q) into the groups of hook_mask
+  float *am_val;         // optional [M][am_stride]: per row and column tile the largest value ...
+  int32_t *am_idx;       // ... and its column
+  int hook_mask, hook_q, hook_qmax, am_stride;
+  int out_f32, res_f32, glu;
+  int vec;               // every pointer above is 16-byte aligned
+};
+
+// 8 consecutive elements as floats; vec: every pointer of the launch is 16-byte aligned
+__device__ __forceinline__ void load8(const bf16_t *p, float (&v)[8], int vec) {
+  if (vec) {
+    const u32x4 w = *reinterpret_cast<const u32x4 *>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[2 * i] = __uint_as_float(w[i] << 16); v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
+  } else {
+    for (int i = 0; i < 8; ++i) v[i] = bf2f(p[i]);
+  }
+}
+__device__ __forceinline__ void load8(const float *p, float (&v)[8], int vec) {
+  if (vec) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const f32x4 q = *reinterpret_cast<const f32x4 *>(p + j * 4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
+    }
+  } else {
+    for (int i = 0; i < 8; ++i) v[i] = p[i];
+  }
+}
+__device__ __forceinline__ void store8(bf16_t *p, const float (&v)[8], int vec) {
+  if (vec) {
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = pack2bf(v[2 * i], v[2 * i + 1]);
+    *reinterpret_cast<u32x4 *>(p) = w;
+  } else {
+    for (int i = 0; i < 8; ++i) p[i] = f2bf(v[i]);
+  }
+}
+__device__ __forceinline__ void store8(float *p, const float (&v)[8], int vec) {
+  if (vec) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(p + j * 4) = f32x4{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
+  } else {
+    for (int i = 0; i < 8; ++i) p[i] = v[i];
+  }
+}
+
+// 8 finished columns of an output row: y, its bf16 copy, the hooked copies
+__device__ __forceinline__ void store_row8(const Epilogue &e, int row, int col, int N, const float (&r)[8]) {
+  const size_t o = (size_t)row * N + col;
+  if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec);
+  else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec);
+  if (e.y2) store8(e.y2 + o, r, e.vec);
+  if (e.hooks) {
+    const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
+#pragma unroll
+    for (int g = 1; g < 4; ++g)
+      if (e.hook_mask >> g & 1) store8(e.hooks + (hrow + g) * N + col, r, e.vec);
+  }
+}
+
+struct Plan {
+  int tiles_m, tiles_n, split_k, kt_per_split;
+  size_t partial_bytes;
+};
+
+// split_k workgroups share a tile's K range.  The partition depends on K and split only -- never on
+// the tile configuration -- because it fixes the fp32 summation order of every output element.
+inline Plan make_plan(int M, int N, int K, int BM, int BN, int split) {
+  Plan p;
+  p.tiles_m = (M + BM - 1) / BM;
+  p.tiles_n = (N + BN - 1) / BN;
+  const int KT = (K + BK - 1) / BK;
+  const int tiles = p.tiles_m * p.tiles_n;
+  const int s = split < 1 ? 1 : (split > KT ? KT : split);
+  p.kt_per_split = (KT + s - 1) / s;
+  p.split_k = (KT + p.kt_per_split - 1) / p.kt_per_split;
+  p.partial_bytes = p.split_k > 1 ? (size_t)tiles * p.split_k * BM * BN * sizeof(float) : 0;
+  return p;
+}
+
+// workspace: [row sums of squares of the fused norm][partial tiles]
+inline bool plan_fits(const Plan &p, int BM, const void *ws, size_t ws_bytes) {
+  if (p.split_k == 1) return true;
+  const size_t ssq_bytes = (size_t)p.tiles_m * p.split_k * BM * sizeof(float);
+  return ws && ws_bytes >= GEMM_SSQ_BYTES + p.partial_bytes && ssq_bytes <= GEMM_SSQ_BYTES;
+}
+
+// adds the partial tiles of a split layer and applies the epilogue (gemm.hip)
+hipError_t launch_split_finish(const float *partial, const float *ssq_part, const Epilogue &e, int split,
+                               const GemmArgs &a, hipStream_t s);
+// the tile configurations (gemm_tiles_*.hip)
+hipError_t dispatch_narrow(int tile, const GemmArgs &a, hipStream_t s, int split);  // 1-5
+hipError_t dispatch_wide(int tile, const GemmArgs &a, hipStream_t s, int split);    // 6-10
+hipError_t dispatch_tall(int tile, const GemmArgs &a, hipStream_t s, int split);    // 11-14
+hipError_t prepare_tall();  // their function attributes, once per device
+
+}  // namespace sf

@@ -22,6 +22,13 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// one 16-byte operand unit; ONCE: nothing else of the launch reads it, so the caches need not keep it
+template <int ONCE>
+__device__ __forceinline__ uint4 load_unit(const uint4 *p) {
+  if constexpr (ONCE) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)));
+  return *p;
+}
+
 // One RoPE pair (x[e], x[e + hd/2]) turned by the angle whose (cos, sin) is cs.  Explicit fused
 // multiply-adds: every kernel that rotates must round the same way.
 __device__ __forceinline__ void rope_pair(float a, float b, float2 cs, float &lo, float &hi) {
@@ -134,7 +141,6 @@ hipError_t gemm_prepare_device();
 int gemm_num_tiles();
 int gemm_tile_rows(int tile);
 GemmConfig gemm_heuristic(int M, int plan_M, int N, int K, size_t ws_bytes);
-bool gemm_config_fits(const GemmConfig &c, const GemmArgs &a);  // split-K partials fit a.ws?
 // bf16 weights are consumed in MFMA-operand-packed form (see gemm.hip); fp32 weights stay row-major
 size_t packed_weight_bytes(int N, int K, int dtype);
 hipError_t launch_pack_weight(const void *w, void *packed, int N, int K, int glu, const void *col_gain, int dtype,
