@@ -50,21 +50,7 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restri
     store8(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * (N >> 1) + col, r, e.vec);
     return;
   }
-  const size_t o = (size_t)row * N + col;
-  if (e.bias) {
-    float bv[8];
-    load8(e.bias + col, bv, e.vec);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] += bv[i];
-  }
-  if (e.residual) {
-    float res[8];
-    if (e.res_f32) load8(reinterpret_cast<const float *>(e.residual) + o, res, e.vec);
-    else load8(reinterpret_cast<const bf16_t *>(e.residual) + o, res, e.vec);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] += res[i];
-  }
-  store_row8(e, row, col, N, r);
+  finish_row8(e, row, col, N, r);
 }
 
 // row-major [N][K] -> packed units; one thread per 16-byte operand register
@@ -305,6 +291,10 @@ hipError_t launch_pack_weight(const void *w, void *packed, int N, int K, int glu
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s) {
+  if (a.tile <= 0 && a.split <= 0 && !a.am_val) {
+    const int columns = gemm_stream_columns(std::max(a.plan_M, a.M), a.N, a.K, a.glu);
+    if (columns) return launch_gemm_stream(a, columns, s);
+  }
   GemmConfig c = {a.tile, a.am_val ? 1 : a.split};  // arg-max partials: one workgroup owns a tile's whole K range
   if (c.tile <= 0 || c.split <= 0) {
     const GemmConfig h = gemm_heuristic(a.M, a.plan_M > 0 ? a.plan_M : a.M, a.N, a.K, a.ws ? a.ws_bytes : 0);

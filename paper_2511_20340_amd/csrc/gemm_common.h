@@ -105,6 +105,45 @@ inline bool plan_fits(const Plan &p, int BM, const void *ws, size_t ws_bytes) {
   return ws && ws_bytes >= GEMM_SSQ_BYTES + p.partial_bytes && ssq_bytes <= GEMM_SSQ_BYTES;
 }
 
+// The rest of a row's epilogue for 8 finished sums: bias, residual, outputs
+__device__ __forceinline__ void finish_row8(const Epilogue &e, int row, int col, int N, float (&r)[8]) {
+  const size_t o = (size_t)row * N + col;
+  if (e.bias) {
+    float bv[8];
+    load8(e.bias + col, bv, e.vec);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] += bv[i];
+  }
+  if (e.residual) {
+    float res[8];
+    if (e.res_f32) load8(reinterpret_cast<const float *>(e.residual) + o, res, e.vec);
+    else load8(reinterpret_cast<const bf16_t *>(e.residual) + o, res, e.vec);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] += res[i];
+  }
+  store_row8(e, row, col, N, r);
+}
+
+inline Epilogue make_epilogue(const GemmArgs &a) {
+  const uintptr_t all = (uintptr_t)a.bias | (uintptr_t)a.residual | (uintptr_t)a.y | (uintptr_t)a.y2 | (uintptr_t)a.hooks;
+  return Epilogue{(const bf16_t *)a.bias, a.residual, a.y, (bf16_t *)a.y2, (bf16_t *)a.hooks, a.am_val, a.am_idx,
+                  a.hook_mask, a.hook_q, a.hook_qmax, a.am_stride, a.out_f32, a.res_f32, a.glu, (all & 15) == 0};
+}
+
+// Weights of a layer with one M-tile are read once per launch; from this size on they leave the caches alone
+// (non-temporal loads stream faster from HBM, and a model of such layers does not fit the memory-side cache from one
+// step to the next anyway).  5 rows: 28672 x 4096 47 -> 41 us, 128256 x 4096 183 -> 160, 4096 x 14336 26.6 -> 24.0,
+// 4096 x 4096 (34 MB) 13.1 -> 11.8; below it the cached loads are the faster ones: 3072 x 2048 (13 MB) 8.9 against 9.8.
+constexpr size_t ONCE_BYTES = 24u << 20;
+
+// PIPE: issue order of the plain kernel, PIPE_NORM: of the one with the fused norm
+inline bool weights_once(const GemmArgs &a, int tiles_m) { return tiles_m == 1 && (size_t)a.N * a.K * 2 >= ONCE_BYTES; }
+
+// The streaming kernel for a handful of rows (gemm_stream.hip): columns per workgroup where a layer planned for plan_M
+// rows should run on it, else 0
+int gemm_stream_columns(int plan_M, int N, int K, int glu);
+hipError_t launch_gemm_stream(const GemmArgs &a, int columns, hipStream_t s);
+
 // adds the partial tiles of a split layer and applies the epilogue (gemm.hip)
 hipError_t launch_split_finish(const float *partial, const float *ssq_part, const Epilogue &e, int split,
                                const GemmArgs &a, hipStream_t s);

@@ -484,13 +484,6 @@ hipError_t ensure_lds() {
   return err;
 }
 
-// Weights of a layer with one M-tile are read once per launch; from this size on they leave the caches alone
-// (non-temporal loads stream faster from HBM, and a model of such layers does not fit the memory-side cache from one
-// step to the next anyway).  5 rows: 28672 x 4096 47 -> 41 us, 128256 x 4096 183 -> 160, 4096 x 14336 26.6 -> 24.0,
-// 4096 x 4096 (34 MB) 13.1 -> 11.8; below it the cached loads are the faster ones: 3072 x 2048 (13 MB) 8.9 against 9.8.
-constexpr size_t ONCE_BYTES = 24u << 20;
-
-// PIPE: issue order of the plain kernel, PIPE_NORM: of the one with the fused norm
 template <int TM, int TN, int R, int OCC, int NW, int PIPE = 0, int PIPE_NORM = PIPE>
 hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split) {
   constexpr int BM = TM * 32, BN = NW * TN * 32;
@@ -504,9 +497,7 @@ hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split) {
   if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;
   if (a.am_val && a.am_parts_out) *a.am_parts_out = p.tiles_n;
   static_assert((size_t)2 * BM * LDK * sizeof(bf16_t) >= (size_t)NW * BM * 8, "arg-max partials fit the activation tile");
-  const Epilogue e{(const bf16_t *)a.bias, a.residual, a.y, (bf16_t *)a.y2, (bf16_t *)a.hooks, a.am_val, a.am_idx,
-                   a.hook_mask, a.hook_q, a.hook_qmax, a.am_stride, a.out_f32, a.res_f32, a.glu,
-                   (((uintptr_t)a.bias | (uintptr_t)a.residual | (uintptr_t)a.y | (uintptr_t)a.y2 | (uintptr_t)a.hooks) & 15) == 0};
+  const Epilogue e = make_epilogue(a);
   if (lds > 64 * 1024) {
     const hipError_t err = ensure_lds<TM, TN, R, OCC, NW, PIPE, PIPE_NORM>();
     if (err != hipSuccess) return err;
@@ -515,7 +506,7 @@ hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split) {
     kernel<<<grid, block, lds, s>>>((const bf16_t *)a.x, (const uint4 *)a.w, e, a.M, a.N, a.K, p.tiles_m, p.tiles_n,
                                     p.split_k, p.kt_per_split, partial, a.norm_eps, ssq_part);
   };
-  const bool once = p.tiles_m == 1 && (size_t)a.N * a.K * 2 >= ONCE_BYTES;
+  const bool once = weights_once(a, p.tiles_m);
   if constexpr (TM <= 5) {
     if (once) launch(a.fused_norm ? &gemm_ring_kernel<TM, TN, R, OCC, NW, 1, PIPE_NORM, 1>
                                   : &gemm_ring_kernel<TM, TN, R, OCC, NW, 0, PIPE, 1>);
