@@ -15,11 +15,11 @@ extern "C" {
  * workspace makes the launch fail with SF_EHIP. host. */
 sf_status sf_tune_linear(sf_ctx *ctx, int32_t tile, int32_t split_k);
 int32_t sf_linear_num_tiles(void);
-/* The automatic choice of the tiled kernel for a bf16 linear layer of M rows whose weight [N][K] is also used with up
- * to plan_M >= M rows (layers of a handful of rows may run on the streaming kernel instead, which has no tile or split
- * to choose; a forced tile or split always means the tiled one): *split_k is the same for every M <= plan_M (so a row's result does not depend on
- * the rows batched with it), *tile follows M; *tile_rows = rows per workgroup of that tile.  Pure
- * host arithmetic, no GPU needed.  host pointers. */
+/* The automatic choice among the ring kernel's tiles (1-14) for a bf16 linear layer of M rows whose weight [N][K] is also
+ * used with up to plan_M >= M rows: *split_k is the same for every M <= plan_M (so a row's result does not depend on the
+ * rows batched with it), *tile follows M; *tile_rows = rows per workgroup of that tile.  A launch with nothing forced keeps
+ * this split but may take one of the block kernel's tiles (15 and up), and layers of a handful of rows may run on the
+ * streaming kernel, which has no tile or split to choose.  Pure host arithmetic, no GPU needed.  host pointers. */
 sf_status sf_linear_config(int32_t M, int32_t plan_M, int32_t N, int32_t K, size_t workspace_bytes,
                            int32_t *tile, int32_t *split_k, int32_t *tile_rows);
 /* Force the attention's split-KV chunk size in 32-key tiles (>= 16) for this context; 0 = automatic. host. */

@@ -72,15 +72,19 @@ constexpr int TURN_STRIDE = 40;
 // Split K (split_k > 1): partial tile and row sums go to the workspace as rows of [split][M][N] and [split][M], and
 // split_finish_kernel does the rest.
 //
-// scratch: LDS the main loop no longer needs, at least NW * BM * 8 (arg-max partials) and NW * 128 * TURN_STRIDE bytes.
-template <int TM, int TN, int NW = 4>
+// The NW waves stand in WM rows of NW / WM; a wave holds TM x TN tiles, block row (wave / (NW / WM)) * TM first.
+// nb0: the wave's first 32-column block.
+//
+// scratch: LDS the main loop no longer needs, at least NW * TM * 32 * 8 (arg-max partials) and NW * 128 * TURN_STRIDE bytes.
+template <int TM, int TN, int NW = 4, int WM = 1>
 __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogue &e, int M, int N, int split_k,
                                             float *__restrict__ partial, int tn, int ks, int m0, int nb0,
                                             void *scratch, float *sS = nullptr, float *__restrict__ ssq_part = nullptr,
                                             int K = 1, float eps = 0.f) {
-  constexpr int BM = TM * 32;
+  constexpr int BM = WM * TM * 32, WN = NW / WM;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ln = lane & 31, lh = lane >> 5;
+  const int a_w = WM == 1 ? 0 : wave / WN * TM;  // this wave's first 32-row block
 
   // A lane holds one column of 16 rows of every 32x32 tile; stored from there, an element is a 2- or 4-byte store
   // of its own, and those stores cost more than the K loop of a short layer (160 x 2048 x 512 on 160-row tiles:
@@ -111,7 +115,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
       constexpr int a = decltype(i_c)::value / TN, b = decltype(i_c)::value % TN;
       float v[16];
       transpose(acc[a][b], t_col, v, 8);
-      const int row = m0 + a * 32 + t_row, col = (nb0 + b) * 32 + t_col;
+      const int row = m0 + (a_w + a) * 32 + t_row, col = (nb0 + b) * 32 + t_col;
       float *o = partial + ((size_t)ks * M + row) * N + col;
       if (row < M && col < N) store8(o, reinterpret_cast<const float(&)[8]>(v[0]), 1);
       if (row < M && col + 8 < N) store8(o + 8, reinterpret_cast<const float(&)[8]>(v[8]), 1);
@@ -124,8 +128,9 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   if (e.am_val) {
     // Arg-max partials of this workgroup's column tile: per row the largest accumulator and the lowest
     // column that holds it.  Columns past N and NaN never take part.
-    float *s_val = reinterpret_cast<float *>(scratch);       // [NW][BM]
-    int32_t *s_idx = reinterpret_cast<int32_t *>(s_val + NW * BM);
+    float *s_val = reinterpret_cast<float *>(scratch);       // [WN][BM]
+    int32_t *s_idx = reinterpret_cast<int32_t *>(s_val + WN * BM);
+    const int w_n = WM == 1 ? wave : wave % WN;
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -148,8 +153,8 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
           }
         }
         if (ln == 0) {
-          s_val[wave * BM + a * 32 + c_row(v, lh)] = best_v;
-          s_idx[wave * BM + a * 32 + c_row(v, lh)] = best_i;
+          s_val[w_n * BM + (a_w + a) * 32 + c_row(v, lh)] = best_v;
+          s_idx[w_n * BM + (a_w + a) * 32 + c_row(v, lh)] = best_i;
         }
       }
     __syncthreads();
@@ -157,7 +162,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
       float bv = s_val[tid];
       int32_t bi = s_idx[tid];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) {  // waves hold ascending column ranges
+      for (int w = 1; w < WN; ++w) {  // waves hold ascending column ranges
         const float v = s_val[w * BM + tid];
         const int32_t i = s_idx[w * BM + tid];
         if (i != INT32_MAX && (bi == INT32_MAX || v > bv)) { bv = v; bi = i; }
@@ -171,7 +176,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   __syncthreads();  // row factors are in place; the other waves are done with the LDS this one is about to write
   auto scale_row = [&](int a, float (&v)[16]) __attribute__((always_inline)) {
     if (!sS) return;
-    const float f = sS[a * 32 + t_row];
+    const float f = sS[(a_w + a) * 32 + t_row];
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] *= f;
   };
@@ -181,7 +186,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
     const int F = N >> 1;
     static_for<TM * TN>([&](auto i_c) {
       constexpr int a = decltype(i_c)::value / TN, b = decltype(i_c)::value % TN;
-      const int col = (nb0 + b) * 16 + (lane & 1) * 8, row = m0 + a * 32 + t_row;
+      const int col = (nb0 + b) * 16 + (lane & 1) * 8, row = m0 + (a_w + a) * 32 + t_row;
       float v[16];
       transpose(acc[a][b], (lane & 1) * 8, v, 16);
       scale_row(a, v);
@@ -197,7 +202,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   // buffer itself): one exposed round trip per group.  A wave with up to five tiles forms one group, taller ones
   // go five, the tallest (no registers to spare) two tiles at a time.
   auto load_residual = [&](int a, int b, float (&res)[16]) __attribute__((always_inline)) {
-    const int row = min(m0 + a * 32 + t_row, M - 1);
+    const int row = min(m0 + (a_w + a) * 32 + t_row, M - 1);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const size_t o = (size_t)row * N + min((nb0 + b) * 32 + t_col + j * 8, N - 8);
@@ -210,7 +215,7 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
     float v[16];
     transpose(c, t_col, v, 8);
     scale_row(a, v);
-    const int row = m0 + a * 32 + t_row;
+    const int row = m0 + (a_w + a) * 32 + t_row;
     if (row >= M) return;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
