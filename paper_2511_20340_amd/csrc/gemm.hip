@@ -99,15 +99,15 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 // 6-8 % faster with it, also inside whole steps; the 320-row kernel with the fused norm measured 3 % faster
 // alone but 3.7 % slower as the gate/up product inside whole steps, so the fused-norm kernels keep the
 // compiler's order (seventh argument).
-// 15-22: the block kernel (gemm_block.h); on a layer that it does not take they stand for tile 10.
-constexpr int N_TILES = 22, N_RING_TILES = 14, N_MODEL_TILES = 10;
-constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5};
+// 15-25: the block kernel (gemm_block.h); on a layer that it does not take they stand for tile 10.
+constexpr int N_TILES = 25, N_RING_TILES = 14, N_MODEL_TILES = 10;
+constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1};
 
 hipError_t dispatch(int tile, const GemmArgs &a, hipStream_t s, int split) {
   if (tile >= 1 && tile <= 5) return dispatch_narrow(tile, a, s, split);
   if (tile >= 6 && tile <= 10) return dispatch_wide(tile, a, s, split);
   if (tile <= N_RING_TILES) return dispatch_tall(tile, a, s, split);
-  if (!block_takes(tile, a.M, a.N, a.K, a.am_val != nullptr)) return dispatch(10, a, s, split);
+  if (!block_takes(tile, a.M, a.N, a.K, split, a.am_val != nullptr)) return dispatch(10, a, s, split);
   return dispatch_block(tile, a, s, split);
 }
 
@@ -254,50 +254,51 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
 
 // What a launch of a layer takes on MI355X, in us; the measured side of the choice below.  A compute unit works through its
 // workgroups one after the other (`least`: how many it takes to keep it busy), each a fixed part and a part per 64
-// positions of K (with the fused norm a little more); the weights have to come from memory, which overlaps all but a
-// fifth of the shorter of the two; a split adds the second launch and its partial rows.  All tiles of both kernels x
-// splits 1 to 8 were measured on 329 shapes (the 1B, 8B and 14B layers and heads at 32 to 2304 rows, weights cold, medians
-// of interleaved repeats) and the constants fitted to them: 4.7 % rms.
+// positions of K (with the fused norm a little more); the weights have to come from memory, which overlaps a good half of
+// the shorter of the two; a split adds the second launch and its partial rows, unless groups of waves share it.  The tiles
+// of both kernels x splits 1 to 8 were measured on 440 shapes (the 1B, 8B and 14B layers and heads at 40 to 2304 rows,
+// weights cold, medians of interleaved repeats) and the constants fitted to them: 4.8 % rms.  (Tile 20's norm by hand: its
+// waves have one row block, and the squares of one chunk wait for each other.)
 struct TileCost {
-  int bm, bn;
+  int bm, bn, groups;
   float slice, fixed, least, norm;
 };
 constexpr TileCost TILE_COST[N_TILES + 1] = {
     {},
-    {32, 128, 0.259f, 1.0f, 0.91f, 0.000f}, {64, 128, 0.321f, 2.0f, 1.28f, 0.018f}, {96, 128, 0.410f, 3.0f, 1.11f, 0.033f},
-    {128, 128, 0.522f, 2.8f, 1.09f, 0.051f}, {160, 128, 0.663f, 3.2f, 1.06f, 0.050f}, {64, 256, 0.560f, 2.7f, 1.10f, 0.000f},
-    {96, 256, 0.735f, 6.4f, 0.95f, 0.022f}, {128, 256, 0.895f, 4.9f, 0.91f, 0.033f}, {160, 256, 1.142f, 5.4f, 0.98f, 0.076f},
-    {160, 256, 1.142f, 5.4f, 0.98f, 0.076f}, {320, 256, 2.120f, 3.7f, 0.98f, 0.315f}, {256, 256, 1.646f, 4.2f, 0.94f, 0.289f},
-    {224, 256, 1.588f, 5.5f, 0.99f, 0.085f}, {192, 256, 1.197f, 7.2f, 0.93f, 0.090f}, {320, 256, 1.743f, 3.7f, 0.95f, 0.213f},
-    {256, 256, 1.345f, 4.6f, 0.95f, 0.226f}, {192, 256, 1.055f, 5.2f, 0.92f, 0.138f}, {128, 256, 0.771f, 5.7f, 0.88f, 0.075f},
-    {128, 64, 0.308f, 1.7f, 1.10f, 0.044f}, {64, 64, 0.219f, 0.9f, 0.96f, 0.048f}, {160, 64, 0.409f, 3.3f, 0.99f, 0.084f},
-    {160, 128, 0.575f, 5.0f, 0.95f, 0.126f},
+    {32, 128, 1, 0.241f, 1.2f, 1.19f, 0.000f}, {64, 128, 1, 0.304f, 2.0f, 1.27f, 0.018f}, {96, 128, 1, 0.385f, 3.2f, 1.11f, 0.034f},
+    {128, 128, 1, 0.493f, 2.9f, 1.09f, 0.045f}, {160, 128, 1, 0.636f, 3.0f, 1.06f, 0.044f}, {64, 256, 1, 0.540f, 2.7f, 1.10f, 0.002f},
+    {96, 256, 1, 0.708f, 5.7f, 0.96f, 0.026f}, {128, 256, 1, 0.849f, 4.1f, 0.94f, 0.044f}, {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f},
+    {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f}, {320, 256, 1, 2.072f, 2.4f, 0.96f, 0.333f}, {256, 256, 1, 1.593f, 3.3f, 0.94f, 0.302f},
+    {224, 256, 1, 1.560f, 4.4f, 0.95f, 0.095f}, {192, 256, 1, 1.167f, 6.0f, 0.92f, 0.096f}, {320, 256, 1, 1.691f, 2.6f, 0.86f, 0.230f},
+    {256, 256, 1, 1.317f, 3.2f, 0.84f, 0.232f}, {192, 256, 1, 1.027f, 3.7f, 0.84f, 0.143f}, {128, 256, 1, 0.744f, 4.5f, 0.90f, 0.081f},
+    {128, 64, 1, 0.293f, 1.7f, 1.12f, 0.041f}, {64, 64, 1, 0.199f, 1.1f, 1.12f, 0.140f}, {160, 64, 1, 0.392f, 3.2f, 0.97f, 0.081f},
+    {160, 128, 1, 0.548f, 4.9f, 0.91f, 0.117f}, {64, 64, 2, 0.469f, 0.2f, 0.63f, 0.083f}, {32, 64, 4, 0.737f, 0.0f, 0.52f, 0.089f},
+    {32, 64, 2, 0.348f, 0.1f, 0.95f, 0.038f},
 };
 double cost_us(int M, int N, int K, GemmConfig c, int norm) {
   const TileCost &t = TILE_COST[c.tile];
   const int KT = (K + BK - 1) / BK, kps = (KT + c.split - 1) / c.split, split = (KT + kps - 1) / kps;
-  const int tiles_m = (M + t.bm - 1) / t.bm, units = (N + t.bn - 1) / t.bn * split;
+  const int tiles_m = (M + t.bm - 1) / t.bm, units = (N + t.bn - 1) / t.bn * (t.groups > 1 ? 1 : split);
   const int per_cu = ((units + XCDS - 1) / XCDS * tiles_m + 31) / 32;  // 32 compute units in the busiest XCD
   const double cu = std::max((double)per_cu, (double)t.least) * ((t.slice + (norm ? t.norm : 0.f)) * kps + t.fixed);
-  const double mem = (double)N * K * 2 / 4.86e6;
-  const double second = split > 1 ? 3.0 + (double)M * N * 4 * split / 2.49e6 : 0.0;
-  return 1.4 + std::max(cu, mem) + 0.2 * std::min(cu, mem) + second;
+  const double mem = (double)N * K * 2 / 7.22e6;
+  const double second = split > 1 && t.groups == 1 ? 2.5 + (double)M * N * 4 * split / 2.27e6 : 0.0;
+  return 1.4 + std::max(cu, mem) + 0.44 * std::min(cu, mem) + second;
 }
 
-// The tile for a layer of more than 96 rows whose split is decided: what the rules above pick for the ring kernel, its
-// smallest tile, or one of the block kernel's, whichever cost_us puts first.  Over the measured shapes it is 1.08 times as
-// fast as the rules above alone, and never more than 5 % slower.  (With the split free as well it would be 1.09 times as
-// fast; but then a layer's sums change their order with the fitted constants.)  Up to 160 rows the ring kernel, which then
-// reads large weights past the caches, is up to 7 % better than its formula; up to 96 rows (latency counts, not
-// throughput) the formula misjudges more than it gains.
+// The tile for a layer of more than 32 rows whose split is decided: what the rules above pick for the ring kernel, or one
+// of the block kernel's, whichever cost_us puts first.  Over the measured shapes it is 1.09 times as fast as the rules
+// above alone, 1.6 % slower than the fastest tile of each shape and nowhere more than 8 % slower than the rules alone.
+// (The split stays what the rules say: it fixes the order of a layer's sums.)  Up to 160 rows the ring kernel, which then
+// reads large weights past the caches, is up to 5 % better than its formula.
 GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, int norm, bool am) {
   GemmConfig best = pick(M, N, K, ws_bytes, split);
-  if (M <= 96) return best;
-  double best_us = cost_us(M, N, K, best, norm) * (M <= 160 ? 0.93 : 1.0);
-  for (int tile = 1; tile <= N_TILES; tile = tile == 1 ? N_RING_TILES + 1 : tile + 1) {
-    if (tile > 1 && !block_takes(tile, M, N, K, am)) continue;
+  if (M <= 32) return best;
+  double best_us = cost_us(M, N, K, best, norm) * (M <= 160 ? 0.95 : 1.0);
+  for (int tile = N_RING_TILES + 1; tile <= N_TILES; ++tile) {
+    if (!block_takes(tile, M, N, K, split, am)) continue;
     const Plan p = make_plan(M, N, K, TILE_COST[tile].bm, TILE_COST[tile].bn, split);
-    if (!plan_fits(p, TILE_COST[tile].bm, (const void *)1, ws_bytes)) continue;
+    if (block_groups(tile) == 1 && !plan_fits(p, TILE_COST[tile].bm, (const void *)1, ws_bytes)) continue;
     const double us = cost_us(M, N, K, {tile, split}, norm);
     if (us < best_us) { best = {tile, split}; best_us = us; }
   }

@@ -12,8 +12,13 @@ namespace sf {
 //   20   64 x  64       2 x 2      4, 2
 //   21  160 x  64       5 x 1      5, 1
 //   22  160 x 128       5 x 2      4, 1
-// Measured and left out, as these eight are within 0.3 % of all sixteen over the measured shapes: 256 x 128, 160 x 256 and
-// 64 x 256 (eight waves), 160 x 128, 128 x 128, 96 x 128, 64 x 128 and 32 x 128 (four).
+// K shared by groups of waves (layers whose K is split that often, see gemm_block_kernel):
+//   23   64 x  64       2 x 2, 2 groups   4, 1
+//   24   32 x  64       1 x 2, 4 groups   3, 1
+//   25   32 x  64       1 x 2, 2 groups   3, 2
+// Measured and left out, as these are within 0.5 % of all of them over the measured shapes: 256 x 128, 160 x 256 and
+// 64 x 256 (eight waves), 160 x 128, 128 x 128, 96 x 128, 64 x 128 and 32 x 128 (four); 64 x 64 in 4 groups, 128 x 64 and
+// 64 x 128 in 2, 32 x 128 in 4, 32 x 32 in 8.
 hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split) {
   switch (tile) {
     case 15: return run_block<2, 4, 5, 2, 2>(a, s, split);
@@ -24,6 +29,9 @@ hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split)
     case 20: return run_block<2, 2, 1, 1, 4>(a, s, split);
     case 21: return run_block<5, 1, 1, 2, 5>(a, s, split);
     case 22: return run_block<5, 2, 1, 2, 4>(a, s, split);
+    case 23: return run_block<2, 2, 1, 1, 4, 2>(a, s, split);
+    case 24: return run_block<1, 2, 1, 1, 3, 4>(a, s, split);
+    case 25: return run_block<1, 2, 1, 1, 3, 2>(a, s, split);
     default: return hipErrorInvalidValue;
   }
 }
@@ -37,12 +45,19 @@ hipError_t prepare_block() {
   if (err == hipSuccess) err = ensure_block_lds<2, 2, 1, 1, 4>();
   if (err == hipSuccess) err = ensure_block_lds<5, 1, 1, 2, 5>();
   if (err == hipSuccess) err = ensure_block_lds<5, 2, 1, 2, 4>();
+  if (err == hipSuccess) err = ensure_block_lds<2, 2, 1, 1, 4, 2>();
+  if (err == hipSuccess) err = ensure_block_lds<1, 2, 1, 1, 3, 4>();
+  if (err == hipSuccess) err = ensure_block_lds<1, 2, 1, 1, 3, 2>();
   return err;
 }
 
-// Whole slices of K; 32-bit byte offsets into both operands; arg-max partials are kept per 128 columns at the finest.
-bool block_takes(int tile, int M, int N, int K, bool am) {
-  if (tile < 15 || tile > 22 || (am && tile >= 19 && tile <= 21)) return false;
+int block_groups(int tile) { return tile == 24 ? 4 : tile == 23 || tile == 25 ? 2 : 1; }
+
+// Whole slices of K; 32-bit byte offsets into both operands; arg-max partials are kept per 128 columns at the finest; a
+// tile with groups takes the layers whose K is split that often.
+bool block_takes(int tile, int M, int N, int K, int split, bool am) {
+  if (tile < 15 || tile > 25 || (am && tile >= 19 && tile != 22)) return false;
+  if (block_groups(tile) > 1 && make_plan(M, N, K, 32, 32, split).split_k != block_groups(tile)) return false;
   const size_t limit = (size_t)1 << 32;
   return K % BK == 0 && (size_t)M * K * 2 < limit && (size_t)((N + 31) / 32) * K * 64 < limit;
 }

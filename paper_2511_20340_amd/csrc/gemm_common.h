@@ -153,8 +153,9 @@ hipError_t dispatch_wide(int tile, const GemmArgs &a, hipStream_t s, int split);
 hipError_t dispatch_tall(int tile, const GemmArgs &a, hipStream_t s, int split);    // 11-14
 hipError_t prepare_tall();  // their function attributes, once per device
 // the block kernel's (gemm_block.hip)
-hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-22
+hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-25
 hipError_t prepare_block();
-bool block_takes(int tile, int M, int N, int K, bool am);  // whether that tile can run such a layer
+int block_groups(int tile);  // groups of waves that share a split K inside a workgroup (1: none)
+bool block_takes(int tile, int M, int N, int K, int split, bool am);  // whether that tile can run such a layer
 
 }  // namespace sf

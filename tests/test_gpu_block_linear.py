@@ -11,7 +11,7 @@ from gpu_common import dev, engine_only, rel_err, to_np
 
 pytestmark = pytest.mark.gpu
 
-BLOCK_TILES = range(15, 23)
+BLOCK_TILES = range(15, 26)
 RING_TILE = 2
 
 
@@ -43,7 +43,7 @@ def test_block_linear(M, N, K):
         y = eng.sf_op_linear(xd, None, out_f32=True, packed=plain)
         return y, r, eng.sf_op_rmsnorm_linear(xd, gd, None, out_f32=True, packed=folded)
     try:
-        for split in (1, 3):
+        for split in (1, 2, 3, 4):
             want = [t.clone() for t in outputs(RING_TILE, split)]
             assert rel_err(to_np(want[0]), ref) < 1e-5
             assert rel_err(to_np(want[2]), ref_norm) < 5e-3     # weight * gain is rounded to bf16 once
