@@ -113,11 +113,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const TI *__restrict__ X, 
 // cos/sin of pos * theta^(-2i/hd), evaluated in double so that large positions stay exact to fp32.
 // One extra workgroup (when `order` is given) ranks the sequences by descending length, ties by
 // index: order[rank] = b.  The attention kernel starts the longest sequences first, which evens out
-// the tail of a ragged batch.
+// the tail of a ragged batch.  From place pair_from on (if not 0) the order is turned round.
 // A second table (table2: n_q2 rows per sequence at positions kv_len[b] + r) can be filled by the same launch.
 __global__ void rope_table_kernel(float2 *__restrict__ table, const int32_t *__restrict__ kv_len,
                                   const int32_t *__restrict__ n_new, int B, int n_q, int half, int pos_mode,
-                                  double log2_theta, int32_t *__restrict__ order, int32_t *__restrict__ dev_err,
+                                  double log2_theta, int32_t *__restrict__ order, int pair_from, int32_t *__restrict__ dev_err,
                                   int len_upper, int cap, float2 *__restrict__ table2, int n_q2) {
   if (dev_err && blockIdx.x == 0) {
     // the launch grids of this step were sized from the host's bound: say so if a length breaks it
@@ -140,7 +140,7 @@ __global__ void rope_table_kernel(float2 *__restrict__ table, const int32_t *__r
         const int other = kv_len[j];
         rank += (other > mine || (other == mine && j < b)) ? 1 : 0;
       }
-      order[rank] = b;
+      order[pair_from && rank >= pair_from ? pair_from + B - 1 - rank : rank] = b;
     }
     return;
   }
@@ -316,7 +316,7 @@ hipError_t launch_rope_table(const RopeArgs &a, hipStream_t s) {
   const int half = a.hd / 2;
   const int n = a.B * (a.n_q + (a.table2 ? a.n_q2 : 0)) * half;
   rope_table_kernel<<<(n + 255) / 256 + (a.order ? 1 : 0), 256, 0, s>>>(a.table, a.kv_len, a.n_new, a.B, a.n_q, half,
-                                                                        a.pos_mode, log2((double)a.theta), a.order,
+                                                                        a.pos_mode, log2((double)a.theta), a.order, a.pair_from,
                                                                         a.dev_err, a.len_upper, a.cap, a.table2, a.n_q2);
   return hipGetLastError();
 }

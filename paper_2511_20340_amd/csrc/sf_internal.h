@@ -174,7 +174,8 @@ struct RopeArgs {
   float2 *table;         // [M][hd/2] cos,sin scratch
   float2 *table2 = nullptr;  // optional second table of the same launch: n_q2 rows per sequence at kv_len[b] + r
   int n_q2 = 0;
-  int32_t *order;        // optional [B]: filled with the sequences in descending kv_len order
+  int32_t *order;        // optional [B]: filled with the sequences in descending kv_len order ...
+  int pair_from;         // ... but from this place on (0: nowhere) in ascending order
   // optional: a sticky word that collects SF_DEVERR_* bits when a device-side length contradicts what the
   // host promised (len_upper >= every kv_len, kv_len + n_q <= cap)
   int32_t *dev_err = nullptr;
