@@ -103,11 +103,14 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 constexpr int N_TILES = 25, N_RING_TILES = 14, N_MODEL_TILES = 10;
 constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1};
 
+// the block kernel's direct loads move 16 bytes at a time; the ring kernel takes rows at any address
+bool rows_aligned(const GemmArgs &a) { return (uintptr_t)a.x % 16 == 0; }
+
 hipError_t dispatch(int tile, const GemmArgs &a, hipStream_t s, int split) {
   if (tile >= 1 && tile <= 5) return dispatch_narrow(tile, a, s, split);
   if (tile >= 6 && tile <= 10) return dispatch_wide(tile, a, s, split);
   if (tile <= N_RING_TILES) return dispatch_tall(tile, a, s, split);
-  if (!block_takes(tile, a.M, a.N, a.K, split, a.am_val != nullptr)) return dispatch(10, a, s, split);
+  if (!block_takes(tile, a.M, a.N, a.K, split, a.am_val != nullptr) || !rows_aligned(a)) return dispatch(10, a, s, split);
   return dispatch_block(tile, a, s, split);
 }
 
@@ -360,7 +363,7 @@ hipError_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s) {
   GemmConfig c = {a.tile, am ? 1 : a.split};  // arg-max partials: one workgroup owns a tile's whole K range
   if (a.tile <= 0 && a.split <= 0) {
     const int split = am ? 1 : gemm_heuristic(a.M, std::max(a.plan_M, a.M), a.N, a.K, ws_bytes).split;
-    c = pick_any(a.M, a.N, a.K, ws_bytes, split, a.fused_norm, am);
+    c = rows_aligned(a) ? pick_any(a.M, a.N, a.K, ws_bytes, split, a.fused_norm, am) : pick(a.M, a.N, a.K, ws_bytes, split);
   } else if (c.tile <= 0 || c.split <= 0) {
     const GemmConfig h = gemm_heuristic(a.M, a.plan_M > 0 ? a.plan_M : a.M, a.N, a.K, ws_bytes);
     if (c.split <= 0) c.split = h.split;
