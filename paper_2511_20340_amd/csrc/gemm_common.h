@@ -136,7 +136,6 @@ inline Epilogue make_epilogue(const GemmArgs &a) {
 // 4096 x 4096 (34 MB) 13.1 -> 11.8; below it the cached loads are the faster ones: 3072 x 2048 (13 MB) 8.9 against 9.8.
 constexpr size_t ONCE_BYTES = 24u << 20;
 
-// PIPE: issue order of the plain kernel, PIPE_NORM: of the one with the fused norm
 inline bool weights_once(const GemmArgs &a, int tiles_m) { return tiles_m == 1 && (size_t)a.N * a.K * 2 >= ONCE_BYTES; }
 
 // The streaming kernel for a handful of rows (gemm_stream.hip): columns per workgroup where a layer planned for plan_M

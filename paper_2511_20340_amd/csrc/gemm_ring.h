@@ -489,6 +489,7 @@ hipError_t ensure_lds() {
   return err;
 }
 
+// PIPE: issue order of the plain kernel, PIPE_NORM: of the one with the fused norm
 template <int TM, int TN, int R, int OCC, int NW, int PIPE = 0, int PIPE_NORM = PIPE>
 hipError_t run_ring(const GemmArgs &a, hipStream_t s, int split) {
   constexpr int BM = TM * 32, BN = NW * TN * 32;
