@@ -340,14 +340,16 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(
   for (int c0 = 0; c0 < sc; c0 += 32) {
     const int n = min(32, sc - c0);
     const float2 mine = c0 == 0 ? first : lane < n ? ml[(c0 + lane) * step] : make_float2(NEG_INF, 0.f);
-    const float f_c = __builtin_amdgcn_exp2f(mine.x - m_use), l_c = mine.y * f_c;  // of chunk c0 + lane
+    const float f_c = __builtin_amdgcn_exp2f(mine.x - m_use);  // of chunk c0 + lane
     for (int c = 0; c < n; c += AHEAD) {
       if (c0 + c > 0) request(c0 + c, sc - 1);
 #pragma unroll
       for (int u = 0; u < AHEAD; ++u)
         if (c + u < n) {
-          l += __shfl(l_c, c + u, 32);
-          o += x[u] * __shfl(f_c, c + u, 32);
+          // one rounding per chunk for the row's sum as for its outputs: the products are not rounded by themselves
+          const float f = __shfl(f_c, c + u, 32);
+          l = fmaf(__shfl(mine.y, c + u, 32), f, l);
+          o += x[u] * f;
         }
     }
   }
