@@ -15,13 +15,26 @@ extern "C" {
  * workspace makes the launch fail with SF_EHIP. host. */
 sf_status sf_tune_linear(sf_ctx *ctx, int32_t tile, int32_t split_k);
 int32_t sf_linear_num_tiles(void);
-/* The automatic choice among the ring kernel's tiles (1-14) for a bf16 linear layer of M rows whose weight [N][K] is also
- * used with up to plan_M >= M rows: *split_k is the same for every M <= plan_M (so a row's result does not depend on the
- * rows batched with it), *tile follows M; *tile_rows = rows per workgroup of that tile.  A launch with nothing forced keeps
- * this split but may take one of the block kernel's tiles (15 and up), and layers of a handful of rows may run on the
- * streaming kernel, which has no tile or split to choose.  Pure host arithmetic, no GPU needed.  host pointers. */
+/* The K split of a bf16 linear layer of M rows whose weight [N][K] is also used with up to plan_M >= M rows, and the ring
+ * kernel's tile (1-14) for it: *split_k is the same for every M <= plan_M (so a row's result does not depend on the rows
+ * batched with it), *tile follows M; *tile_rows = rows per workgroup of that tile.  A launch with nothing forced keeps this
+ * split and may run on another kernel, with the same bits: sf_linear_choice.  Pure host arithmetic, no GPU needed.  host
+ * pointers. */
 sf_status sf_linear_config(int32_t M, int32_t plan_M, int32_t N, int32_t K, size_t workspace_bytes,
                            int32_t *tile, int32_t *split_k, int32_t *tile_rows);
+/* What a launch of that layer runs on.  flags: SF_LINEAR_*.  In: *tile and *split_k as given to sf_tune_linear (0: automatic).
+ * Out: *kernel SF_KERNEL_*, *tile its tile (streaming kernel: 16-column tiles per wave), *split_k the split.  A block tile
+ * forced on a layer that the block kernel does not take comes back as ring tile 10, which is what runs.  Pure host
+ * arithmetic.  host pointers. */
+enum { SF_KERNEL_RING = 0, SF_KERNEL_BLOCK = 1, SF_KERNEL_STREAM = 2 };
+enum {
+  SF_LINEAR_GLU = 1,       /* the SwiGLU gate (N = 2F)                      */
+  SF_LINEAR_NORM = 2,      /* the fused RMSNorm                             */
+  SF_LINEAR_ARGMAX = 4,    /* arg-max partials (LM head)                    */
+  SF_LINEAR_UNALIGNED = 8  /* x does not start on a 16-byte boundary        */
+};
+sf_status sf_linear_choice(int32_t M, int32_t plan_M, int32_t N, int32_t K, size_t workspace_bytes, int32_t flags,
+                           int32_t *kernel, int32_t *tile, int32_t *split_k);
 /* Force the attention's split-KV chunk size in 32-key tiles (>= 16) for this context; 0 = automatic. host. */
 sf_status sf_tune_attention(sf_ctx *ctx, int32_t chunk_tiles);
 

@@ -9,6 +9,8 @@ LIB_PATH = os.environ.get("SF_LIB") or os.path.join(HERE, "libspecformer.so")
 SF_OK, SF_EINVAL, SF_ECAPACITY, SF_ESTATE, SF_EHIP, SF_EUNSUPPORTED = range(6)
 SF_BF16, SF_F32 = 0, 1
 SF_MASK_CAUSAL, SF_MASK_BIDIR = 0, 1
+SF_KERNEL_RING, SF_KERNEL_BLOCK, SF_KERNEL_STREAM = range(3)
+SF_LINEAR_GLU, SF_LINEAR_NORM, SF_LINEAR_ARGMAX, SF_LINEAR_UNALIGNED = 1, 2, 4, 8
 SF_DRAFT_TWO_STAGE = 16   # OR-ed into sf_draft_step's mask
 KERNEL_CLASSES = ["linear", "attention", "attention_combine", "rmsnorm", "rope_kv_append", "silu_mul",
                   "embed_hook", "argmax", "accept"]
@@ -22,7 +24,7 @@ EXPORTS = [
     "sf_op_silu_mul", "sf_argmax_workspace_bytes", "sf_op_argmax", "sf_op_argmax_noalloc", "sf_op_accept", "sf_strerror",
     "sf_last_hip_error", "sf_version",
     # include/specformer_aux.h
-    "sf_tune_linear", "sf_linear_num_tiles", "sf_linear_config", "sf_tune_attention", "sf_calib_copy",
+    "sf_tune_linear", "sf_linear_num_tiles", "sf_linear_config", "sf_linear_choice", "sf_tune_attention", "sf_calib_copy",
     "sf_profile_begin", "sf_profile_end",
 ]
 
@@ -106,6 +108,7 @@ def lib():
     L.sf_linear_num_tiles.argtypes = []
     L.sf_linear_num_tiles.restype = i32
     L.sf_linear_config.argtypes = [i32, i32, i32, i32, C.c_size_t, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
+    L.sf_linear_choice.argtypes = [i32, i32, i32, i32, C.c_size_t, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     L.sf_tune_attention.argtypes = [vp, i32]
     L.sf_op_rmsnorm.argtypes = [vp, vp, vp, vp, i32, i32, i32, vp]
     L.sf_op_rope_kv_append.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp, vp, sz, vp]

@@ -655,6 +655,23 @@ sf_status sf_linear_config(int32_t M, int32_t plan_M, int32_t N, int32_t K, size
   return SF_OK;
 }
 
+sf_status sf_linear_choice(int32_t M, int32_t plan_M, int32_t N, int32_t K, size_t workspace_bytes, int32_t flags,
+                           int32_t *kernel, int32_t *tile, int32_t *split_k) {
+  if (M < 1 || plan_M < M || N < 1 || K < 1 || !kernel || !tile || !split_k) return SF_EINVAL;
+  if (*tile < 0 || *tile > gemm_num_tiles() || *split_k < 0 || *split_k > 64) return SF_EINVAL;
+  GemmArgs a{};  // the choice looks at which pointers are set and at the alignment of x, never behind them
+  float set;
+  a.x = (const void *)(uintptr_t)(flags & SF_LINEAR_UNALIGNED ? 2 : 0);
+  a.M = M; a.N = N; a.K = K; a.plan_M = plan_M;
+  a.ws = workspace_bytes ? &set : nullptr; a.ws_bytes = workspace_bytes;
+  a.glu = (flags & SF_LINEAR_GLU) != 0; a.fused_norm = (flags & SF_LINEAR_NORM) != 0;
+  a.am_val = flags & SF_LINEAR_ARGMAX ? &set : nullptr;
+  a.tile = *tile; a.split = *split_k;
+  const GemmChoice c = gemm_choose(a);
+  *kernel = c.kernel; *tile = c.tile; *split_k = c.split;
+  return SF_OK;
+}
+
 sf_status sf_op_linear(const sf_ctx *c, const void *x, const void *w, const void *bias, const void *residual,
                        void *y, int32_t M, int32_t N, int32_t K, int32_t out_f32, void *workspace,
                        size_t workspace_bytes, void *stream) {

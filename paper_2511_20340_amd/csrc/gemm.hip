@@ -106,14 +106,6 @@ constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7,
 // the block kernel's direct loads move 16 bytes at a time; the ring kernel takes rows at any address
 bool rows_aligned(const GemmArgs &a) { return (uintptr_t)a.x % 16 == 0; }
 
-hipError_t dispatch(int tile, const GemmArgs &a, hipStream_t s, int split) {
-  if (tile >= 1 && tile <= 5) return dispatch_narrow(tile, a, s, split);
-  if (tile >= 6 && tile <= 10) return dispatch_wide(tile, a, s, split);
-  if (tile <= N_RING_TILES) return dispatch_tall(tile, a, s, split);
-  if (!block_takes(tile, a.M, a.N, a.K, split, a.am_val != nullptr) || !rows_aligned(a)) return dispatch(10, a, s, split);
-  return dispatch_block(tile, a, s, split);
-}
-
 // Heuristic choice (used when nothing was measured for the shape).  What the sweeps on MI355X
 // showed: a compute unit draws at most ~20-40 B/clk from L2, so both the weight re-reads of the
 // M-tiles and the activation re-reads of the column tiles count; ~224 workgroups fill the chip;
@@ -353,23 +345,31 @@ hipError_t launch_pack_weight(const void *w, void *packed, int N, int K, int glu
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s) {
-  if (a.tile <= 0 && a.split <= 0 && !a.am_val) {
-    const int columns = gemm_stream_columns(std::max(a.plan_M, a.M), a.N, a.K, a.glu);
-    if (columns) return launch_gemm_stream(a, columns, s);
-  }
+GemmChoice gemm_choose(const GemmArgs &a) {
   const size_t ws_bytes = a.ws ? a.ws_bytes : 0;
   const bool am = a.am_val != nullptr;
   GemmConfig c = {a.tile, am ? 1 : a.split};  // arg-max partials: one workgroup owns a tile's whole K range
   if (a.tile <= 0 && a.split <= 0) {
     const int split = am ? 1 : gemm_heuristic(a.M, std::max(a.plan_M, a.M), a.N, a.K, ws_bytes).split;
+    const int tiles = am ? 0 : gemm_stream_tiles(a.M, a.N, a.K, split, a.glu);
+    if (tiles) return {GEMM_STREAM, tiles, split};
     c = rows_aligned(a) ? pick_any(a.M, a.N, a.K, ws_bytes, split, a.fused_norm, am) : pick(a.M, a.N, a.K, ws_bytes, split);
   } else if (c.tile <= 0 || c.split <= 0) {
     const GemmConfig h = gemm_heuristic(a.M, a.plan_M > 0 ? a.plan_M : a.M, a.N, a.K, ws_bytes);
     if (c.split <= 0) c.split = h.split;
     if (c.tile <= 0) c.tile = c.split == h.split ? h.tile : pick(a.M, a.N, a.K, ws_bytes, c.split).tile;
   }
-  return dispatch(c.tile, a, s, c.split);
+  if (c.tile > N_RING_TILES && (!block_takes(c.tile, a.M, a.N, a.K, c.split, am) || !rows_aligned(a))) c.tile = 10;
+  return {c.tile > N_RING_TILES ? GEMM_BLOCK : GEMM_RING, c.tile, c.split};
+}
+
+hipError_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s) {
+  const GemmChoice c = gemm_choose(a);
+  if (c.kernel == GEMM_STREAM) return launch_gemm_stream(a, c.tile, c.split, s);
+  if (c.kernel == GEMM_BLOCK) return dispatch_block(c.tile, a, s, c.split);
+  if (c.tile <= 5) return dispatch_narrow(c.tile, a, s, c.split);
+  if (c.tile <= 10) return dispatch_wide(c.tile, a, s, c.split);
+  return dispatch_tall(c.tile, a, s, c.split);
 }
 
 }  // namespace sf

@@ -138,10 +138,10 @@ constexpr size_t ONCE_BYTES = 24u << 20;
 
 inline bool weights_once(const GemmArgs &a, int tiles_m) { return tiles_m == 1 && (size_t)a.N * a.K * 2 >= ONCE_BYTES; }
 
-// The streaming kernel for a handful of rows (gemm_stream.hip): columns per workgroup where a layer planned for plan_M
-// rows should run on it, else 0
-int gemm_stream_columns(int plan_M, int N, int K, int glu);
-hipError_t launch_gemm_stream(const GemmArgs &a, int columns, hipStream_t s);
+// The streaming kernel for a handful of rows (gemm_stream.hip): 16-column tiles per wave (1 or 2) where a layer whose K is
+// cut into `split` parts should run on it, else 0
+int gemm_stream_tiles(int M, int N, int K, int split, int glu);
+hipError_t launch_gemm_stream(const GemmArgs &a, int tiles, int split, hipStream_t s);
 
 // adds the partial tiles of a split layer and applies the epilogue (gemm.hip)
 hipError_t launch_split_finish(const float *partial, const float *ssq_part, const Epilogue &e, int split,

@@ -134,6 +134,11 @@ inline int gemm_argmax_parts(int N) { return (N + 127) / 128; }
 struct GemmConfig {
   int tile, split;
 };
+// which kernel a bf16 layer runs on, with which tile (the streaming kernel: column tiles per wave) and split
+enum { GEMM_RING = 0, GEMM_BLOCK = 1, GEMM_STREAM = 2 };
+struct GemmChoice {
+  int kernel, tile, split;
+};
 constexpr size_t GEMM_PARTIAL_BYTES = 96u * 1024 * 1024;
 constexpr size_t GEMM_SSQ_BYTES = 1024 * 1024;  // split-K: per-split row sums of squares of the fused norm
 size_t gemm_workspace_bytes(int M_max);
@@ -141,6 +146,7 @@ hipError_t gemm_prepare_device();
 int gemm_num_tiles();
 int gemm_tile_rows(int tile);
 GemmConfig gemm_heuristic(int M, int plan_M, int N, int K, size_t ws_bytes);
+GemmChoice gemm_choose(const GemmArgs &a);  // host arithmetic only
 // bf16 weights are consumed in MFMA-operand-packed form (see gemm.hip); fp32 weights stay row-major
 size_t packed_weight_bytes(int N, int K, int dtype);
 hipError_t launch_pack_weight(const void *w, void *packed, int N, int K, int glu, const void *col_gain, int dtype,

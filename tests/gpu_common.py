@@ -1,5 +1,7 @@
 """Shared helpers of the GPU parity tests: build an oracle and an engine from the same seeded
 synthetic inputs.  The HIP library and the oracle never see each other; only this test code does."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -40,3 +42,13 @@ def make_pair(shape: synth.ModelShape, B, cap, k, seed, std=0.02, round_bf16=Fal
 
 def engine_only(shape, B, cap, k):
     return Engine(shape.cfg(), B, cap, k)
+
+
+LINEAR_WS = 97 << 20     # bytes of a full split-K workspace
+
+
+def linear_choice(M, N, K, flags=0, plan=None, tile=0, split=0, ws=LINEAR_WS):
+    """(kernel, tile, split) that a bf16 linear layer of M rows runs on; tile, split: as forced with sf_tune_linear."""
+    k, t, s = C.c_int32(), C.c_int32(tile), C.c_int32(split)
+    sfb.check(sfb.lib().sf_linear_choice(M, plan or M, N, K, ws, flags, C.byref(k), C.byref(t), C.byref(s)), "sf_linear_choice")
+    return k.value, t.value, s.value

@@ -6,6 +6,7 @@ import ctypes as C
 
 import pytest
 
+from gpu_common import linear_choice
 from paper_2511_20340_amd import binding as sfb
 
 WS = (64 << 10) + (96 << 20)
@@ -115,3 +116,38 @@ def test_large_m_choice_leaves_the_small_batches_alone():
     # the 1B (160 rows) and 8B batch-64 (320 rows) workloads keep their rule-based choices
     assert [config(160, 160, N, K)[:2] for N, K in SHAPES[:4]] == [(1, 2), (1, 2), (3, 1), (2, 4)]
     assert [config(320, 320, N, K)[:2] for N, K in SHAPES[5:9]] == [(2, 1), (1, 1), (10, 1), (5, 4)]
+
+
+# ---- what a launch runs on (sf_linear_choice) ---------------------------------------------------------------------------
+FLAGS = [0, sfb.SF_LINEAR_NORM, sfb.SF_LINEAR_GLU | sfb.SF_LINEAR_NORM]
+
+
+@pytest.mark.parametrize("plan", [5, 32, 160, 320, 640, 1280, 4096])
+def test_launches_keep_the_planned_split(plan):
+    """Whatever kernel a layer of M rows runs on, its K is cut as planned, so its sums have the same order for every M."""
+    for N, K in SHAPES + [(512, 1000), (1024, 24576), (4104, 2056), (2048, 16384)]:
+        want = config(plan, plan, N, K)[1]
+        for M in sorted({1, 8, 9, 16, 17, 31, 32, 33, plan // 5, plan // 2, plan - 1, plan}):
+            for flags in FLAGS if N % 64 == 0 else FLAGS[:2]:
+                if 1 <= M <= plan:
+                    kernel, tile, split = linear_choice(M, N, K, flags, plan)
+                    assert split == want, (M, plan, N, K, flags)
+                    if kernel == sfb.SF_KERNEL_STREAM:
+                        assert split in (1, 2, 4, 8) and tile in (1, 2)
+
+
+def test_layers_of_a_handful_of_rows_stream():
+    stream = lambda M, N, K, flags=0: linear_choice(M, N, K, flags)[0] == sfb.SF_KERNEL_STREAM
+    # one user's step: QKV, O, down and gate/up of the 1B, 8B and 14B models
+    for N, K in [(3072, 2048), (2048, 2048), (2048, 8192), (6144, 4096), (4096, 4096), (4096, 14336), (7168, 5120), (5120, 5120)]:
+        assert stream(5, N, K, sfb.SF_LINEAR_NORM) and stream(1, N, K)
+    assert stream(5, 16384, 2048, sfb.SF_LINEAR_GLU | sfb.SF_LINEAR_NORM)
+    # rows that are read by every workgroup beside a long K, few columns under a long K: measured slower
+    # (us streaming / ring): 32 x 2048 x 8192 21.7 / 14.1, 32 x 512 x 24576 52 / 17, 24 x 1024 x 16384 34 / 15
+    for M, N, K in [(32, 2048, 8192), (32, 512, 24576), (24, 1024, 16384), (16, 64, 24576), (24, 2048, 16384)]:
+        assert not stream(M, N, K) and not stream(M, N, K, sfb.SF_LINEAR_GLU)
+    # more rows: only instead of a second launch, all workgroups at once, K up to 2048
+    assert stream(96, 512, 1000) and stream(64, 2048, 2048) and not stream(64, 4096, 4096) and not stream(320, 2048, 2048)
+    assert not stream(5, 152064, 5120, sfb.SF_LINEAR_ARGMAX) and not stream(64, 1024, 1024)
+    # nowhere to put partial tiles: K is not split, whatever runs
+    assert linear_choice(5, 2048, 2048, ws=0)[2] == 1
