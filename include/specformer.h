@@ -129,7 +129,7 @@ typedef struct {
 /* Context.  host.  max_B <= 4096, 0 <= max_k <= 127 (decoding uses a handful of slots; blocks of up to 128
  * rows serve chunked prefill: sf_verify_step over prompt tokens + sf_accept_commit with force_len).  target and draft must agree on every field
  * but n_layers (draft: 1).  SF_EUNSUPPORTED unless head_dim in {64,128} for SF_BF16 (any multiple
- * of 8 up to 256 for SF_F32), d_model % 8 == 0, d_ffn % 32 == 0, (n_q_heads * head_dim) % 32 == 0. */
+ * of 8 up to 256 for SF_F32), d_model % 8 == 0, d_ffn % 32 == 0, (n_q_heads * head_dim) % 32 == 0; any vocab. */
 sf_status sf_create(const sf_model_cfg *target, const sf_model_cfg *draft, int32_t max_B, int32_t max_k,
                     sf_ctx **out);
 sf_status sf_destroy(sf_ctx *ctx);

@@ -364,6 +364,8 @@ GemmChoice gemm_choose(const GemmArgs &a) {
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs &a, hipStream_t s) {
+  // the epilogues move 8 columns at a time; of rows that end within 8 (the vocabulary of an LM head) they know y alone
+  if (a.N % 8 && (!a.am_val || a.bias || a.residual || a.y2 || a.hooks || a.glu)) return hipErrorInvalidValue;
   const GemmChoice c = gemm_choose(a);
   if (c.kernel == GEMM_STREAM) return launch_gemm_stream(a, c.tile, c.split, s);
   if (c.kernel == GEMM_BLOCK) return dispatch_block(c.tile, a, s, c.split);

@@ -20,7 +20,7 @@ struct Epilogue {
   int32_t *am_idx;       // ... and its column
   int hook_mask, hook_q, hook_qmax, am_stride;
   int out_f32, res_f32, glu;
-  int vec;               // every pointer above is 16-byte aligned
+  int vec;               // every pointer above is 16-byte aligned and so are the rows (N % 8 == 0)
 };
 
 // 8 consecutive elements as floats; vec: every pointer of the launch is 16-byte aligned
@@ -45,30 +45,34 @@ __device__ __forceinline__ void load8(const float *p, float (&v)[8], int vec) {
     for (int i = 0; i < 8; ++i) v[i] = p[i];
   }
 }
-__device__ __forceinline__ void store8(bf16_t *p, const float (&v)[8], int vec) {
+// n: elements that exist behind p (8 or more where vec)
+__device__ __forceinline__ void store8(bf16_t *p, const float (&v)[8], int vec, int n = 8) {
   if (vec) {
     u32x4 w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = pack2bf(v[2 * i], v[2 * i + 1]);
     *reinterpret_cast<u32x4 *>(p) = w;
   } else {
-    for (int i = 0; i < 8; ++i) p[i] = f2bf(v[i]);
+    for (int i = 0; i < 8; ++i)
+      if (i < n) p[i] = f2bf(v[i]);
   }
 }
-__device__ __forceinline__ void store8(float *p, const float (&v)[8], int vec) {
+__device__ __forceinline__ void store8(float *p, const float (&v)[8], int vec, int n = 8) {
   if (vec) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(p + j * 4) = f32x4{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
   } else {
-    for (int i = 0; i < 8; ++i) p[i] = v[i];
+    for (int i = 0; i < 8; ++i)
+      if (i < n) p[i] = v[i];
   }
 }
 
-// 8 finished columns of an output row: y, its bf16 copy, the hooked copies
+// 8 finished columns of an output row: y, its bf16 copy, the hooked copies.  Only y, the logits of an LM head, can have
+// rows that end within the 8.
 __device__ __forceinline__ void store_row8(const Epilogue &e, int row, int col, int N, const float (&r)[8]) {
   const size_t o = (size_t)row * N + col;
-  if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec);
-  else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec);
+  if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec, N - col);
+  else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec, N - col);
   if (e.y2) store8(e.y2 + o, r, e.vec);
   if (e.hooks) {
     const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
@@ -127,7 +131,7 @@ __device__ __forceinline__ void finish_row8(const Epilogue &e, int row, int col,
 inline Epilogue make_epilogue(const GemmArgs &a) {
   const uintptr_t all = (uintptr_t)a.bias | (uintptr_t)a.residual | (uintptr_t)a.y | (uintptr_t)a.y2 | (uintptr_t)a.hooks;
   return Epilogue{(const bf16_t *)a.bias, a.residual, a.y, (bf16_t *)a.y2, (bf16_t *)a.hooks, a.am_val, a.am_idx,
-                  a.hook_mask, a.hook_q, a.hook_qmax, a.am_stride, a.out_f32, a.res_f32, a.glu, (all & 15) == 0};
+                  a.hook_mask, a.hook_q, a.hook_qmax, a.am_stride, a.out_f32, a.res_f32, a.glu, (all & 15) == 0 && a.N % 8 == 0};
 }
 
 // Weights of a layer with one M-tile are read once per launch; from this size on they leave the caches alone
