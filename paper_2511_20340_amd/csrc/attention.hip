@@ -370,7 +370,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
                                                        const int32_t *__restrict__ kv_len, float *__restrict__ O,
                                                        int n_q, int Hq, int Hkv, int hd, int cap, int mode,
                                                        float scale) {
-  __shared__ float sq[256], sc[CK], red[8];
+  __shared__ __attribute__((aligned(16))) float sq[256];
+  __shared__ float sc[CK], red[8];
   __shared__ f32x4 so[256];
   const int hq = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = hq / (Hq / Hkv);
@@ -401,16 +402,17 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
     if (lane == 0) red[wave] = mx;
     __syncthreads();
     const float m_new = fmaxf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), m_run);
+    const float m_use = m_new == NEG_INF ? 0.f : m_new;  // no finite score yet: keep exp finite
     float sum = 0.f;
     for (int x = tid; x < nk; x += 256) {
-      const float p = expf(sc[x] - m_new);
+      const float p = expf(sc[x] - m_use);
       sc[x] = p;
       sum += p;
     }
     for (int w = 32; w; w >>= 1) sum += __shfl_xor(sum, w);
     if (lane == 0) red[4 + wave] = sum;
     __syncthreads();
-    const float alpha = expf(m_run - m_new);
+    const float alpha = expf(m_run - m_use);
     l_run = l_run * alpha + ((red[4] + red[5]) + (red[6] + red[7]));
     m_run = m_new;
     o *= alpha;

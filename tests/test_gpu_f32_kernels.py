@@ -62,3 +62,21 @@ def test_attention_f32_head_sizes(mode, Hq, Hkv, hd, nq):
     eng.sf_kv_import(kc, "dk"); eng.sf_kv_import(vc, "dv")
     out = eng.sf_op_attention(dev(q, "f32"), eng.dk, eng.dv, torch.from_numpy(lens).cuda(), nq, mode)
     assert rel_err(to_np(out), ref) < 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("first", [512, 700])
+def test_attention_chunk_without_a_finite_score(dtype, first):
+    """Keys whose scores are all -inf weigh nothing, also where they fill the first chunk of keys whole."""
+    B, Hq, Hkv, hd, nq, cap = 2, 4, 2, 64, 3, 1152
+    lens = np.array([1100, 800], np.int32)
+    q, kc, vc = synth.random_qkv(37, B, nq, Hq, Hkv, hd, cap, dtype)
+    q = np.abs(q) + 0.25
+    ref = sfo.attention(synth.to_bf16_values(q), np.concatenate([kc[:, :, first:], kc[:, :, :first]], 2),
+                        np.concatenate([vc[:, :, first:], vc[:, :, :first]], 2), lens - first, sfb.SF_MASK_CAUSAL)
+    kc[:, :, :first] = -np.inf
+    eng = engine_only(synth.ModelShape("t", 1, Hq * hd, Hq, Hkv, hd, 256, 512, dtype), B, cap, nq - 1)
+    eng.sf_kv_import(kc, "dk"); eng.sf_kv_import(vc, "dv")
+    out = to_np(eng.sf_op_attention(dev(synth.to_bf16_values(q), dtype), eng.dk, eng.dv, torch.from_numpy(lens).cuda(), nq,
+                                    sfb.SF_MASK_CAUSAL))
+    assert rel_err(out, ref) < (1e-5 if dtype == "f32" else 2e-2)      # the tolerances of the other attention tests
