@@ -18,15 +18,18 @@
 namespace sf {
 namespace {
 
-constexpr int MAX_WAVES = 16, UNROLL = 4;  // K chunks of 16 positions a wave keeps in flight
+constexpr int MAX_WAVES = 16;
 
-template <int TM, int TN>
+__device__ __forceinline__ f32x4 keep(f32x4 v, bool yes) { return yes ? v : f32x4{0.f, 0.f, 0.f, 0.f}; }
+
+// U: chunks of 16 positions a wave has in flight
+template <int TM, int TN, int U>
 __global__ __launch_bounds__(64 * MAX_WAVES) void linear_f32_kernel(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ gain, float eps,
     const float *__restrict__ bias, const float *residual, float *Y, float *__restrict__ hooks, int hook_mask,
     int hook_q, int hook_qmax, int glu, int M, int N, int K, int chunks_per_wave) {
   extern __shared__ float part[];  // [waves][TM * TN][16][16] partial tiles, then [waves][16 * TM] sums of squares
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
   const int r = lane & 15, g = lane >> 4;
   const int m0 = blockIdx.y * 16 * TM;
   const int F = N >> 1;
@@ -48,41 +51,49 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void linear_f32_kernel(
   for (int b = 0; b < TN; ++b)  // with the gate, tile 1 holds the up rows of tile 0's gate rows
     wp[b] = W + (size_t)(min(n0 + (glu ? 0 : b * 16) + r, n_end - 1) + (glu ? b * F : 0)) * K;
   const int c0 = wave * chunks_per_wave, c1 = min(c0 + chunks_per_wave, (K + 15) / 16);
-  for (int c = c0; c < c1; c += UNROLL) {
-    f32x4 xa[UNROLL][TM], wb[UNROLL][TN], gv[UNROLL];
+  const int whole = min(c1, K >> 4);  // the chunks before this one lie inside K
+  auto product = [&](f32x4 (&x)[TM], const f32x4 (&w)[TN], const f32x4 &gains) __attribute__((always_inline)) {
+    if (gain) {
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
+      for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          ssq[a] += x[a][j] * x[a][j];
+          x[a][j] *= gains[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[a][j], w[b][j], acc[a][b], 0, 0, 0);
+  };
+  for (int c = c0; c < c1; c += U) {
+    f32x4 xa[U][TM], wb[U][TN], gv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       // lane (r, g) takes positions k .. k+3 of its row; product j of the four pairs element j of every lane
-      const int k = (c + u) * 16 + g * 4, kk = min(k, K - 4);
-      const bool live = c + u < c1 && k < K;
+      const int kk = min((c + u) * 16 + g * 4, K - 4);
 #pragma unroll
-      for (int a = 0; a < TM; ++a) {
-        xa[u][a] = *reinterpret_cast<const f32x4 *>(xp[a] + kk);
-        if (!live) xa[u][a] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+      for (int a = 0; a < TM; ++a) xa[u][a] = *reinterpret_cast<const f32x4 *>(xp[a] + kk);
 #pragma unroll
       for (int b = 0; b < TN; ++b) wb[u][b] = *reinterpret_cast<const f32x4 *>(wp[b] + kk);
-      if (gain) gv[u] = *reinterpret_cast<const f32x4 *>(gain + kk);
+      gv[u] = gain ? *reinterpret_cast<const f32x4 *>(gain + kk) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    if (c + U > whole) {  // past the share or past K: zeros on all sides (a zero times an infinity is none)
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      if (gain) {
+      for (int u = 0; u < U; ++u) {
+        const bool in = c + u < c1 && (c + u) * 16 + g * 4 < K;
 #pragma unroll
-        for (int a = 0; a < TM; ++a)
+        for (int a = 0; a < TM; ++a) xa[u][a] = keep(xa[u][a], in);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            ssq[a] += xa[u][a][j] * xa[u][a][j];
-            xa[u][a][j] *= gv[u][j];
-          }
+        for (int b = 0; b < TN; ++b) wb[u][b] = keep(wb[u][b], in);
+        gv[u] = keep(gv[u], in);
       }
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-          for (int b = 0; b < TN; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[u][a][j], wb[u][b][j], acc[a][b], 0, 0, 0);
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) product(xa[u], wb[u], gv[u]);
   }
 
   constexpr int TILE = TM * TN * 256;
@@ -147,10 +158,13 @@ hipError_t run(const GemmArgs &a, hipStream_t s) {
   const int cols = a.glu ? a.N / 2 : a.N, bn = a.glu ? 16 : 16 * TN;
   const dim3 grid((cols + bn - 1) / bn, (a.M + 16 * TM - 1) / (16 * TM));
   const size_t lds = (size_t)waves * (TM * TN * 256 + 16 * TM) * sizeof(float);
-  linear_f32_kernel<TM, TN><<<grid, 64 * waves, lds, s>>>(
-      (const float *)a.x, (const float *)a.w, (const float *)a.gain_f32, a.norm_eps, (const float *)a.bias,
-      (const float *)a.residual, (float *)a.y, (float *)a.hooks, a.hook_mask, a.hook_q, a.hook_qmax, a.glu, a.M, a.N,
-      a.K, per_wave);
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, 64 * waves, lds, s>>>(
+        (const float *)a.x, (const float *)a.w, (const float *)a.gain_f32, a.norm_eps, (const float *)a.bias,
+        (const float *)a.residual, (float *)a.y, (float *)a.hooks, a.hook_mask, a.hook_q, a.hook_qmax, a.glu, a.M, a.N,
+        a.K, per_wave);
+  };
+  if (per_wave <= 2) launch(&linear_f32_kernel<TM, TN, 2>); else launch(&linear_f32_kernel<TM, TN, 4>);
   return hipGetLastError();
 }
 

@@ -80,3 +80,18 @@ def test_attention_chunk_without_a_finite_score(dtype, first):
     out = to_np(eng.sf_op_attention(dev(synth.to_bf16_values(q), dtype), eng.dk, eng.dv, torch.from_numpy(lens).cuda(), nq,
                                     sfb.SF_MASK_CAUSAL))
     assert rel_err(out, ref) < (1e-5 if dtype == "f32" else 2e-2)      # the tolerances of the other attention tests
+
+
+# K: one chunk and a half, 32.5 chunks over 8 waves, 65 over 16, 130 over 16 (shares that end off the four chunks in flight)
+@pytest.mark.parametrize("M", [1, 17])
+@pytest.mark.parametrize("K", [24, 520, 1040, 2080])
+def test_linear_f32_infinite_weight_stays_in_its_column(M, K):
+    g = synth.rng(38, K)
+    x = np.abs(g.standard_normal((M, K), dtype=np.float32)) + 0.5
+    w = g.standard_normal((40, K), dtype=np.float32)
+    at = {5 * i: k for i, k in enumerate((0, K // 2, K - 1, K - 9, K // 4 + 3, K // 8, K // 16))}
+    for n, k in at.items():
+        w[n, k] = np.inf
+    y = to_np(engine_only(shape_for(2, 2, 64), 1, 64, 1).sf_op_linear(dev(x, "f32"), dev(w, "f32")))
+    cols = np.array(sorted(at))
+    assert np.all(y[:, cols] == np.inf) and np.all(np.isfinite(np.delete(y, cols, 1)))
