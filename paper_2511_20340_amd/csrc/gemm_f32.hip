@@ -146,14 +146,146 @@ __global__ __launch_bounds__(64 * MAX_WAVES) void linear_f32_kernel(
   }
 }
 
+// Many rows: the same sums without LDS.  A workgroup of 2 x 2 waves owns 128 rows x 64 columns (with the gate 64 gate and
+// up rows of the weight); a wave takes 64 x 32 of them over the whole of K, one share after the other in wave order of the
+// kernel above, and adds a share's products to the total when the share ends: the same bits.  A fragment loaded from
+// memory is used four or two times here and once or twice there.  8192 x 2048 x 256 174 -> 111 us, 2048 x 4096 x 1024
+// 415 -> 194, 8192 x 4096 x 4096 5760 -> 2794.
+constexpr int RM = 4, RN = 2;  // 16-row and 16-column tiles of a wave
+constexpr int ROWS_BM = 2 * RM * 16, ROWS_BN = 2 * RN * 16;
+
+__global__ __launch_bounds__(256) void linear_f32_rows_kernel(
+    const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ gain, float eps,
+    const float *__restrict__ bias, const float *residual, float *Y, float *__restrict__ hooks, int hook_mask,
+    int hook_q, int hook_qmax, int glu, int M, int N, int K, int chunks_per_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.y * ROWS_BM + (wave >> 1) * RM * 16;
+  const int F = N >> 1, n_end = glu ? F : N;
+  const int n0 = (blockIdx.x * 2 + (wave & 1)) * (glu ? 16 : RN * 16);
+  const int chunks = (K + 15) / 16;
+  const float *xp[RM], *wp[RN];
+#pragma unroll
+  for (int a = 0; a < RM; ++a) xp[a] = X + (size_t)min(m0 + a * 16 + r, M - 1) * K;
+#pragma unroll
+  for (int b = 0; b < RN; ++b) wp[b] = W + (size_t)(min(n0 + (glu ? 0 : b * 16) + r, n_end - 1) + (glu ? b * F : 0)) * K;
+
+  f32x4 acc[RM][RN], sum[RM][RN];
+  float ssq[RM], sq[RM];
+#pragma unroll
+  for (int a = 0; a < RM; ++a) {
+    ssq[a] = sq[a] = 0.f;
+#pragma unroll
+    for (int b = 0; b < RN; ++b) acc[a][b] = sum[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  f32x4 xa[2][RM], wb[2][RN], gv[2];
+  auto load = [&](int buf, int c) __attribute__((always_inline)) {
+    const int kk = min(c * 16 + g * 4, K - 4);
+#pragma unroll
+    for (int a = 0; a < RM; ++a) xa[buf][a] = *reinterpret_cast<const f32x4 *>(xp[a] + kk);
+#pragma unroll
+    for (int b = 0; b < RN; ++b) wb[buf][b] = *reinterpret_cast<const f32x4 *>(wp[b] + kk);
+    gv[buf] = gain ? *reinterpret_cast<const f32x4 *>(gain + kk) : f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  int left = chunks_per_wave;  // chunks of the current share
+  auto multiply = [&](int buf, int c) __attribute__((always_inline)) {
+    if (c * 16 + 16 > K) {
+      const bool in = c * 16 + g * 4 < K;
+#pragma unroll
+      for (int a = 0; a < RM; ++a) xa[buf][a] = keep(xa[buf][a], in);
+#pragma unroll
+      for (int b = 0; b < RN; ++b) wb[buf][b] = keep(wb[buf][b], in);
+      gv[buf] = keep(gv[buf], in);
+    }
+    if (gain) {
+#pragma unroll
+      for (int a = 0; a < RM; ++a)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          ssq[a] += xa[buf][a][j] * xa[buf][a][j];
+          xa[buf][a][j] *= gv[buf][j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int a = 0; a < RM; ++a)
+#pragma unroll
+        for (int b = 0; b < RN; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[buf][a][j], wb[buf][b][j], acc[a][b], 0, 0, 0);
+    if (--left == 0 || c == chunks - 1) {
+      left = chunks_per_wave;
+#pragma unroll
+      for (int a = 0; a < RM; ++a) {
+#pragma unroll
+        for (int b = 0; b < RN; ++b) {
+          sum[a][b] += acc[a][b];
+          acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (gain) {
+          float t = ssq[a];
+          t += __shfl_xor(t, 16);
+          t += __shfl_xor(t, 32);
+          sq[a] += t;
+          ssq[a] = 0.f;
+        }
+      }
+    }
+  };
+  load(0, 0);
+  for (int c = 0; c < chunks; c += 2) {
+    load(1, min(c + 1, chunks - 1));
+    multiply(0, c);
+    if (c + 1 == chunks) break;
+    load(0, min(c + 2, chunks - 1));
+    multiply(1, c + 1);
+  }
+
+#pragma unroll
+  for (int a = 0; a < RM; ++a) {
+    const float rinv = gain ? 1.0f / sqrtf(sq[a] / (float)K + eps) : 1.f;  // of row a * 16 + r
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float f = __shfl(rinv, g * 4 + v);
+      const int m = m0 + a * 16 + g * 4 + v;
+      if (glu) {
+        const int n = n0 + r;
+        const float x = sum[a][0][v] * f, up = sum[a][1][v] * f;
+        if (m < M && n < F) Y[(size_t)m * F + n] = x / (1.0f + expf(-x)) * up;
+        continue;
+      }
+#pragma unroll
+      for (int b = 0; b < RN; ++b) {
+        const int n = n0 + b * 16 + r;
+        if (m >= M || n >= N) continue;
+        float x = sum[a][b][v] * f;
+        if (bias) x += bias[n];
+        if (residual) x += residual[(size_t)m * N + n];
+        Y[(size_t)m * N + n] = x;
+        if (hooks) {
+          const size_t hrow = ((size_t)(m / hook_q) * hook_qmax + m % hook_q) * 4;
+#pragma unroll
+          for (int h = 1; h < 4; ++h)
+            if (hook_mask >> h & 1) hooks[(hrow + h) * N + n] = x;
+        }
+      }
+    }
+  }
+}
+
+// K's shares: two chunks or more each; K = 256 has 8, K = 512 and above 16 (8 with the gate, whose partial tiles would
+// outgrow 64 KiB); never a matter of M
+int shares_of(const GemmArgs &a) {
+  const int chunks = (a.K + 15) / 16, most = a.glu ? MAX_WAVES / 2 : MAX_WAVES;
+  int waves = 1;
+  while (waves < most && waves * 4 <= chunks) waves *= 2;
+  return waves;
+}
+
 template <int TM, int TN>
 hipError_t run(const GemmArgs &a, hipStream_t s) {
   const int chunks = (a.K + 15) / 16;
-  // two chunks or more per wave: K = 256 takes 8 waves, K = 512 and above 16 (8 with the gate, whose partial
-  // tiles would outgrow 64 KiB); never a matter of M
-  const int most = a.glu ? MAX_WAVES / 2 : MAX_WAVES;
-  int waves = 1;
-  while (waves < most && waves * 4 <= chunks) waves *= 2;
+  const int waves = shares_of(a);
   const int per_wave = (chunks + waves - 1) / waves;
   const int cols = a.glu ? a.N / 2 : a.N, bn = a.glu ? 16 : 16 * TN;
   const dim3 grid((cols + bn - 1) / bn, (a.M + 16 * TM - 1) / (16 * TM));
@@ -171,6 +303,18 @@ hipError_t run(const GemmArgs &a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
+  // From about ten workgroups of the small kernel per compute unit on, the chip is full either way and the larger tile is
+  // the faster one, unless rows fill little of it: 512 x 4096 x 1024 (4096 workgroups) 106 -> 56 us, 768 x 2048 x 256 (3072)
+  // 20.2 -> 19.2, but 512 x 2048 x 512 (2048) 26 against 31 and 33 x 32000 x 1024 86 against 93.
+  if (a.M >= 64 && (long)((a.N + 15) / 16) * ((a.M + 31) / 32) >= 2560) {
+    const int shares = shares_of(a), chunks = (a.K + 15) / 16;
+    const int cols = a.glu ? a.N / 2 : a.N, bn = a.glu ? ROWS_BN / 2 : ROWS_BN;
+    linear_f32_rows_kernel<<<dim3((cols + bn - 1) / bn, (a.M + ROWS_BM - 1) / ROWS_BM), 256, 0, s>>>(
+        (const float *)a.x, (const float *)a.w, (const float *)a.gain_f32, a.norm_eps, (const float *)a.bias,
+        (const float *)a.residual, (float *)a.y, (float *)a.hooks, a.hook_mask, a.hook_q, a.hook_qmax, a.glu, a.M, a.N,
+        a.K, (chunks + shares - 1) / shares);
+    return hipGetLastError();
+  }
   if (a.glu) return a.M <= 16 ? run<1, 2>(a, s) : run<2, 2>(a, s);
   return a.M <= 16 ? run<1, 1>(a, s) : run<2, 1>(a, s);
 }

@@ -6,6 +6,7 @@ import torch
 import synth
 from oracle import sfo
 from paper_2511_20340_amd import binding as sfb
+from paper_2511_20340_amd.engine import Engine
 
 from gpu_common import dev, engine_only, rel_err, to_np
 
@@ -95,3 +96,56 @@ def test_linear_f32_infinite_weight_stays_in_its_column(M, K):
     y = to_np(engine_only(shape_for(2, 2, 64), 1, 64, 1).sf_op_linear(dev(x, "f32"), dev(w, "f32")))
     cols = np.array(sorted(at))
     assert np.all(y[:, cols] == np.inf) and np.all(np.isfinite(np.delete(y, cols, 1)))
+
+
+# the kernel for many rows against the small one, which takes up to 63 of the same rows: tile edges in rows (128) and columns
+# (64; 32 features with the gate), a remainder of 8 columns, K of half a chunk behind 5 (2 shares) and of 16 uneven shares
+@pytest.mark.parametrize("M,N,K", [(64, 20488, 88), (1300, 1000, 1000), (4100, 320, 520), (129, 8200, 24)])
+def test_linear_f32_many_rows_give_the_bits_of_few(M, N, K):
+    assert M >= 64 and -(-N // 16) * -(-M // 32) >= 2560      # the rule's line
+    g = torch.Generator(device="cuda").manual_seed(M)
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, w, bias, res = rand(M, K), rand(N, K) * 0.05, rand(N), rand(M, N)
+    w[3, K - 1] = torch.inf
+    x[:, K - 1] = x[:, K - 1].abs() + 0.5
+    eng = engine_only(shape_for(2, 2, 64), 1, 64, 1)
+    y = res.clone()
+    eng.sf_op_linear(x, w, bias=bias, residual=y, y=y)
+    Fw = w[8:8 + (N - 8) // 64 * 64]
+    act = eng.sf_op_linear_swiglu(x, Fw)
+    exact = x.double() @ w.double().T + bias.double() + res.double()
+    finite = [n for n in range(N) if n != 3]
+    assert bool((y[:, 3] == torch.inf).all())
+    assert rel_err(to_np(y[:, finite]), exact[:, finite].cpu().numpy()) < 1e-5
+    for first in sorted({0, 63, M // 2, max(0, M - 40)}):
+        few = slice(first, min(first + 40, M))
+        r = res[few].clone()
+        eng.sf_op_linear(x[few].contiguous(), w, bias=bias, residual=r, y=r)
+        assert torch.equal(r, y[few])
+        assert torch.equal(eng.sf_op_linear_swiglu(x[few].contiguous(), Fw), act[few])
+
+
+def test_step_f32_many_rows_give_the_bits_of_few():
+    """A whole fp32 draft and verify step of 512 sequences (norm, gate, residual, hooked copies through the kernel for many
+    rows) against the same sequences eight at a time."""
+    shape, B, k, cap = synth.ModelShape("t", 2, 512, 4, 4, 128, 1024, 1024, "f32"), 512, 3, 64
+    tw, dw = synth.target_weights(shape, 3), synth.draft_weights(shape, k, 3)
+    g = synth.rng(39, 0)
+    toks = g.integers(0, shape.vocab, (B, k + 1)).astype(np.int32)
+    hooks = torch.from_numpy(g.standard_normal((B, k + 1, 4, 512), dtype=np.float32)).cuda()
+
+    def step(rows):
+        eng = Engine(shape.cfg(), len(rows), cap, k)
+        eng.bind(tw, dw)
+        eng.set_state(kv_len=np.full(len(rows), 2, np.int32), pending=toks[rows, 0], n_new=np.full(len(rows), 2, np.int32))
+        eng.hooks.copy_(hooks[rows])
+        dl = torch.empty(len(rows), k, shape.vocab, device="cuda")
+        eng.sf_draft_step(k, logits_out=dl)
+        logits, _ = eng.sf_verify_step(k, torch.from_numpy(toks[rows, 1:].copy()).cuda())
+        torch.cuda.synchronize()
+        return dl, logits.clone(), eng.hooks.clone()
+    whole = step(np.arange(B))
+    for first in (0, 256, B - 8):
+        rows = np.arange(first, first + 8)
+        for got, want in zip(whole, step(rows)):
+            assert torch.equal(got[rows], want)
