@@ -28,11 +28,11 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restri
 #pragma unroll 4
   for (int s = 0; s < split; ++s) {
     float q[8];
-    load8(p + s * step, q, 1);
+    load_n(p + s * step, q, 1);
 #pragma unroll
     for (int i = 0; i < 8; ++i) r[i] += q[i];
     if (e.glu) {
-      load8(p + s * step + 16, q, 1);
+      load_n(p + s * step + 16, q, 1);
 #pragma unroll
       for (int i = 0; i < 8; ++i) up[i] += q[i];
     }
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const float *__restri
   if (e.glu) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) r[i] = r[i] / (1.0f + __expf(-r[i])) * up[i];
-    store8(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * (N >> 1) + col, r, e.vec);
+    store_n(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * (N >> 1) + col, r, e.vec);
     return;
   }
   finish_row8(e, row, col, N, r);

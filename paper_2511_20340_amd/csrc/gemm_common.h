@@ -23,62 +23,69 @@ struct Epilogue {
   int vec;               // every pointer above is 16-byte aligned and so are the rows (N % 8 == 0)
 };
 
-// 8 consecutive elements as floats; vec: every pointer of the launch is 16-byte aligned
-__device__ __forceinline__ void load8(const bf16_t *p, float (&v)[8], int vec) {
+// W (4 or 8) consecutive elements as floats; vec: every pointer of the launch is 16-byte aligned
+template <int W>
+__device__ __forceinline__ void load_n(const bf16_t *p, float (&v)[W], int vec) {
+  typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
   if (vec) {
-    const u32x4 w = *reinterpret_cast<const u32x4 *>(p);
+    const words w = *reinterpret_cast<const words *>(p);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { v[2 * i] = __uint_as_float(w[i] << 16); v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
+    for (int i = 0; i < W / 2; ++i) { v[2 * i] = __uint_as_float(w[i] << 16); v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
   } else {
-    for (int i = 0; i < 8; ++i) v[i] = bf2f(p[i]);
+    for (int i = 0; i < W; ++i) v[i] = bf2f(p[i]);
   }
 }
-__device__ __forceinline__ void load8(const float *p, float (&v)[8], int vec) {
+template <int W>
+__device__ __forceinline__ void load_n(const float *p, float (&v)[W], int vec) {
   if (vec) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < W / 4; ++j) {
       const f32x4 q = *reinterpret_cast<const f32x4 *>(p + j * 4);
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
     }
   } else {
-    for (int i = 0; i < 8; ++i) v[i] = p[i];
+    for (int i = 0; i < W; ++i) v[i] = p[i];
   }
 }
-// n: elements that exist behind p (8 or more where vec)
-__device__ __forceinline__ void store8(bf16_t *p, const float (&v)[8], int vec, int n = 8) {
+// n: elements that exist behind p (W or more where vec)
+template <int W>
+__device__ __forceinline__ void store_n(bf16_t *p, const float (&v)[W], int vec, int n = W) {
+  typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
   if (vec) {
-    u32x4 w;
+    words w;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = pack2bf(v[2 * i], v[2 * i + 1]);
-    *reinterpret_cast<u32x4 *>(p) = w;
+    for (int i = 0; i < W / 2; ++i) w[i] = pack2bf(v[2 * i], v[2 * i + 1]);
+    *reinterpret_cast<words *>(p) = w;
   } else {
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < W; ++i)
       if (i < n) p[i] = f2bf(v[i]);
   }
 }
-__device__ __forceinline__ void store8(float *p, const float (&v)[8], int vec, int n = 8) {
+template <int W>
+__device__ __forceinline__ void store_n(float *p, const float (&v)[W], int vec, int n = W) {
   if (vec) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) *reinterpret_cast<f32x4 *>(p + j * 4) = f32x4{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
+    for (int j = 0; j < W / 4; ++j) *reinterpret_cast<f32x4 *>(p + j * 4) = f32x4{v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]};
   } else {
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < W; ++i)
       if (i < n) p[i] = v[i];
   }
 }
 
-// 8 finished columns of an output row: y, its bf16 copy, the hooked copies.  Only y, the logits of an LM head, can have
-// rows that end within the 8.
-__device__ __forceinline__ void store_row8(const Epilogue &e, int row, int col, int N, const float (&r)[8]) {
+// W finished columns of an output row: y, its bf16 copy, the hooked copies.  Only y, the logits of an LM head, can have
+// rows that end within the W.
+template <int W>
+__device__ __forceinline__ void store_row(const Epilogue &e, int row, int col, int N, const float (&r)[W]) {
   const size_t o = (size_t)row * N + col;
-  if (e.out_f32) store8(reinterpret_cast<float *>(e.y) + o, r, e.vec, N - col);
-  else store8(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec, N - col);
-  if (e.y2) store8(e.y2 + o, r, e.vec);
+  if (e.out_f32) store_n(reinterpret_cast<float *>(e.y) + o, r, e.vec, N - col);
+  else store_n(reinterpret_cast<bf16_t *>(e.y) + o, r, e.vec, N - col);
+  if (e.y2) store_n(e.y2 + o, r, e.vec);
   if (e.hooks) {
     const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
 #pragma unroll
     for (int g = 1; g < 4; ++g)
-      if (e.hook_mask >> g & 1) store8(e.hooks + (hrow + g) * N + col, r, e.vec);
+      if (e.hook_mask >> g & 1) store_n(e.hooks + (hrow + g) * N + col, r, e.vec);
   }
 }
 
@@ -114,18 +121,18 @@ __device__ __forceinline__ void finish_row8(const Epilogue &e, int row, int col,
   const size_t o = (size_t)row * N + col;
   if (e.bias) {
     float bv[8];
-    load8(e.bias + col, bv, e.vec);
+    load_n(e.bias + col, bv, e.vec);
 #pragma unroll
     for (int i = 0; i < 8; ++i) r[i] += bv[i];
   }
   if (e.residual) {
     float res[8];
-    if (e.res_f32) load8(reinterpret_cast<const float *>(e.residual) + o, res, e.vec);
-    else load8(reinterpret_cast<const bf16_t *>(e.residual) + o, res, e.vec);
+    if (e.res_f32) load_n(reinterpret_cast<const float *>(e.residual) + o, res, e.vec);
+    else load_n(reinterpret_cast<const bf16_t *>(e.residual) + o, res, e.vec);
 #pragma unroll
     for (int i = 0; i < 8; ++i) r[i] += res[i];
   }
-  store_row8(e, row, col, N, r);
+  store_row(e, row, col, N, r);
 }
 
 inline Epilogue make_epilogue(const GemmArgs &a) {

@@ -88,24 +88,37 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
 
   // A lane holds one column of 16 rows of every 32x32 tile; stored from there, an element is a 2- or 4-byte store
   // of its own, and those stores cost more than the K loop of a short layer (160 x 2048 x 512 on 160-row tiles:
-  // 20.1 us, 11.1 us this way).  So each wave turns its tiles through a private piece of LDS, one after the other,
-  // and lane l then holds 16 consecutive columns of row l / 2: residual, output and copies move in 16-byte units.
+  // 20.1 us, 11.1 us this way).  So each wave turns its tiles through a private piece of LDS, one after the other, and
+  // a lane then holds 16 / W groups of W consecutive columns: W = 4 where floats are stored (eight lanes a row, so one
+  // instruction writes whole 128-byte lines of 8 rows; with two groups of 8 columns a lane every line is left to four
+  // instructions: 4096 x 16384 x 2048 with a float output 282 us, 342 that way), W = 8 where bf16 is (four lanes a row).
+  // The two rows that a quarter of a wave reads are four apart: different halves of the banks, as for the writes.
   float *turn = reinterpret_cast<float *>(scratch) + wave * (32 * TURN_STRIDE);
-  const int t_row = lane >> 1, t_col = (lane & 1) * 16;
-  auto transpose = [&](const f32x16 &c, int col0, float (&v)[16], int step) __attribute__((always_inline)) {
+  auto unit_row = [&](int W, int u) __attribute__((always_inline)) {
+    return W == 4 ? u * 8 + (lane >> 3 & 1) * 4 + (lane >> 4) : u * 16 + (lane >> 2);
+  };
+  auto unit_col = [&](int W) __attribute__((always_inline)) { return W == 4 ? (lane & 7) * 4 : (lane & 3) * 8; };
+  auto put = [&](const f32x16 &c) __attribute__((always_inline)) {
     __builtin_amdgcn_sched_barrier(0);  // tile by tile: overlapping them would cost registers the tall tiles lack
 #pragma unroll
     for (int i = 0; i < 16; ++i) turn[c_row(i, lh) * TURN_STRIDE + ln] = c[i];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+  };
+  auto taken = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto transpose = [&](auto w_c, const f32x16 &c, float (&v)[16]) __attribute__((always_inline)) {
+    constexpr int W = decltype(w_c)::value;
+    put(c);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const f32x4 q = *reinterpret_cast<const f32x4 *>(turn + t_row * TURN_STRIDE + col0 + (j >> 1) * step + (j & 1) * 4);
+      const f32x4 q = *reinterpret_cast<const f32x4 *>(turn + unit_row(W, j / (W / 4)) * TURN_STRIDE + unit_col(W) + j % (W / 4) * 4);
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    taken();
   };
 
   if (split_k > 1) {
@@ -114,11 +127,14 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
     static_for<TM * TN>([&](auto i_c) {
       constexpr int a = decltype(i_c)::value / TN, b = decltype(i_c)::value % TN;
       float v[16];
-      transpose(acc[a][b], t_col, v, 8);
-      const int row = m0 + (a_w + a) * 32 + t_row, col = (nb0 + b) * 32 + t_col;
-      float *o = partial + ((size_t)ks * M + row) * N + col;
-      if (row < M && col < N) store8(o, reinterpret_cast<const float(&)[8]>(v[0]), 1);
-      if (row < M && col + 8 < N) store8(o + 8, reinterpret_cast<const float(&)[8]>(v[8]), 1);
+      transpose(std::integral_constant<int, 4>{}, acc[a][b], v);
+      const int col = (nb0 + b) * 32 + unit_col(4);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int row = m0 + (a_w + a) * 32 + unit_row(4, u);
+        if (row < M && col < N)
+          store_n(partial + ((size_t)ks * M + row) * N + col, reinterpret_cast<const float(&)[4]>(v[u * 4]), 1);
+      }
     });
     return;
   }
@@ -174,26 +190,32 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   }
 
   __syncthreads();  // row factors are in place; the other waves are done with the LDS this one is about to write
-  auto scale_row = [&](int a, float (&v)[16]) __attribute__((always_inline)) {
-    if (!sS) return;
-    const float f = sS[(a_w + a) * 32 + t_row];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] *= f;
-  };
   if (e.glu) {
     // SwiGLU.  The weight was packed with gate and up rows interleaved 16 by 16: columns 0-15 of a tile are gate
     // features f..f+15, columns 16-31 the matching up features.  Lane l takes 8 features of both.
     const int F = N >> 1;
+    const int t_row = lane >> 1, t_col = (lane & 1) * 8;
     static_for<TM * TN>([&](auto i_c) {
       constexpr int a = decltype(i_c)::value / TN, b = decltype(i_c)::value % TN;
-      const int col = (nb0 + b) * 16 + (lane & 1) * 8, row = m0 + (a_w + a) * 32 + t_row;
+      const int col = (nb0 + b) * 16 + t_col, row = m0 + (a_w + a) * 32 + t_row;
       float v[16];
-      transpose(acc[a][b], (lane & 1) * 8, v, 16);
-      scale_row(a, v);
+      put(acc[a][b]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 q = *reinterpret_cast<const f32x4 *>(turn + t_row * TURN_STRIDE + t_col + (j >> 1) * 16 + (j & 1) * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[j * 4 + i] = q[i];
+      }
+      taken();
+      if (sS) {
+        const float f = sS[(a_w + a) * 32 + t_row];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] *= f;
+      }
       float r[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) r[i] = v[i] / (1.0f + __expf(-v[i])) * v[8 + i];
-      if (row < M && col < F) store8(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * F + col, r, e.vec);
+      if (row < M && col < F) store_n(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * F + col, r, e.vec);
     });
     return;
   }
@@ -201,60 +223,60 @@ __device__ __forceinline__ void gemm_finish(f32x16 (&acc)[TM][TN], const Epilogu
   // The residual values of a group of tiles are requested before the group's first store (y may be the residual
   // buffer itself): one exposed round trip per group.  A wave with up to five tiles forms one group, taller ones
   // go five, the tallest (no registers to spare) two tiles at a time.
-  auto load_residual = [&](int a, int b, float (&res)[16]) __attribute__((always_inline)) {
-    const int row = min(m0 + (a_w + a) * 32 + t_row, M - 1);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const size_t o = (size_t)row * N + min((nb0 + b) * 32 + t_col + j * 8, N - 8);
-      float(&dst)[8] = reinterpret_cast<float(&)[8]>(res[j * 8]);
-      if (e.res_f32) load8(reinterpret_cast<const float *>(e.residual) + o, dst, e.vec);
-      else load8(reinterpret_cast<const bf16_t *>(e.residual) + o, dst, e.vec);
-    }
-  };
-  auto store_tile = [&](int a, int b, const f32x16 &c, const float (&res)[16]) __attribute__((always_inline)) {
-    float v[16];
-    transpose(c, t_col, v, 8);
-    scale_row(a, v);
-    const int row = m0 + (a_w + a) * 32 + t_row;
-    if (row >= M) return;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = (nb0 + b) * 32 + t_col + j * 8;
-      if (col >= N) continue;
-      float r[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) r[i] = v[j * 8 + i];
-      if (e.bias) {
-        float bv[8];
-        load8(e.bias + col, bv, e.vec);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] += bv[i];
-      }
-      if (e.residual) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] += res[j * 8 + i];
-      }
-      store_row8(e, row, col, N, r);
-    }
-  };
   // constant tile indices whatever the size of the body: an unroll pragma gives up beyond a size threshold, and a
   // run-time index into the accumulators would move them out of registers
   constexpr int MOST = TM * TN > 7 ? 2 : 5;  // tiles per group
   constexpr int AG = TN >= MOST ? 1 : (TM < MOST / TN ? TM : MOST / TN), GROUPS = (TM + AG - 1) / AG;
-  static_for<GROUPS>([&](auto g_c) {
-    constexpr int a0 = decltype(g_c)::value * AG, a1 = a0 + AG < TM ? a0 + AG : TM;
-    float res[AG][TN][16];
-    if (e.residual) {
+  auto store_all = [&](auto w_c) __attribute__((always_inline)) {
+    constexpr int W = decltype(w_c)::value, UNITS = 16 / W;
+    auto load_residual = [&](int a, int b, float (&res)[16]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < UNITS; ++u) {
+        const int row = min(m0 + (a_w + a) * 32 + unit_row(W, u), M - 1);
+        const size_t o = (size_t)row * N + min((nb0 + b) * 32 + unit_col(W), N - W);
+        float(&dst)[W] = reinterpret_cast<float(&)[W]>(res[u * W]);
+        if (e.res_f32) load_n(reinterpret_cast<const float *>(e.residual) + o, dst, e.vec);
+        else load_n(reinterpret_cast<const bf16_t *>(e.residual) + o, dst, e.vec);
+      }
+    };
+    auto store_tile = [&](int a, int b, const f32x16 &c, const float (&res)[16]) __attribute__((always_inline)) {
+      float v[16];
+      transpose(w_c, c, v);
+      const int col = (nb0 + b) * 32 + unit_col(W);
+      float bv[W];
+      if (e.bias) load_n(e.bias + min(col, N - W), bv, e.vec);
+#pragma unroll
+      for (int u = 0; u < UNITS; ++u) {
+        const int in_tile = (a_w + a) * 32 + unit_row(W, u), row = m0 + in_tile;
+        if (row >= M || col >= N) continue;
+        const float f = sS ? sS[in_tile] : 1.f;
+        float r[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+          r[i] = sS ? v[u * W + i] * f : v[u * W + i];
+          if (e.bias) r[i] += bv[i];
+          if (e.residual) r[i] += res[u * W + i];
+        }
+        store_row(e, row, col, N, r);
+      }
+    };
+    static_for<GROUPS>([&](auto g_c) {
+      constexpr int a0 = decltype(g_c)::value * AG, a1 = a0 + AG < TM ? a0 + AG : TM;
+      float res[AG][TN][16];
+      if (e.residual) {
+#pragma unroll
+        for (int a = a0; a < a1; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b) load_residual(a, b, res[a - a0][b]);
+      }
 #pragma unroll
       for (int a = a0; a < a1; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b) load_residual(a, b, res[a - a0][b]);
-    }
-#pragma unroll
-    for (int a = a0; a < a1; ++a)
-#pragma unroll
-      for (int b = 0; b < TN; ++b) store_tile(a, b, acc[a][b], res[a - a0][b]);
-  });
+        for (int b = 0; b < TN; ++b) store_tile(a, b, acc[a][b], res[a - a0][b]);
+    });
+  };
+  if (e.out_f32) store_all(std::integral_constant<int, 4>{});
+  else store_all(std::integral_constant<int, 8>{});
 }
 
 // Dynamic LDS of a workgroup: the activation double buffer, later the epilogue's transposition pieces (+ the fused

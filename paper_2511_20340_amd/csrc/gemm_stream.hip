@@ -183,7 +183,7 @@ __global__ __launch_bounds__(64 * KS * stream_groups(KS), KS <= 4 ? 2 : 4) void 
       total(c8 + 16, up);
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] = v[i] / (1.0f + __expf(-v[i])) * (up[i] * rinv);
-      if (f < (N >> 1)) store8(reinterpret_cast<bf16_t *>(e.y) + (size_t)(m0 + row) * (N >> 1) + f, v, e.vec);
+      if (f < (N >> 1)) store_n(reinterpret_cast<bf16_t *>(e.y) + (size_t)(m0 + row) * (N >> 1) + f, v, e.vec);
       continue;
     }
     const int col = n0 + c8;
