@@ -1,5 +1,6 @@
-"""The order in which a step's attention workgroups start follows the sequences' lengths (descending, or its second half
-turned round); whatever it is, a sequence's results are the same bits as in a small batch that is not ordered."""
+"""The order in which a step's attention workgroups start follows the sequences' lengths (descending, or what goes beyond one
+workgroup per compute unit turned round); whatever it is, a sequence's results are the same bits as in a small batch that is
+not ordered."""
 import numpy as np
 import pytest
 import torch
@@ -28,8 +29,8 @@ def step(rows, lens, caches, pending, draft, weights):
     return logits.clone(), eng.sf_kv_export("tk", 0).clone()
 
 
-# 8 kv heads: 264 and 512 workgroups (turned round from place 32 on), 520 (descending)
-@pytest.mark.parametrize("B", [33, 64, 65])
+# 8 kv heads: 264, 384 and 512 workgroups (turned round from place 32 on: one, 16 and 32 sequences), 520 (descending)
+@pytest.mark.parametrize("B", [33, 48, 64, 65])
 def test_order_leaves_the_results(B):
     g = synth.rng(61, B)
     weights = synth.target_weights(SHAPE, 7)

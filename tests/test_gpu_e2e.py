@@ -288,8 +288,8 @@ def test_lossless_on_the_gpu(name):
 
 def test_one_engine_switching_between_k0_and_k4():
     """Plain greedy steps (k = 0) and speculative steps (k = 4) issued through the SAME engine and
-    workspace give bit-identical logits for the same rows (the workspace layout depends on k; the
-    split-K ticket counters must survive that), and verify-block rows equal the step-by-step rows."""
+    workspace give bit-identical logits for the same rows (the workspace layout depends on k,
+    the K partition of its layers does not), and verify-block rows equal the step-by-step rows."""
     m = SLICES["8b-slice"]
     B, k, seed, cap = 6, 4, 21, 160
     lens = [40, 77, 12, 64, 100, 33]

@@ -17,8 +17,8 @@ def shape_for(Hq, Hkv, hd):
     return synth.ModelShape("t", 1, Hq * hd, Hq, Hkv, hd, 256, 512, "f32")
 
 
-# rows around the 16-row tiles (1 and 2 per workgroup), a column remainder of 8, K of one, one and a half, 16 and
-# 32.5 chunks of 16 positions (1, 1, 4 and 8 waves), and the longest K split over all waves.  K products summed in
+# rows around the 16-row tiles (1 and 2 per workgroup), a column remainder of 8, K of half a chunk of 16 positions, one and a
+# half, 16 and 32.5 (1, 1, 8 and 16 waves), and a longer K over 16 waves.  K products summed in
 # fp32 in any order: relative error below K * 2^-24 <= 1.3e-4 of the absolute sums, in practice sqrt(K) * 2^-24.
 @pytest.mark.parametrize("M", [1, 16, 17, 50])
 @pytest.mark.parametrize("N,K", [(8, 8), (24, 24), (264, 256), (40, 520), (72, 2048)])

@@ -14,7 +14,7 @@ from oracle import sfo
 from paper_2511_20340_amd import binding as sfb
 from paper_2511_20340_amd.engine import Engine
 
-from gpu_common import engine_only, rel_err, to_np
+from gpu_common import engine_only, linear_choice, rel_err, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -56,13 +56,14 @@ def test_attention_full_shape_sampled_sequences(name, B, Hq, Hkv, hd, lo, hi, nq
 
 
 # ---- linear layers: real weight shapes, sampled rows x columns -----------------------------------------
-@pytest.mark.parametrize("M,N,K,glu", [
-    (160, 3072, 2048, False), (160, 2048, 8192, False), (160, 32000, 2048, False), (160, 16384, 2048, True),
-    (32, 2048, 8192, False), (320, 6144, 4096, False), (320, 4096, 14336, False), (320, 28672, 4096, True),
-    (1280, 28672, 4096, True), (640, 5120, 13824, False),
-    # wide layers that take the tall tiles (320 / 256 / 224 / 192 rows per workgroup)
-    (640, 27648, 5120, True), (1024, 28672, 4096, True), (896, 27648, 5120, False), (768, 28672, 4096, False)])
-def test_linear_full_shape_sampled_outputs(M, N, K, glu):
+# also_on: a ring tile that the layer is forced onto as well, with the same bits: the tall ones (320 / 256 / 224 / 192 rows
+# per workgroup), which wide layers take where the block kernel does not run
+@pytest.mark.parametrize("M,N,K,glu,also_on", [
+    (160, 3072, 2048, False, 0), (160, 2048, 8192, False, 0), (160, 32000, 2048, False, 0), (160, 16384, 2048, True, 0),
+    (32, 2048, 8192, False, 0), (320, 6144, 4096, False, 0), (320, 4096, 14336, False, 0), (320, 28672, 4096, True, 0),
+    (1280, 28672, 4096, True, 0), (640, 5120, 13824, False, 0),
+    (640, 27648, 5120, True, 11), (1024, 28672, 4096, True, 12), (896, 27648, 5120, False, 13), (768, 28672, 4096, False, 14)])
+def test_linear_full_shape_sampled_outputs(M, N, K, glu, also_on):
     x = device_normal((M, K), 5)
     w = (device_normal((N, K), 6, torch.float32) * 0.02).to(torch.bfloat16)
     eng = engine_only(synth.ModelShape("t", 1, 128, 2, 2, 64, 64, 64, "bf16"), 1, 64, 1)
@@ -83,6 +84,12 @@ def test_linear_full_shape_sampled_outputs(M, N, K, glu):
         ref = sfo.linear(to_np(x[rows]), to_np(w[cols]))
         got = to_np(y)[np.ix_(rows, cols)]
         assert rel_err(got, ref) < 1e-5          # fp32 accumulators, unrounded output
+    if also_on:
+        assert linear_choice(M, N, K, sfb.SF_LINEAR_GLU * glu)[0] == sfb.SF_KERNEL_BLOCK
+        eng.sf_tune_linear(also_on, 1)
+        again = eng.sf_op_linear_swiglu(x, w) if glu else eng.sf_op_linear(x, w, out_f32=True)
+        eng.sf_tune_linear(0, 0)
+        assert torch.equal(again, y)
 
 
 # ---- acceptance at full vocabulary / batch ---------------------------------------------------------------
@@ -355,8 +362,8 @@ def test_real_width_two_layer_steps_teacher_forced(index, k, fixed_prefix):
 # ---- a verify pass over more attention workgroups than the chip holds: sequences ranked by length ---------
 def test_batch128_step_bits_do_not_depend_on_the_linear_tiles():
     """The 14B-shaped model at one layer, the benchmark's batch (128 sequences, k = 4: 640 rows, where the
-    wide layers run on the tall tiles): drafts, target choices, logits-free hooks and the appended K/V must be
-    bit-identical when every linear layer is forced onto the 160-row and the 128-row tiles instead."""
+    layers run on the block kernel): drafts, target choices, logits-free hooks and the appended K/V must be
+    bit-identical when every linear layer is forced onto the ring kernel's 160-, 128- and 320-row tiles instead."""
     wl = synth.WORKLOADS[4]
     m = wl.model.scaled(n_layers=1)
     B, k = 128, 4
@@ -371,7 +378,7 @@ def test_batch128_step_bits_do_not_depend_on_the_linear_tiles():
     hooks0 = device_normal(tuple(eng.hooks.shape), 11)
     results = []
     try:
-        for tile in (0, 9, 4):
+        for tile in (0, 9, 4, 11):
             eng.sf_tune_linear(tile, 0)
             eng.hooks.copy_(hooks0)
             eng.set_state(kv_len=lens, pending=g.integers(0, m.vocab, B).astype(np.int32) if not results else pending,

@@ -1,4 +1,5 @@
-"""Host logic of the linear layers' kernel choice (no GPU): the split-K factor must be the same for
+"""Host logic of the linear layers' kernel choice (no GPU): the ring kernel's rules (sf_linear_config), whose split every
+launch keeps, and what launches run on (sf_linear_choice).  The split-K factor must be the same for
 every row count up to the planned one, since the K partition fixes the fp32 summation order and the
 target's logits for a position may not depend on how many draft positions are verified with it
 (lossless verification, SpecFormer section on draft-then-verify)."""
@@ -54,8 +55,8 @@ def test_rejects_bad_arguments():
     assert L.sf_linear_config(8, 8, 8, 8, 0, None, C.byref(t), C.byref(t)) != 0
 
 
-# (M, N, K) -> configurations measured within 3 % of the fastest (tile, split) in sweeps of every
-# tile x split {1,2,4} on one MI355X, medians of interleaved repeats (8B layer shapes at 384 ... 1792 rows,
+# The ring kernel's rules.  (M, N, K) -> configurations measured within 3 % of its fastest (tile, split) in sweeps of every
+# ring tile x split {1,2,4} on one MI355X, medians of interleaved repeats (8B layer shapes at 384 ... 1792 rows,
 # 14B layer shapes at 448 ... 896 rows, the draft's 4d -> d projection, the two LM heads).
 MEASURED_NEAR_BEST = {
     (384, 4096, 14336): {(7, 4)},
@@ -151,3 +152,48 @@ def test_layers_of_a_handful_of_rows_stream():
     assert not stream(5, 152064, 5120, sfb.SF_LINEAR_ARGMAX) and not stream(64, 1024, 1024)
     # nowhere to put partial tiles: K is not split, whatever runs
     assert linear_choice(5, 2048, 2048, ws=0)[2] == 1
+
+
+def test_layers_of_many_rows_run_on_the_block_kernel():
+    wide = sfb.SF_LINEAR_GLU | sfb.SF_LINEAR_NORM
+    for (M, N, K), tile in {(640, 27648, 5120): 15, (1024, 28672, 4096): 16, (896, 27648, 5120): 16, (768, 28672, 4096): 17,
+                            (1280, 28672, 4096): 15}.items():
+        assert linear_choice(M, N, K, wide)[:2] == (sfb.SF_KERNEL_BLOCK, tile)
+    assert linear_choice(1280, 128256, 4096, sfb.SF_LINEAR_ARGMAX)[0] == sfb.SF_KERNEL_BLOCK
+    assert linear_choice(160, 2048, 2048) == (sfb.SF_KERNEL_BLOCK, 25, 2)             # K shared by groups of waves
+    # one row tile, large weights: the ring kernel reads them past the caches
+    assert linear_choice(160, 152064, 5120, sfb.SF_LINEAR_ARGMAX)[0] == sfb.SF_KERNEL_RING
+    # what the block kernel does not take: K that is no whole number of slices, rows off 16 bytes, operands of 4 GiB
+    assert linear_choice(1280, 28672, 4104, wide)[0] == sfb.SF_KERNEL_RING
+    assert linear_choice(1280, 28672, 4096, wide | sfb.SF_LINEAR_UNALIGNED)[0] == sfb.SF_KERNEL_RING
+    assert linear_choice(1 << 19, 28672, 4096)[0] == sfb.SF_KERNEL_RING and linear_choice((1 << 19) - 1, 28672, 4096)[0] == sfb.SF_KERNEL_BLOCK
+    assert linear_choice(640, 1 << 19, 4096)[0] == sfb.SF_KERNEL_RING
+    # a forced tile that cannot run is reported as what runs in its place
+    assert linear_choice(97, 1032, 192, sfb.SF_LINEAR_ARGMAX, tile=20, split=1) == (sfb.SF_KERNEL_RING, 10, 1)
+    assert linear_choice(97, 1032, 192, tile=23, split=1) == (sfb.SF_KERNEL_RING, 10, 1)
+
+
+@pytest.mark.parametrize("ws", [0, WS, 3 << 20])
+def test_chosen_configurations_can_run(ws):
+    """Partial tiles of a launch with a second one fit the workspace; groups of waves are as many as the parts of K; arg-max
+    launches are not split."""
+    rows = {**{t: r for t, r in zip(range(1, 15), (32, 64, 96, 128, 160, 64, 96, 128, 160, 160, 320, 256, 224, 192))},
+            **{t: r for t, r in zip(range(15, 26), (320, 256, 192, 128, 128, 64, 160, 160, 64, 32, 32))}}
+    cols = {**{t: 128 for t in range(1, 6)}, **{t: 256 for t in range(6, 19)}, **{t: 64 for t in range(19, 26)}, 22: 128}
+    for N, K in SHAPES + [(512, 1000), (1024, 24576), (4104, 2056), (2048, 16384)]:
+        for M in (1, 17, 33, 64, 97, 136, 160, 200, 320, 500, 640, 1024, 1280, 3000):
+            for flags in FLAGS[:2] + [sfb.SF_LINEAR_ARGMAX]:
+                kernel, tile, split = linear_choice(M, N, K, flags, ws=ws)
+                slices = (K + 63) // 64
+                parts = -(-slices // -(-slices // min(split, slices)))
+                if flags == sfb.SF_LINEAR_ARGMAX or ws == 0:
+                    assert split == 1
+                if kernel == sfb.SF_KERNEL_STREAM:
+                    continue
+                groups = {23: 2, 24: 4, 25: 2}.get(tile, 1)
+                assert groups in (1, parts)
+                if parts > 1 and groups == 1:
+                    tiles = -(-M // rows[tile]) * -(-N // cols[tile])
+                    assert (1 << 20) + tiles * parts * rows[tile] * cols[tile] * 4 <= ws, (M, N, K, flags)
+                if kernel == sfb.SF_KERNEL_BLOCK:
+                    assert K % 64 == 0 and tile >= 15
