@@ -252,7 +252,8 @@ sf_status sf_op_rmsnorm_linear(const sf_ctx *ctx, const void *x, const void *w, 
                                int32_t K, int32_t out_f32, void *workspace, size_t workspace_bytes,
                                void *stream);
 /* SwiGLU input half: act[M][F] = silu(x . Wg^T) * (x . Wu^T); w_gate_up packed with glu = 1 (SF_BF16:
- * one kernel, gate/up never leave registers; SF_F32: workspace must hold M*2F floats). act: dev elem. */
+ * one kernel, gate/up never leave registers; SF_F32 likewise, but workspace must have room for M*2F floats,
+ * or SF_ECAPACITY). act: dev elem. */
 sf_status sf_op_linear_swiglu(const sf_ctx *ctx, const void *x, const void *w_gate_up, void *act, int32_t M,
                               int32_t F, int32_t K, void *workspace, size_t workspace_bytes, void *stream);
 /* The LM head with its arg-max, as the step calls run it: ids[m] = argmax_n (x . w^T)[m][n] (lowest index

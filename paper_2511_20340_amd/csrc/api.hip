@@ -119,7 +119,7 @@ sf_status check_attn_shape(const sf_model_cfg &m, int n_q) {
   if (m.dtype == SF_BF16) {
     if (G * n_q > 1024) return SF_EUNSUPPORTED;  // 32 row tiles of 32 rows per (sequence, kv head)
   } else {
-    if (n_q * m.head_dim > 2048) return SF_EUNSUPPORTED;
+    if (n_q * m.head_dim > 2048) return SF_EUNSUPPORTED;  // a limit of the interface; the kernel has none
   }
   return SF_OK;
 }
@@ -347,8 +347,8 @@ sf_status sf_bind(sf_ctx *c, const sf_target_weights *t, const sf_draft_weights 
   c->w_down.assign(t->w_down, t->w_down + L);
   c->has_draft = d != nullptr;
   if (d) c->dw = *d;
-  // function attributes of the tall linear tiles, set here so that the first launch (possibly under stream
-  // capture) has nothing left to set; best effort -- a launch repeats the call and reports its error
+  // function attributes of the linear tiles that need more LDS than the default, set here so that the first launch
+  // (possibly under stream capture) has nothing left to set; best effort -- a launch repeats the call and reports its error
   if (c->tc.dtype == SF_BF16) (void)gemm_prepare_device();
   c->bound = true;
   return SF_OK;
@@ -390,10 +390,10 @@ sf_status sf_verify_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_t
   ra.B = B; ra.n_q = q; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.cap = cap;
   ra.kv_only = 0; ra.pos_mode = 0; ra.theta = m.rope_theta;
   // bf16, more attention workgroups than compute units: the table kernel also ranks the sequences by length, and the
-  // attention launches of this call go by that order.  More than the chip holds at once (2 per compute unit): the longest
-  // start first.  Up to that many, all start at once and a compute unit shares its bandwidth between two: the longest half
-  // comes first, then the rest from the shortest, so the longest gets the shortest beside it.  61 sequences of 100 to
-  // 1800, plain decoding: 2757 -> 2680 us a step; 64 of 256 to 2048: 5569 -> 5504.
+  // attention launches of this call go by that order.  More than 512: the longest start first.  257 to 512 (what the chip
+  // holds at once with a head dim of 128, two to a compute unit): the longest 256 workgroups' sequences come first, then the
+  // rest from the shortest, so that a compute unit that takes two has a short one beside a long one.  Measured with a head
+  // dim of 128: 61 sequences of 100 to 1800, plain decoding, 2757 -> 2680 us a step; 64 of 256 to 2048, 5569 -> 5504.
   const int attn_groups = B * m.n_kv_heads * ((m.n_q_heads / m.n_kv_heads * q + 31) / 32);
   ra.order = bf && attn_groups > 256 ? (int32_t *)(ws + A.order) : nullptr;
   ra.pair_from = attn_groups > 512 ? 0 : std::max(1, 256 * B / attn_groups);
@@ -729,6 +729,7 @@ sf_status sf_op_linear_swiglu(const sf_ctx *c, const void *x, const void *w_gate
   if (K % 8 || F % 32) return SF_EUNSUPPORTED;
   if (workspace && ((uintptr_t)workspace) % ALIGN) return SF_EINVAL;
   const bool bf = c->tc.dtype == SF_BF16;
+  // fp32: nothing is kept in the workspace any more; the interface still asks for it
   const size_t lin = bf ? gemm_workspace_bytes(M) : 0, gu_bytes = bf ? 0 : up((size_t)M * 2 * F * sizeof(float));
   if (!bf && (!workspace || workspace_bytes < gu_bytes)) return SF_ECAPACITY;
   Run r{c, (hipStream_t)stream};

@@ -1,4 +1,4 @@
-// bf16 linear layers: kernel choice, split-K finish, weight packing (the kernel itself: gemm_ring.h).
+// bf16 linear layers: kernel choice, split-K finish, weight packing (the kernels: gemm_ring.h, gemm_block.h, gemm_stream.hip).
 #include "gemm_common.h"
 
 #include <algorithm>
@@ -85,7 +85,8 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 }
 
 // Tile configurations: rows per workgroup TM*32, columns NW*32 (one 32-column block per wave).
-//   id  TM  ring  wg/CU  waves      (11-14: tall tiles for wide layers, see pick_large)
+// The ring kernel's 1-14: gemm_tiles_*.hip (11-14: tall tiles for wide layers, see pick_large; 9, the three-slot form of 10,
+// is chosen by no rule).
 // A sixth template argument of 1 selects the hand-pinned issue order of the slice (same arithmetic, same
 // bits).  Measured against the compiler's order on 27 shapes x splits {1, 2, 4}: 2-12 % faster on the 96-row
 // tiles and the 128-row tiles, up to 17 % on the 64 x 256 tile, 9-60 % on the two-slot 160 x 256 tile (which
@@ -99,7 +100,7 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 // 6-8 % faster with it, also inside whole steps; the 320-row kernel with the fused norm measured 3 % faster
 // alone but 3.7 % slower as the gate/up product inside whole steps, so the fused-norm kernels keep the
 // compiler's order (seventh argument).
-// 15-25: the block kernel (gemm_block.h); on a layer that it does not take they stand for tile 10.
+// 15-25: the block kernel's (gemm_block.hip); forced on a layer that it does not take they stand for tile 10.
 constexpr int N_TILES = 25, N_RING_TILES = 14, N_MODEL_TILES = 10;
 constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1};
 
@@ -127,8 +128,10 @@ int pow2floor(int v) { int p = 1; while (p * 2 <= v) p *= 2; return p; }
 // sweeps of all tiles x splits {1,2,4} (medians of interleaved repeats) of 30 shapes on MI355X: the 8B
 // layers at 384 ... 1792 rows, the 14B layers at 448 ... 896 rows and the two LM heads; the factors of the
 // tiles whose issue order was pinned later (4, 5, 7, 8, 10) were lowered by what the pinning gained in a repeat of
-// the same sweeps.  Over the 32 shapes of that repeat the choice (this model, then the tall-tile rule) is
-// the fastest measured configuration of every shape.
+// the same sweeps.  Over the 32 shapes of that repeat the choice (this model, then the tall-tile rule) was
+// the fastest configuration of the ring kernel at every shape.  Since then the second launch of a split has become cheaper
+// than the model has it, and most of these layers run on the block kernel (pick_any).  The split is still decided here, as
+// it fixes the order of a layer's sums; the tiles serve the layers that the block kernel does not take.
 double model_us(int M, int N, int K, int tile, int split) {
   static const double factor[N_MODEL_TILES + 1] = {0, 1.0, 1.022, 1.005, 1.015, 1.080, 1.0, 0.889, 0.842, 0.938, 0.910};
   const int BM = TILE_TM[tile] * 32, BN = tile >= 6 ? 256 : 128;

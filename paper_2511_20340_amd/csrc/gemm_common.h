@@ -143,7 +143,7 @@ inline Epilogue make_epilogue(const GemmArgs &a) {
 
 // Weights of a layer with one M-tile are read once per launch; from this size on they leave the caches alone
 // (non-temporal loads stream faster from HBM, and a model of such layers does not fit the memory-side cache from one
-// step to the next anyway).  5 rows: 28672 x 4096 47 -> 41 us, 128256 x 4096 183 -> 160, 4096 x 14336 26.6 -> 24.0,
+// step to the next anyway).  Ring kernel, 5 rows: 28672 x 4096 47 -> 41 us, 128256 x 4096 183 -> 160, 4096 x 14336 26.6 -> 24.0,
 // 4096 x 4096 (34 MB) 13.1 -> 11.8; below it the cached loads are the faster ones: 3072 x 2048 (13 MB) 8.9 against 9.8.
 constexpr size_t ONCE_BYTES = 24u << 20;
 
