@@ -255,8 +255,9 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
 // positions of K (with the fused norm a little more); the weights have to come from memory, which overlaps a good half of
 // the shorter of the two; a split adds the second launch and its partial rows, unless groups of waves share it.  The tiles
 // of both kernels x splits 1 to 8 were measured on 440 shapes (the 1B, 8B and 14B layers and heads at 40 to 2304 rows,
-// weights cold, medians of interleaved repeats) and the constants fitted to them: 4.8 % rms.  (Tile 20's norm by hand: its
-// waves have one row block, and the squares of one chunk wait for each other.)
+// weights cold, medians of interleaved repeats) and the constants fitted to them: 4.8 % rms.  Since float outputs leave in
+// whole lines, launches of the tall tiles are up to 12 % faster than this; constants fitted anew choose no better.  (Tile
+// 20's norm by hand: its waves have one row block, and the squares of one chunk wait for each other.)
 struct TileCost {
   int bm, bn, groups;
   float slice, fixed, least, norm;
@@ -285,14 +286,17 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
 }
 
 // The tile for a layer of more than 32 rows whose split is decided: what the rules above pick for the ring kernel, or one
-// of the block kernel's, whichever cost_us puts first.  Over the measured shapes it is 1.09 times as fast as the rules
-// above alone, 1.6 % slower than the fastest tile of each shape and nowhere more than 8 % slower than the rules alone.
-// (The split stays what the rules say: it fixes the order of a layer's sums.)  Up to 160 rows the ring kernel, which then
-// reads large weights past the caches, is up to 5 % better than its formula.
+// of the block kernel's, whichever cost_us puts first.  (The split stays what the rules say: it fixes the order of a
+// layer's sums.)  Up to 160 rows the ring kernel, which then reads large weights past the caches, is up to 5 % better than
+// its formula; an LM head with arg-max partials up to 192 rows is up to 10 % better (160 x 152064 x 5120 372 us against
+// 384 on the block kernel, 192 x 32000 x 2048 46.6 against 51.4).  Over 521 shapes (33 to 8192 rows, with the norm, the
+// gate, float output or arg-max, replayed from graphs) the choice takes 0.92 times as long as the rules alone and 1.1 %
+// longer than the fastest tile of each shape; 19 are more than 2 % slower than by the rules, the worst by 11 % (norm, 136 x
+// 7168 x 5120: 35 us on five 32-row tiles, 39 on two of 128).
 GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, int norm, bool am) {
   GemmConfig best = pick(M, N, K, ws_bytes, split);
   if (M <= 32) return best;
-  double best_us = cost_us(M, N, K, best, norm) * (M <= 160 ? 0.95 : 1.0);
+  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : 1.0);
   for (int tile = N_RING_TILES + 1; tile <= N_TILES; ++tile) {
     if (!block_takes(tile, M, N, K, split, am)) continue;
     const Plan p = make_plan(M, N, K, TILE_COST[tile].bm, TILE_COST[tile].bn, split);
