@@ -298,7 +298,7 @@ GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, int norm, b
   if (M <= 32) return best;
   double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : 1.0);
   for (int tile = N_RING_TILES + 1; tile <= N_TILES; ++tile) {
-    if (!block_takes(tile, M, N, K, split, am)) continue;
+    if (!block_takes(tile, M, N, K, split, am, norm ? (ptrdiff_t)ws_bytes : -1)) continue;
     const Plan p = make_plan(M, N, K, TILE_COST[tile].bm, TILE_COST[tile].bn, split);
     if (block_groups(tile) == 1 && !plan_fits(p, TILE_COST[tile].bm, (const void *)1, ws_bytes)) continue;
     const double us = cost_us(M, N, K, {tile, split}, norm);
@@ -366,7 +366,7 @@ GemmChoice gemm_choose(const GemmArgs &a) {
     if (c.split <= 0) c.split = h.split;
     if (c.tile <= 0) c.tile = c.split == h.split ? h.tile : pick(a.M, a.N, a.K, ws_bytes, c.split).tile;
   }
-  if (c.tile > N_RING_TILES && (!block_takes(c.tile, a.M, a.N, a.K, c.split, am) || !rows_aligned(a))) c.tile = 10;
+  if (c.tile > N_RING_TILES && (!block_takes(c.tile, a.M, a.N, a.K, c.split, am, a.fused_norm ? (ptrdiff_t)ws_bytes : -1) || !rows_aligned(a))) c.tile = 10;
   return {c.tile > N_RING_TILES ? GEMM_BLOCK : GEMM_RING, c.tile, c.split};
 }
 

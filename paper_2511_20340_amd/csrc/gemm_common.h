@@ -157,6 +157,9 @@ hipError_t launch_gemm_stream(const GemmArgs &a, int tiles, int split, hipStream
 // adds the partial tiles of a split layer and applies the epilogue (gemm.hip)
 hipError_t launch_split_finish(const float *partial, const float *ssq_part, const Epilogue &e, int split,
                                const GemmArgs &a, hipStream_t s);
+// the fused norm's row sums of squares by a launch of their own: ssq[split][M] in the workspace (gemm_panel.hip)
+inline bool squares_fit(int M, size_t ws_bytes) { return (size_t)M * sizeof(float) <= GEMM_SSQ_BYTES && ws_bytes >= GEMM_SSQ_BYTES; }
+hipError_t launch_row_squares(const GemmArgs &a, int split_k, int kt_per_split, float *ssq, hipStream_t s);
 // the tile configurations (gemm_tiles_*.hip)
 hipError_t dispatch_narrow(int tile, const GemmArgs &a, hipStream_t s, int split);  // 1-5
 hipError_t dispatch_wide(int tile, const GemmArgs &a, hipStream_t s, int split);    // 6-10
@@ -165,7 +168,9 @@ hipError_t prepare_tall();  // their function attributes, once per device
 // the block kernel's (gemm_block.hip)
 hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-25
 hipError_t prepare_block();
+hipError_t dispatch_panel(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-17 of these (gemm_panel.hip)
+hipError_t prepare_panel();
 int block_groups(int tile);  // groups of waves that share a split K inside a workgroup (1: none)
-bool block_takes(int tile, int M, int N, int K, int split, bool am);  // whether that tile can run such a layer
+bool block_takes(int tile, int M, int N, int K, int split, bool am, ptrdiff_t norm_ws);  // whether that tile can run such a layer
 
 }  // namespace sf
