@@ -10,8 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspecformer.so")
 SOURCES = ["api.hip", "attention.hip", "gemm.hip", "gemm_tiles_narrow.hip",
            "gemm_tiles_wide.hip", "gemm_tiles_tall.hip", "gemm_stream.hip", "gemm_block.hip", "gemm_panel.hip",
-           "gemm_f32.hip",
-           "elementwise.hip", "accept.hip"]
+           "gemm_panel_narrow.hip", "gemm_f32.hip", "elementwise.hip", "accept.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-result"]

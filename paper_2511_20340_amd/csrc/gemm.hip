@@ -101,8 +101,8 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 // alone but 3.7 % slower as the gate/up product inside whole steps, so the fused-norm kernels keep the
 // compiler's order (seventh argument).
 // 15-25: the block kernel's (gemm_block.hip); forced on a layer that it does not take they stand for tile 10.
-constexpr int N_TILES = 25, N_RING_TILES = 14, N_MODEL_TILES = 10;
-constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1};
+constexpr int N_TILES = 28, N_RING_TILES = 14, N_MODEL_TILES = 10;
+constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1, 4, 5, 5};
 
 // the block kernel's direct loads move 16 bytes at a time; the ring kernel takes rows at any address
 bool rows_aligned(const GemmArgs &a) { return (uintptr_t)a.x % 16 == 0; }
@@ -264,25 +264,31 @@ struct TileCost {
 };
 constexpr TileCost TILE_COST[N_TILES + 1] = {
     {},
-    {32, 128, 1, 0.241f, 1.2f, 1.19f, 0.000f}, {64, 128, 1, 0.304f, 2.0f, 1.27f, 0.018f}, {96, 128, 1, 0.385f, 3.2f, 1.11f, 0.034f},
-    {128, 128, 1, 0.493f, 2.9f, 1.09f, 0.045f}, {160, 128, 1, 0.636f, 3.0f, 1.06f, 0.044f}, {64, 256, 1, 0.540f, 2.7f, 1.10f, 0.002f},
-    {96, 256, 1, 0.708f, 5.7f, 0.96f, 0.026f}, {128, 256, 1, 0.849f, 4.1f, 0.94f, 0.044f}, {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f},
-    {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f}, {320, 256, 1, 2.072f, 2.4f, 0.96f, 0.333f}, {256, 256, 1, 1.593f, 3.3f, 0.94f, 0.302f},
-    {224, 256, 1, 1.560f, 4.4f, 0.95f, 0.095f}, {192, 256, 1, 1.167f, 6.0f, 0.92f, 0.096f}, {320, 256, 1, 1.691f, 2.6f, 0.86f, 0.230f},
-    {256, 256, 1, 1.317f, 3.2f, 0.84f, 0.232f}, {192, 256, 1, 1.027f, 3.7f, 0.84f, 0.143f}, {128, 256, 1, 0.744f, 4.5f, 0.90f, 0.081f},
-    {128, 64, 1, 0.293f, 1.7f, 1.12f, 0.041f}, {64, 64, 1, 0.199f, 1.1f, 1.12f, 0.140f}, {160, 64, 1, 0.392f, 3.2f, 0.97f, 0.081f},
-    {160, 128, 1, 0.548f, 4.9f, 0.91f, 0.117f}, {64, 64, 2, 0.469f, 0.2f, 0.63f, 0.083f}, {32, 64, 4, 0.737f, 0.0f, 0.52f, 0.089f},
-    {32, 64, 2, 0.348f, 0.1f, 0.95f, 0.038f},
+    {32, 128, 1, 0.241f, 1.2f, 1.19f, 0.000f}, {64, 128, 1, 0.304f, 2.0f, 1.27f, 0.018f},
+    {96, 128, 1, 0.385f, 3.2f, 1.11f, 0.034f}, {128, 128, 1, 0.493f, 2.9f, 1.09f, 0.045f},
+    {160, 128, 1, 0.636f, 3.0f, 1.06f, 0.044f}, {64, 256, 1, 0.540f, 2.7f, 1.10f, 0.002f},
+    {96, 256, 1, 0.708f, 5.7f, 0.96f, 0.026f}, {128, 256, 1, 0.849f, 4.1f, 0.94f, 0.044f},
+    {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f}, {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f},
+    {320, 256, 1, 2.072f, 2.4f, 0.96f, 0.333f}, {256, 256, 1, 1.593f, 3.3f, 0.94f, 0.302f},
+    {224, 256, 1, 1.560f, 4.4f, 0.95f, 0.095f}, {192, 256, 1, 1.167f, 6.0f, 0.92f, 0.096f},
+    {320, 256, 1, 1.403f, 11.3f, 0.85f, 6.2f}, {256, 256, 1, 1.238f, 8.9f, 0.11f, 7.0f},
+    {192, 256, 1, 1.071f, 7.1f, 0.97f, 7.2f}, {128, 256, 1, 0.744f, 4.5f, 0.90f, 0.081f},
+    {128, 64, 1, 0.293f, 1.7f, 1.12f, 0.041f}, {64, 64, 1, 0.199f, 1.1f, 1.12f, 0.140f},
+    {160, 64, 1, 0.392f, 3.2f, 0.97f, 0.081f}, {160, 128, 1, 0.548f, 4.9f, 0.91f, 0.117f},
+    {64, 64, 2, 0.469f, 0.2f, 0.63f, 0.083f}, {32, 64, 4, 0.737f, 0.0f, 0.52f, 0.089f},
+    {32, 64, 2, 0.348f, 0.1f, 0.95f, 0.038f}, {128, 128, 1, 0.526f, 1.1f, 0.69f, 8.5f},
+    {160, 128, 1, 0.486f, 1.9f, 1.63f, 7.8f}, {160, 128, 1, 0.509f, 4.3f, 0.61f, 7.0f},
 };
 double cost_us(int M, int N, int K, GemmConfig c, int norm) {
   const TileCost &t = TILE_COST[c.tile];
   const int KT = (K + BK - 1) / BK, kps = (KT + c.split - 1) / c.split, split = (KT + kps - 1) / kps;
   const int tiles_m = (M + t.bm - 1) / t.bm, units = (N + t.bn - 1) / t.bn * (t.groups > 1 ? 1 : split);
   const int per_cu = ((units + XCDS - 1) / XCDS * tiles_m + 31) / 32;  // 32 compute units in the busiest XCD
-  const double cu = std::max((double)per_cu, (double)t.least) * ((t.slice + (norm ? t.norm : 0.f)) * kps + t.fixed);
+  const bool before = squares_before(c.tile);  // a launch in front
+  const double cu = std::max((double)per_cu, (double)t.least) * ((t.slice + (norm && !before ? t.norm : 0.f)) * kps + t.fixed);
   const double mem = (double)N * K * 2 / 7.22e6;
   const double second = split > 1 && t.groups == 1 ? 2.5 + (double)M * N * 4 * split / 2.27e6 : 0.0;
-  return 1.4 + std::max(cu, mem) + 0.44 * std::min(cu, mem) + second;
+  return 1.4 + std::max(cu, mem) + 0.44 * std::min(cu, mem) + second + (norm && before ? t.norm : 0.f);
 }
 
 // The tile for a layer of more than 32 rows whose split is decided: what the rules above pick for the ring kernel, or one
@@ -296,9 +302,9 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
 GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, int norm, bool am) {
   GemmConfig best = pick(M, N, K, ws_bytes, split);
   if (M <= 32) return best;
-  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : 1.0);
+  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : 1.08);
   for (int tile = N_RING_TILES + 1; tile <= N_TILES; ++tile) {
-    if (!block_takes(tile, M, N, K, split, am, norm ? (ptrdiff_t)ws_bytes : -1)) continue;
+    if ((tile > 25 && M <= 160) || !block_takes(tile, M, N, K, split, am, norm ? (ptrdiff_t)ws_bytes : -1)) continue;
     const Plan p = make_plan(M, N, K, TILE_COST[tile].bm, TILE_COST[tile].bn, split);
     if (block_groups(tile) == 1 && !plan_fits(p, TILE_COST[tile].bm, (const void *)1, ws_bytes)) continue;
     const double us = cost_us(M, N, K, {tile, split}, norm);

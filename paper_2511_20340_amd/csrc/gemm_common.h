@@ -166,10 +166,13 @@ hipError_t dispatch_wide(int tile, const GemmArgs &a, hipStream_t s, int split);
 hipError_t dispatch_tall(int tile, const GemmArgs &a, hipStream_t s, int split);    // 11-14
 hipError_t prepare_tall();  // their function attributes, once per device
 // the block kernel's (gemm_block.hip)
-hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-25
+hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-28
 hipError_t prepare_block();
-hipError_t dispatch_panel(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-17 of these (gemm_panel.hip)
+hipError_t dispatch_panel(int tile, const GemmArgs &a, hipStream_t s, int split);  // those of them on the panel kernel
+hipError_t dispatch_panel_narrow(int tile, const GemmArgs &a, hipStream_t s, int split);
 hipError_t prepare_panel();
+hipError_t prepare_panel_narrow();
+inline bool squares_before(int tile) { return (tile >= 15 && tile <= 17) || tile >= 26; }  // a norm's row sums: a launch of their own
 int block_groups(int tile);  // groups of waves that share a split K inside a workgroup (1: none)
 bool block_takes(int tile, int M, int N, int K, int split, bool am, ptrdiff_t norm_ws);  // whether that tile can run such a layer
 

@@ -11,8 +11,13 @@
 //   * the weights are the products' first operand: a lane then holds four consecutive columns of a row, and the epilogue
 //     turns its tiles through LDS in 16-byte units, several in flight.
 // With one wave on a SIMD nothing hides what the wave itself does between products, so the order is written out: after
-// every product at most one LDS read or one load (or one step of the norm's squares).  Loads four products apart: at two
-// apart they queue up in front of the L1 and 2048 x 8192 x 8192 takes 199 us instead of 187.
+// every product at most one LDS read or one load.  On the two largest tiles loads go out four products apart: at two apart
+// they queue up in front of the L1 and 2048 x 8192 x 8192 takes 199 us instead of 187; on the others two apart (640 x 27648 x
+// 5120 on 192 x 256 214 -> 198 us).
+//
+// The smaller tiles serve layers whose workgroups just fill the chip once: there the time of a slice is the wait for its
+// loads, so three or four slices are kept in LDS (640 x 5120 x 5120: 128 x 128 with two 65 us, with four 45.6; the block
+// kernel 53), or two workgroups share a compute unit.
 #pragma once
 #include "gemm_block.h"
 
@@ -23,19 +28,21 @@ namespace {
 // loop, and it does not know when a product written out below is done.
 constexpr int IN_ACC = 56;
 
-// WM x WN waves, each with TM x TN tiles of 16 x 16; two slices of 64 positions of K in LDS.
-template <int WM, int WN, int TM, int TN>
+// WM x WN waves, each with TM x TN tiles of 16 x 16; STAGES slices of 64 positions of K in LDS.
+template <int WM, int WN, int TM, int TN, int STAGES>
 struct PanelShape {
   static constexpr int NW = WM * WN, BM = WM * TM * 16, BN = WN * TN * 16;
-  static constexpr int A_UNITS = BM / 8, UNITS = (BM + BN) / 8, PER = (UNITS + NW - 1) / NW;  // 1 KiB each; PER: loads per wave
+  static constexpr int A_UNITS = BM / 8, UNITS = (BM + BN) / 8, PER = UNITS / NW;  // 1 KiB each; PER: loads per wave
   static constexpr int A_SLICE = A_UNITS * UNIT, SLICE = UNITS * UNIT;
   // after the loop the same LDS holds the row factors, the sums of squares by chunk (or the arg-max partials of the WN
   // columns of waves), and per wave pieces of 16 rows
   static constexpr int ROW = TN * 16 + 4, PIECE = 16 * ROW * 4, PIECES = 2;
   static constexpr size_t rows = (size_t)BM * 9 * 4;
-  static constexpr size_t after = rows + (size_t)NW * PIECES * PIECE, loop = 2 * (size_t)SLICE;
+  static constexpr size_t after = rows + (size_t)NW * PIECES * PIECE, loop = STAGES * (size_t)SLICE;
   static constexpr size_t lds = loop > after ? loop : after;
+  static constexpr bool PAIR = lds <= 80 * 1024;  // two workgroups on a compute unit
   static_assert(lds <= 160 * 1024 && TN % 2 == 0 && WN <= 4, "LDS of a compute unit; whole 32-column blocks per wave");
+  static_assert(UNITS % NW == 0, "loads in flight are counted: every wave has as many");
   static_assert(TM * TN <= 80, "IN_ACC tiles in accumulation registers, the rest in vector registers");
 };
 
@@ -56,20 +63,24 @@ __device__ __forceinline__ f32x4 finished(f32x4 &c) {
 }
 #endif
 
-template <int WM, int WN, int TM, int TN>
+template <int WM, int WN, int TM, int TN, int STAGES>
 __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_t *__restrict__ A, const uint4 *__restrict__ Wp,
                                                                      const Epilogue e, int M, int N, int K, int tiles_m,
                                                                      int tiles_n, int split_k, int kt_per_split,
                                                                      float *__restrict__ partial, float eps,
                                                                      const float *__restrict__ ssq) {
 #ifdef __HIP_DEVICE_COMPILE__
-  using S = PanelShape<WM, WN, TM, TN>;
+  using S = PanelShape<WM, WN, TM, TN, STAGES>;
   constexpr int NW = S::NW, BM = S::BM, PER = S::PER;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
   const int id = blockIdx.x;
   const int xcd = id % XCDS, j = id / XCDS;
-  const int tm = j % tiles_m, unit = (j / tiles_m) * XCDS + xcd;
+  // The units of an XCD and the row tiles that share a unit's weights: those side by side, or, where a compute unit holds
+  // two workgroups, all units of one row tile first, so that the second half of a not quite full round spreads evenly
+  // (320 x 28672 x 4096 on 160 x 128: 86 -> 75 us; with one to a compute unit 1280 x 28672 x 4096 takes 241 us that way, 222).
+  const int per = (tiles_n * split_k + XCDS - 1) / XCDS;
+  const int tm = S::PAIR ? j / per : j % tiles_m, unit = (S::PAIR ? j % per : j / tiles_m) * XCDS + xcd;
   if (unit >= tiles_n * split_k) return;
   const int tn = unit / split_k, ks = unit % split_k;
   const int m0 = tm * BM, n0 = tn * S::BN;
@@ -102,16 +113,16 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     auto *to = (__attribute__((address_space(3))) void *)(smem + fill + u * UNIT);
     if constexpr ((i + 1) * NW <= S::A_UNITS) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(buf_a, to, 16, src[i], a_pos, 0, 0);
-    } else if constexpr (i * NW >= S::A_UNITS && (i + 1) * NW <= S::UNITS) {
+    } else if constexpr (i * NW >= S::A_UNITS) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(buf_w, to, 16, src[i], w_pos, 0, 0);
     } else {
       if (u < S::A_UNITS) __builtin_amdgcn_raw_ptr_buffer_load_lds(buf_a, to, 16, src[i], a_pos, 0, 0);
-      else if (u < S::UNITS) __builtin_amdgcn_raw_ptr_buffer_load_lds(buf_w, to, 16, src[i], w_pos, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(buf_w, to, 16, src[i], w_pos, 0, 0);
     }
     if constexpr (i == PER - 1) {
       a_pos = min(a_pos + BK * 2, a_last);
       w_pos = min(w_pos + 4 * UNIT, w_last);
-      fill = S::SLICE - fill;
+      fill = fill == (STAGES - 1) * S::SLICE ? 0 : fill + S::SLICE;
     }
   };
 
@@ -136,9 +147,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   };
   // Row a of a k-step is TN products with activation fragment a.  That fragment is read AHEAD rows before; the weights of
   // the next k-step in the rows from TURN on.  In the second k-step of a slice those reads are of the next slice: before
-  // row TURN the waves meet, the next slice has landed, and as nobody reads this one any more the loads of the one after
-  // next begin, LOAD_GAP products apart.
-  constexpr int AHEAD = TN >= 8 ? (TM >= 6 ? 3 : 2) : 3, TURN = TM - AHEAD, LOAD_GAP = 4;
+  // row TURN the waves meet, the next slice has landed, and as nobody reads this one any more the loads of the slice that
+  // takes its place begin, LOAD_GAP products apart.
+  constexpr int AHEAD = TN >= 8 ? (TM >= 6 ? 3 : 2) : 3, TURN = TM - AHEAD, LOAD_GAP = TM * TN >= 64 ? 4 : 2;
   constexpr int NEW = AHEAD + TN, SPACE = AHEAD * TN;  // reads in the rows from TURN on, and their products
   static_assert(TURN >= 1 && SPACE >= NEW, "reads fit between the products");
   constexpr int TAIL = SPACE / LOAD_GAP < PER ? SPACE / LOAD_GAP : PER;  // loads in the second k-step
@@ -148,8 +159,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     static_for<TM * TN>([&](auto i_c) __attribute__((always_inline)) {
       constexpr int i = decltype(i_c)::value, a = i / TN, b = i % TN;
       if constexpr (s == 1 && i == TURN * TN) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        cur = S::SLICE - cur;
+        wait_loads_and_meet<(STAGES - 2) * PER>();
+        cur = cur == (STAGES - 1) * S::SLICE ? 0 : cur + S::SLICE;
       }
       product<(i < IN_ACC)>(acc[a][b], fb[s][b], fa[s][a]);
       __builtin_amdgcn_sched_barrier(0);
@@ -176,8 +187,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     });
   };
 
-  static_for<PER>(load);
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  static_for<STAGES - 1>([&](auto) __attribute__((always_inline)) { static_for<PER>(load); });
+  wait_loads_and_meet<(STAGES - 2) * PER>();
   static_for<TAIL>(load);
 #pragma unroll
   for (int b = 0; b < TN; ++b) read_w(0, b);
@@ -297,8 +308,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     });
     return;
   }
-  // how_c: PLAIN rows; FULL: bias, the float residual stream (requested one piece ahead: y may be the residual, a lane's own
-  // elements), bf16 copy, hooked copies; ANY: any types and addresses, in a loop that is not unrolled
+  // how_c: PLAIN rows; FULL: bias, the float residual stream (requested as many pieces ahead as registers allow: y may
+  // be the residual, a lane's own elements), bf16 copy, hooked copies; ANY: any types and addresses, in a loop that is not unrolled
   enum { PLAIN, FULL, ANY };
   auto outputs = [&](auto w_c, auto how_c, auto store) __attribute__((always_inline)) {
     constexpr int W = decltype(w_c)::value, PR = TN * 16 / W, T = (16 * PR + 63) / 64;  // units per row; units per lane
@@ -309,7 +320,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       row = m0 + (wm * TM + a) * 16 + r;
       col = col0 + (u - r * PR) * W;
     };
-    f32x4 res[how == FULL ? 2 : 1][how == FULL ? T : 1];
+    constexpr int DEEP = 24 / T < 1 ? 1 : 24 / T, RING = TM < DEEP ? TM : DEEP;  // pieces of residual rows in flight
+    f32x4 res[how == FULL ? RING : 1][how == FULL ? T : 1];
     auto request = [&](int to, int a) __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < T; ++t) {
@@ -327,11 +339,13 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       load_n(p + r * S::ROW + (col - col0), v, 1);
       if (row < M && col < N) store((wm * TM + a) * 16 + r, row, col, v, own);
     };
-    if (how == FULL && e.residual) request(0, 0);
+    if (how == FULL && e.residual) {
+#pragma unroll
+      for (int a = 0; a < RING; ++a) request(a, a);
+    }
     static_for<TM>([&](auto a_c) __attribute__((always_inline)) {
       constexpr int a = decltype(a_c)::value;
       float *p = reinterpret_cast<float *>(pieces + a % S::PIECES * S::PIECE);
-      if (how == FULL && a + 1 < TM && e.residual) request((a + 1) & 1, a + 1);
       static_for<TN>([&](auto b_c) __attribute__((always_inline)) {
         constexpr int b = decltype(b_c)::value;
         *reinterpret_cast<f32x4 *>(p + l16 * S::ROW + b * 16 + lq * 4) = finished<(a * TN + b < IN_ACC)>(acc[a][b]);
@@ -342,7 +356,10 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
         for (int t = 0; t < T; ++t) piece(a, t, p, res[0][0]);
       } else {
 #pragma unroll
-        for (int t = 0; t < T; ++t) piece(a, t, p, res[how == FULL ? a & 1 : 0][how == FULL ? t : 0]);
+        for (int t = 0; t < T; ++t) piece(a, t, p, res[how == FULL ? a % RING : 0][how == FULL ? t : 0]);
+        if constexpr (how == FULL && a + RING < TM) {
+          if (e.residual) request(a % RING, a + RING);
+        }
       }
       settle();
     });
@@ -410,23 +427,23 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
 #endif
 }
 
-template <int WM, int WN, int TM, int TN>
+template <int WM, int WN, int TM, int TN, int STAGES>
 hipError_t ensure_panel_lds() {
-  constexpr int cap = (int)PanelShape<WM, WN, TM, TN>::lds;
+  constexpr int cap = (int)PanelShape<WM, WN, TM, TN, STAGES>::lds;
   if (cap <= 64 * 1024) return hipSuccess;
   static bool raised[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (raised[dev]) return hipSuccess;
-  const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_panel_kernel<WM, WN, TM, TN>),
+  const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_panel_kernel<WM, WN, TM, TN, STAGES>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, cap);
   if (err == hipSuccess) raised[dev] = true;
   return err;
 }
 
-template <int WM, int WN, int TM, int TN>
+template <int WM, int WN, int TM, int TN, int STAGES>
 hipError_t run_panel(const GemmArgs &a, hipStream_t s, int split) {
-  using S = PanelShape<WM, WN, TM, TN>;
+  using S = PanelShape<WM, WN, TM, TN, STAGES>;
   const Plan p = make_plan(a.M, a.N, a.K, S::BM, S::BN, split);
   if (!plan_fits(p, S::BM, a.ws, a.ws_bytes) || (a.fused_norm && !squares_fit(a.M, a.ws_bytes))) return hipErrorInvalidValue;
   const bool two = p.split_k > 1;  // a second launch adds the partial tiles
@@ -435,11 +452,11 @@ hipError_t run_panel(const GemmArgs &a, hipStream_t s, int split) {
   if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;
   if (a.am_val && a.am_parts_out) *a.am_parts_out = p.tiles_n;
   const Epilogue e = make_epilogue(a);
-  hipError_t err = ensure_panel_lds<WM, WN, TM, TN>();
+  hipError_t err = ensure_panel_lds<WM, WN, TM, TN, STAGES>();
   float *ssq = a.fused_norm ? (float *)a.ws : nullptr;  // [split][M]
   if (err == hipSuccess && ssq) err = launch_row_squares(a, p.split_k, p.kt_per_split, ssq, s);
   if (err != hipSuccess) return err;
-  gemm_panel_kernel<WM, WN, TM, TN><<<groups * XCDS * p.tiles_m, 64 * S::NW, S::lds, s>>>(
+  gemm_panel_kernel<WM, WN, TM, TN, STAGES><<<groups * XCDS * p.tiles_m, 64 * S::NW, S::lds, s>>>(
       (const bf16_t *)a.x, (const uint4 *)a.w, e, a.M, a.N, a.K, p.tiles_m, p.tiles_n, p.split_k, p.kt_per_split, partial,
       a.norm_eps, two ? nullptr : ssq);
   err = hipGetLastError();

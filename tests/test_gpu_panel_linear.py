@@ -1,0 +1,115 @@
+"""The panel kernel (four waves, 16 x 16 tiles, written-out order): what its dispatch adds to the block kernel's tests, against
+the CPU oracle and the ring kernel's bits -- its own tiles 26 and 27, every tile at its edges, the row sums' own launch, rows
+and outputs off 16 bytes, and the float residual stream with its copies inside a step."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import sfo
+
+from paper_2511_20340_amd import binding as sfb
+from paper_2511_20340_amd.engine import Engine
+
+from gpu_common import dev, engine_only, linear_choice, rel_err, to_np
+
+pytestmark = pytest.mark.gpu
+
+ROWS = {15: 320, 16: 256, 17: 192, 18: 128, 26: 128, 27: 160, 28: 160}   # tile -> rows per workgroup
+COLS = {15: 256, 16: 256, 17: 256, 18: 256, 26: 128, 27: 128, 28: 128}
+RING_TILE = 2
+
+
+def engine():
+    return engine_only(synth.ModelShape("t", 1, 128, 2, 2, 64, 256, 512, "bf16"), 1, 64, 1)
+
+
+# rows and columns one short of, at and 8 beyond a tile; K: one slice, as many as are kept in LDS, more, a remainder.
+# fp32 accumulators of K <= 576 bf16 products: 1e-5 of the largest result, as for the other kernels; the norm folds its gain
+# into the weights and rounds them to bf16 once: 5e-3.
+@pytest.mark.parametrize("tile", ROWS)
+@pytest.mark.parametrize("K", [64, 128, 256, 576])
+def test_edges(tile, K):
+    eng = engine()
+    for M, N in [(ROWS[tile] - 1, COLS[tile]), (ROWS[tile], COLS[tile] + 8), (ROWS[tile] + 1, 2 * COLS[tile] - 8)]:
+        g = synth.rng(61, tile * 7919 + M * 31 + N + K)
+        x = synth.to_bf16_values(g.standard_normal((M, K), dtype=np.float32))
+        w = synth.to_bf16_values(g.standard_normal((N, K), dtype=np.float32) * 0.05)
+        gain = synth.to_bf16_values(1.0 + 0.5 * g.standard_normal(K, dtype=np.float32))
+        res = synth.to_bf16_values(g.standard_normal((M, N), dtype=np.float32))
+        xd, wd, gd = dev(x, "bf16"), dev(w, "bf16"), dev(gain, "bf16")
+        plain, folded = (eng.sf_pack_weight(wd), N), (eng.sf_pack_weight(wd, gain=gd), N)
+
+        def outputs(t):
+            eng.sf_tune_linear(t, 1)
+            r = dev(res, "bf16")
+            eng.sf_op_linear(xd, None, residual=r, y=r, packed=plain)
+            return (eng.sf_op_linear(xd, None, out_f32=True, packed=plain), eng.sf_op_linear(xd, None, packed=plain), r,
+                    eng.sf_op_rmsnorm_linear(xd, gd, None, out_f32=True, packed=folded),
+                    eng.sf_op_rmsnorm_linear(xd, gd, None, packed=folded))
+        try:
+            assert linear_choice(M, N, K, sfb.SF_LINEAR_NORM, tile=tile, split=1)[:2] == (sfb.SF_KERNEL_BLOCK, tile)
+            want = [t.clone() for t in outputs(RING_TILE)]
+            assert rel_err(to_np(want[0]), sfo.linear(x, w)) < 1e-5
+            assert rel_err(to_np(want[3]), sfo.linear(sfo.rmsnorm(x, gain, 1e-6), w)) < 5e-3
+            for got, ref in zip(outputs(tile), want):
+                assert torch.equal(got, ref), (M, N)
+        finally:
+            eng.sf_tune_linear(0, 0)
+
+
+@pytest.mark.parametrize("tile", ROWS)
+def test_special_values(tile):
+    """A NaN and both infinities in one row stay in that row; a row of zeros comes out as zeros behind the norm (eps)."""
+    M, N, K = 70, 136, 192
+    g = synth.rng(62, tile)
+    x = synth.to_bf16_values(g.standard_normal((M, K), dtype=np.float32))
+    w = synth.to_bf16_values(g.standard_normal((N, K), dtype=np.float32) * 0.05)
+    x[3, 5], x[17, 100], x[40, 0], x[41] = np.nan, np.inf, -np.inf, 0.0
+    eng = engine()
+    xd, wd = dev(x, "bf16"), dev(w, "bf16")
+    packed = (eng.sf_pack_weight(wd), N)
+    ones = torch.ones(K, device="cuda", dtype=torch.bfloat16)
+    try:
+        out = []
+        for t in (RING_TILE, tile):
+            eng.sf_tune_linear(t, 1)
+            out.append((eng.sf_op_linear(xd, None, out_f32=True, packed=packed),
+                        eng.sf_op_rmsnorm_linear(xd, ones, None, out_f32=True, packed=packed)))
+        for got, ref in zip(out[1], out[0]):
+            assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(got.nan_to_num(), ref.nan_to_num())
+        assert not out[1][1][41].any() and torch.isnan(out[1][0][3]).all()
+    finally:
+        eng.sf_tune_linear(0, 0)
+
+
+def test_a_norm_without_workspace_runs_on_tiles_that_need_none():
+    """The largest tiles' row sums go through the workspace: a caller that hands over none gets another tile."""
+    M, N, K = 640, 27648, 5120
+    assert linear_choice(M, N, K, sfb.SF_LINEAR_NORM)[:2] == (sfb.SF_KERNEL_BLOCK, 15)
+    assert linear_choice(M, N, K, sfb.SF_LINEAR_NORM, ws=0)[1] not in (15, 16, 17)
+    assert linear_choice(M, N, K, ws=0)[:2] == (sfb.SF_KERNEL_BLOCK, 15)
+
+
+@pytest.mark.parametrize("tile", ROWS)
+@pytest.mark.parametrize("split", [1, 2])
+def test_residual_stream_in_a_step(tile, split):
+    """A whole step forced onto the tile: norm, gate, float residual, bf16 copy, hooked copies, logits and arg-max; more rows
+    than the tile has, and not a multiple."""
+    shape, B, k, cap = synth.ModelShape("t", 2, 512, 4, 2, 128, 544, 1032, "bf16"), 67, 4, 64
+    weights = synth.target_weights(shape, 5, 0.05)
+    toks = synth.rng(63, tile).integers(0, shape.vocab, (B, k + 1)).astype(np.int32)
+    eng = Engine(shape.cfg(), B, cap, k)
+    eng.bind(weights, None)
+
+    def step(t):
+        eng.sf_tune_linear(t, split)
+        eng.set_state(kv_len=np.full(B, 2, np.int32), pending=toks[:, 0], n_new=np.ones(B, np.int32))
+        logits, ids = eng.sf_verify_step(k, torch.from_numpy(toks[:, 1:].copy()).cuda())
+        torch.cuda.synchronize()
+        return logits.clone(), ids.clone(), eng.hooks.clone(), eng.sf_kv_export("tk", 1), eng.sf_kv_export("tv", 1)
+    try:
+        for got, ref in zip(step(tile), step(RING_TILE)):
+            assert torch.equal(got, ref)
+    finally:
+        eng.sf_tune_linear(0, 0)
