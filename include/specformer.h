@@ -310,6 +310,23 @@ sf_status sf_op_argmax(const sf_ctx *ctx, const float *logits, int32_t M, int32_
 sf_status sf_op_argmax_noalloc(const sf_ctx *ctx, const float *logits, int32_t M, int32_t V, int32_t *ids,
                                void *stream);
 
+/* One block of a chunked prefill over the first n_seq sequences of a state: the target's layers over the block
+ * [pending, tokens], the commit of block_len rows, and the draft cache's context rows.  The state arrays, hooks and tokens are
+ * indexed 0..n_seq-1; sequence j's K/V live in cache slot slots[j] (dev [st->B], distinct, in [0, st->B)), so that a caller who
+ * orders its prompts by length runs each block over the sequences that have tokens left, without moving any cache.  Results
+ * are those of sf_verify_step, sf_accept_commit(force_len = block_len), sf_draft_step(k_draft) on the same rows; what later
+ * blocks overwrite anyway is not computed: choices and draft slots, except in the block with last != 0.
+ *   tokens       dev [n_seq][k]; pending[j] is the block's first token
+ *   block_len    dev [n_seq], in [0, k+1]: rows to commit
+ *   len_upper    host, >= every kv_len[j] before the call; len_after: after it
+ *   k_draft      slots of the draft step, 0: no draft cache to follow
+ *   target_ids   dev [n_seq][k+1] scratch, zero-filled once by the caller; last: the target's choices
+ *   accept_len, out_tokens, draft_tokens   dev, as in the three steps; draft_tokens: last only */
+sf_status sf_prefill_step(sf_ctx *ctx, const sf_state *st, int32_t k, const int32_t *tokens, const int32_t *block_len,
+                          int32_t n_seq, const int32_t *slots, int32_t len_upper, int32_t len_after, int32_t k_draft,
+                          int32_t last, int32_t *target_ids, int32_t *accept_len, int32_t *out_tokens,
+                          int32_t *draft_tokens, void *stream);
+
 /* The acceptance rule alone, on explicit state arrays (what sf_accept_commit launches after its call-order
  * check): all pointers dev; kv_len, pending: [B] in/out; n_new: [B] out; cu_new: [B+1] out. */
 sf_status sf_op_accept(const sf_ctx *ctx, int32_t B, int32_t k, const int32_t *draft_tokens,

@@ -247,10 +247,11 @@ void norm_swiglu_in(Run &r, const sf_model_cfg &m, const void *x, const void *xb
 
 void attention(Run &r, const sf_model_cfg &m, const void *q, const void *kc, const void *vc, const int32_t *kv_len,
                void *out, float *part_o, float *part_ml, int B, int n_q, int cap, int mode, int len_upper,
-               const void *qkv = nullptr, const float2 *table = nullptr, const int32_t *order = nullptr) {
+               const void *qkv = nullptr, const float2 *table = nullptr, const int32_t *order = nullptr,
+               const int32_t *slots = nullptr) {
   if (r.st != SF_OK) return;
   AttnArgs a{};
-  a.q = q; a.qkv = qkv; a.table = table; a.order = order; a.kc = kc; a.vc = vc; a.kv_len = kv_len; a.out = out; a.part_o = part_o; a.part_ml = part_ml;
+  a.q = q; a.qkv = qkv; a.table = table; a.order = order; a.slots = slots; a.kc = kc; a.vc = vc; a.kv_len = kv_len; a.out = out; a.part_o = part_o; a.part_ml = part_ml;
   a.B = B; a.n_q = n_q; a.Hq = m.n_q_heads; a.Hkv = m.n_kv_heads; a.hd = m.head_dim; a.cap = cap; a.mode = mode;
   const int n_rt = (m.n_q_heads / m.n_kv_heads * n_q + 31) / 32;
   a.chunk_tiles = r.c->tune_chunk > 0 ? r.c->tune_chunk : attn_chunk_tiles(B * m.n_kv_heads * n_rt, len_upper + n_q);
@@ -264,6 +265,14 @@ size_t kv_layer_bytes(const sf_model_cfg &m, int B, int cap) {
   return (size_t)B * m.n_kv_heads * cap * m.head_dim * esize(m.dtype);
 }
 
+// The sequences a pass runs over: rows and state arrays 0..n-1, whose caches are those of sequence slots[j] (null: j).
+// whole = false: of a verify pass the layers and their hooked states (no choices), of a draft step the context rows' K, V.
+struct Subset {
+  int n;
+  const int32_t *slots;
+  bool whole;
+};
+
 sf_status check_state(const sf_ctx *c, const sf_state *st, int k, bool need_draft) {
   if (!c || !st) return SF_EINVAL;
   if (!c->bound) return SF_ESTATE;
@@ -276,6 +285,179 @@ sf_status check_state(const sf_ctx *c, const sf_state *st, int k, bool need_draf
   if (((uintptr_t)st->workspace) % ALIGN) return SF_EINVAL;
   if (st->workspace_bytes < plan(c, st->B, k, st->cap).total) return SF_ECAPACITY;
   return SF_OK;
+}
+
+sf_status verify_pass(sf_ctx *c, const sf_state *st, int32_t k, const int32_t *draft, int32_t len_upper, float *logits,
+                      int32_t *target_ids, void *stream, const Subset &sub) {
+  sf_status v = check_state(c, st, k, false);
+  if (v != SF_OK) return v;
+  if (!target_ids || (k > 0 && !draft) || len_upper < 0) return SF_EINVAL;
+  const sf_model_cfg &m = c->tc;
+  const int B = sub.n, q = k + 1, M = B * q, cap = st->cap, qm = c->max_k + 1;
+  if ((long)len_upper + q > cap) return SF_ECAPACITY;
+  if ((v = check_attn_shape(m, q)) != SF_OK) return v;
+  const Arena A = plan(c, st->B, k, cap);
+  char *ws = (char *)st->workspace;
+  float *h = (float *)(ws + A.h);                                    // the residual stream
+  void *hb = m.dtype == SF_BF16 ? (void *)(ws + A.hb) : (void *)h;   // bf16: its copy for the matrix products
+  void *a = ws + A.a, *qkv = ws + A.qkv, *qr = ws + A.qr, *ao = ws + A.ao, *act = ws + A.act;
+  const int d = m.d_model, F = m.d_ffn, L = m.n_layers;
+  const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
+  const bool bf = m.dtype == SF_BF16;
+  Run r{c, (hipStream_t)stream};
+  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes;
+  // the target's logits for a position must not depend on how many draft positions are verified
+  // with it: every k of this state uses the K partition chosen for the largest block
+  r.plan_rows = st->B * qm;
+  // hooked states: group g holds the stream after layer hook_layer[g] (0 = the embedding)
+  const int hook_layer[4] = {0, L / 2, L - 1, L};
+  auto hook_mask_of = [&](int l) {
+    int mask = 0;
+    for (int g = 0; g < 4; ++g) mask |= (hook_layer[g] == l) << g;
+    return mask;
+  };
+  LAUNCH(K_EMBED_HOOK, launch_embed(c->tw.embed, st->pending, draft, h, bf ? hb : nullptr, st->hooks, hook_mask_of(0),
+                                    B, k, qm, d, m.vocab, m.dtype, r.s));
+  RopeArgs ra{};
+  ra.qkv = qkv; ra.q_out = qr; ra.kv_len = st->kv_len; ra.n_new = nullptr; ra.table = (float2 *)(ws + A.table);
+  ra.B = B; ra.n_q = q; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.cap = cap;
+  ra.kv_only = 0; ra.pos_mode = 0; ra.theta = m.rope_theta; ra.slots = sub.slots;
+  // bf16, more attention workgroups than compute units: the table kernel also ranks the sequences by length, and the
+  // attention launches of this call go by that order.  More than 512: the longest start first.  257 to 512 (what the chip
+  // holds at once with a head dim of 128, two to a compute unit): the longest 256 workgroups' sequences come first, then the
+  // rest from the shortest, so that a compute unit that takes two has a short one beside a long one.  Measured with a head
+  // dim of 128: 61 sequences of 100 to 1800, plain decoding, 2757 -> 2680 us a step; 64 of 256 to 2048, 5569 -> 5504.
+  const int attn_groups = B * m.n_kv_heads * ((m.n_q_heads / m.n_kv_heads * q + 31) / 32);
+  ra.order = bf && attn_groups > 256 ? (int32_t *)(ws + A.order) : nullptr;
+  ra.pair_from = attn_groups > 512 ? 0 : std::max(1, 256 * B / attn_groups);
+  ra.dev_err = (int32_t *)(ws + A.dev_err); ra.len_upper = len_upper;
+  LAUNCH(K_ROPE, launch_rope_table(ra, r.s));
+  const size_t lb = kv_layer_bytes(m, st->B, cap);
+  for (int l = 0; l < L && r.st == SF_OK; ++l) {
+    void *kc = (char *)st->tk + l * lb, *vc = (char *)st->tv + l * lb;
+    norm_gemm(r, m, h, hb, c->attn_norm[l], c->wqkv[l], qkv, M, nq + 2 * nkv, d, 0);
+    ra.kc = kc; ra.vc = vc;
+    // bf16: the attention kernel rotates Q and K and appends the block's K, V rows itself
+    if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
+    attention(r, m, qr, kc, vc, st->kv_len, ao, (float *)(ws + A.part_o), (float *)(ws + A.part_ml), B, q, cap,
+              SF_MASK_CAUSAL, len_upper, bf ? qkv : nullptr, ra.table, ra.order, sub.slots);
+    // h += attention . W_O, and h += W_down . act: float sums; bf16 mode also refreshes the bf16 copy
+    GemmExtra ex;
+    ex.res_f32 = 1; ex.y2 = hb;
+    gemm(r, m.dtype, ao, c->wo[l], nullptr, h, h, M, d, nq, 1, 0, 0, 0.f, &ex);
+    norm_swiglu_in(r, m, h, hb, c->ffn_norm[l], c->w_gate_up[l], act, M, F, d);
+    const int mask = hook_mask_of(l + 1);  // the stream after this layer is hooked state(s) `mask`
+    if (mask) { ex.hooks = st->hooks; ex.hook_mask = mask; ex.hook_q = q; ex.hook_qmax = qm; }
+    gemm(r, m.dtype, act, c->w_down[l], nullptr, h, h, M, d, F, 1, 0, 0, 0.f, &ex);
+  }
+  if (!sub.whole) return r.st;
+  // the LM head serves two norms (this one and the draft's), so no gain is folded into it
+  if (bf) norm(r, m, h, c->tw.final_norm, a, M, 1, 0, 1, 1, nullptr, 1);
+  lm_head_argmax(r, m, bf ? a : h, c->tw.lm_head, logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
+                 (int32_t *)(ws + A.pidx), target_ids, M, c->tw.final_norm);
+  return r.st;
+}
+
+sf_status draft_pass(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int32_t len_upper, int32_t *draft_tokens,
+                     float *draft_logits, void *stream, const Subset &sub) {
+  sf_status v = check_state(c, st, k, true);
+  if (v != SF_OK) return v;
+  if (k == 0) return SF_OK;
+  const bool two_stage = (mask & SF_DRAFT_TWO_STAGE) != 0;
+  mask &= ~SF_DRAFT_TWO_STAGE;
+  if (!draft_tokens || len_upper < 0 || (mask != SF_MASK_CAUSAL && mask != SF_MASK_BIDIR)) return SF_EINVAL;
+  const sf_model_cfg &m = c->dc;
+  const int B = sub.n, cap = st->cap, qm = c->max_k + 1, Mh = B * qm, Ms = B * k;
+  if ((long)len_upper + k > cap) return SF_ECAPACITY;
+  if ((v = check_attn_shape(m, k)) != SF_OK) return v;
+  const sf_draft_weights &w = c->dw;
+  if (two_stage && (!w.sa_norm || !w.sa_wqkv || !w.sa_wo)) return SF_ESTATE;
+  if (two_stage && k > TK) return SF_EUNSUPPORTED;
+  const Arena A = plan(c, st->B, k, cap);
+  char *ws = (char *)st->workspace;
+  const bool bf = m.dtype == SF_BF16;
+  void *a = ws + A.a, *qkv = ws + A.qkv, *qr = ws + A.qr, *ao = ws + A.ao, *act = ws + A.act;
+  void *f4 = ws + A.f4, *x = ws + A.x, *kvc = ws + A.kvc, *xl = ws + A.xl;
+  float *s0 = (float *)(ws + A.s0);                                    // the slot layer's residual stream
+  void *s0b = bf ? (void *)(ws + A.s0b) : (void *)s0;                  // bf16: its copy for the matrix products
+  float *part_o = (float *)(ws + A.part_o), *part_ml = (float *)(ws + A.part_ml);
+  const int d = m.d_model, F = m.d_ffn;
+  const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
+  const size_t es = esize(m.dtype);
+  Run r{c, (hipStream_t)stream};
+  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes;
+  r.plan_rows = B < st->B ? st->B * qm : 0;  // a part of the batch keeps the whole batch's order of sums
+  // context rows: Grouped RMSNorm -> W_D -> K,V of the draft attention layer at the rows' positions
+  norm(r, m, st->hooks, w.group_norm, f4, Mh * 4, 4, 1, qm, qm, nullptr);
+  gemm(r, m.dtype, f4, w.w_ds, nullptr, nullptr, x, Mh, d, 4 * d, 0);
+  // K and V rows of wqkv start after the nq query rows (a whole number of packed 32-row blocks)
+  const size_t kv_off = bf ? packed_weight_bytes(nq, d, m.dtype) : (size_t)nq * d * es;
+  norm_gemm(r, m, x, x, w.attn_norm, (const char *)w.wqkv + kv_off, kvc, Mh, 2 * nkv, d, 0);
+  RopeArgs ra{};
+  ra.qkv = kvc; ra.q_out = nullptr; ra.kc = st->dk; ra.vc = st->dv; ra.kv_len = st->kv_len; ra.n_new = st->n_new;
+  ra.table = (float2 *)(ws + A.table);
+  ra.B = B; ra.n_q = qm; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.cap = cap;
+  ra.kv_only = 1; ra.pos_mode = 1; ra.theta = m.rope_theta; ra.slots = sub.slots;
+  // the same launch fills the slots' table (positions kv_len[b] + s) when they sit behind the cached context
+  float2 *slot_table = ra.table + (size_t)Mh * (m.head_dim / 2);
+  if (!two_stage && sub.whole) {
+    ra.table2 = slot_table; ra.n_q2 = k;
+    ra.dev_err = (int32_t *)(ws + A.dev_err); ra.len_upper = len_upper;
+  }
+  LAUNCH(K_ROPE, launch_rope_table(ra, r.s));
+  LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
+  ra.table2 = nullptr; ra.dev_err = nullptr;
+  if (!sub.whole) return r.st;
+  const void *norm_s = w.attn_norm, *wqkv_s = w.wqkv, *wo_s = w.wo;  // the slot attention's parameters
+  const void *kc_s = st->dk, *vc_s = st->dv;
+  const int32_t *len_s = st->kv_len;
+  int cap_s = cap, len_upper_s = len_upper;
+  if (!two_stage) {
+    // positional FFN on the newest committed row -> k slot states
+    norm(r, m, x, w.pos_norm, xl, B, 1, 2, qm, qm, st->n_new);
+  } else {
+    // The context attention's own output at the newest row (its K/V are in the cache by now):
+    // I_D = X + W_O . attention(RoPE(W_Q . RMS(X)), keys up to and including the row itself).
+    void *x_last = ws + A.x_last, *q1 = ws + A.q1, *qr1 = ws + A.qr1, *ao1 = ws + A.ao1;
+    float *id_last = (float *)(ws + A.id_last);
+    int32_t *len_m1 = (int32_t *)(ws + A.len_m1);
+    LAUNCH(K_EMBED_HOOK, launch_gather_last(x, x_last, st->n_new, st->kv_len, len_m1, B, qm, d, m.dtype, r.s));
+    norm_gemm(r, m, x_last, x_last, w.attn_norm, w.wqkv, q1, B, nq, d, 0);  // the nq query rows lead wqkv
+    RopeArgs rq{};
+    rq.qkv = q1; rq.q_out = qr1; rq.kc = nullptr; rq.vc = nullptr; rq.kv_len = len_m1; rq.n_new = nullptr;
+    rq.table = ra.table; rq.B = B; rq.n_q = 1; rq.Hq = m.n_q_heads; rq.Hkv = 0; rq.hd = m.head_dim; rq.cap = cap;
+    rq.kv_only = 0; rq.pos_mode = 0; rq.theta = m.rope_theta;
+    LAUNCH(K_ROPE, launch_rope_table(rq, r.s));
+    LAUNCH(K_ROPE, launch_rope_kv(rq, m.dtype, r.s));
+    attention(r, m, qr1, st->dk, st->dv, len_m1, ao1, part_o, part_ml, B, 1, cap, SF_MASK_CAUSAL, len_upper);
+    gemm(r, m.dtype, ao1, w.wo, nullptr, x_last, id_last, B, d, nq, 1);  // float row of the stream
+    norm(r, m, id_last, w.pos_norm, xl, B, 1, 3, 1, 1, st->n_new, 1);
+    // the slots attend to each other only: an empty prefix in a one-tile cache of their own
+    norm_s = w.sa_norm; wqkv_s = w.sa_wqkv; wo_s = w.sa_wo;
+    kc_s = ws + A.kc2; vc_s = ws + A.vc2; len_s = (const int32_t *)(ws + A.zeros);
+    cap_s = TK; len_upper_s = 0;
+  }
+  GemmExtra ex;
+  ex.y2 = s0b;
+  gemm(r, m.dtype, xl, w.w_pos, w.b_pos, nullptr, s0, B, k * d, d, 1, 0, 0, 0.f, &ex);
+  // one attention + SwiGLU layer over the slots
+  norm_gemm(r, m, s0, s0b, norm_s, wqkv_s, qkv, Ms, nq + 2 * nkv, d, 0);
+  ra.qkv = qkv; ra.q_out = qr; ra.kc = (void *)kc_s; ra.vc = (void *)vc_s; ra.kv_len = len_s; ra.n_new = nullptr;
+  ra.n_q = k; ra.cap = cap_s; ra.kv_only = 0; ra.pos_mode = 0; ra.table = slot_table;
+  if (two_stage) LAUNCH(K_ROPE, launch_rope_table(ra, r.s));  // slots at positions 0..k-1 of their own tile
+  // bf16: the attention kernel rotates the slots' Q and K and appends their K, V rows itself
+  if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
+  attention(r, m, qr, kc_s, vc_s, len_s, ao, part_o, part_ml, B, k, cap_s, mask, len_upper_s, bf ? qkv : nullptr,
+            ra.table, nullptr, two_stage ? nullptr : sub.slots);
+  ex.res_f32 = 1;
+  gemm(r, m.dtype, ao, wo_s, nullptr, s0, s0, Ms, d, nq, 1, 0, 0, 0.f, &ex);
+  norm_swiglu_in(r, m, s0, s0b, w.ffn_norm, w.w_gate_up, act, Ms, F, d);
+  ex.y2 = nullptr;
+  gemm(r, m.dtype, act, w.w_down, nullptr, s0, s0, Ms, d, F, 1, 0, 0, 0.f, &ex);
+  if (bf) norm(r, m, s0, w.out_norm, a, Ms, 1, 0, 1, 1, nullptr, 1);
+  lm_head_argmax(r, m, bf ? a : s0, c->tw.lm_head, draft_logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
+                 (int32_t *)(ws + A.pidx), draft_tokens, Ms, w.out_norm);
+  return r.st;
 }
 
 }  // namespace
@@ -356,173 +538,35 @@ sf_status sf_bind(sf_ctx *c, const sf_target_weights *t, const sf_draft_weights 
 
 sf_status sf_verify_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_t *draft, int32_t len_upper,
                          float *logits, int32_t *target_ids, void *stream) {
-  sf_status v = check_state(c, st, k, false);
-  if (v != SF_OK) return v;
-  if (!target_ids || (k > 0 && !draft) || len_upper < 0) return SF_EINVAL;
-  const sf_model_cfg &m = c->tc;
-  const int B = st->B, q = k + 1, M = B * q, cap = st->cap, qm = c->max_k + 1;
-  if ((long)len_upper + q > cap) return SF_ECAPACITY;
-  if ((v = check_attn_shape(m, q)) != SF_OK) return v;
-  const Arena A = plan(c, B, k, cap);
-  char *ws = (char *)st->workspace;
-  float *h = (float *)(ws + A.h);                                    // the residual stream
-  void *hb = m.dtype == SF_BF16 ? (void *)(ws + A.hb) : (void *)h;   // bf16: its copy for the matrix products
-  void *a = ws + A.a, *qkv = ws + A.qkv, *qr = ws + A.qr, *ao = ws + A.ao, *act = ws + A.act;
-  const int d = m.d_model, F = m.d_ffn, L = m.n_layers;
-  const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
-  const bool bf = m.dtype == SF_BF16;
-  Run r{c, (hipStream_t)stream};
-  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes;
-  // the target's logits for a position must not depend on how many draft positions are verified
-  // with it: every k of this state uses the K partition chosen for the largest block
-  r.plan_rows = B * qm;
-  // hooked states: group g holds the stream after layer hook_layer[g] (0 = the embedding)
-  const int hook_layer[4] = {0, L / 2, L - 1, L};
-  auto hook_mask_of = [&](int l) {
-    int mask = 0;
-    for (int g = 0; g < 4; ++g) mask |= (hook_layer[g] == l) << g;
-    return mask;
-  };
-  LAUNCH(K_EMBED_HOOK, launch_embed(c->tw.embed, st->pending, draft, h, bf ? hb : nullptr, st->hooks, hook_mask_of(0),
-                                    B, k, qm, d, m.vocab, m.dtype, r.s));
-  RopeArgs ra{};
-  ra.qkv = qkv; ra.q_out = qr; ra.kv_len = st->kv_len; ra.n_new = nullptr; ra.table = (float2 *)(ws + A.table);
-  ra.B = B; ra.n_q = q; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.cap = cap;
-  ra.kv_only = 0; ra.pos_mode = 0; ra.theta = m.rope_theta;
-  // bf16, more attention workgroups than compute units: the table kernel also ranks the sequences by length, and the
-  // attention launches of this call go by that order.  More than 512: the longest start first.  257 to 512 (what the chip
-  // holds at once with a head dim of 128, two to a compute unit): the longest 256 workgroups' sequences come first, then the
-  // rest from the shortest, so that a compute unit that takes two has a short one beside a long one.  Measured with a head
-  // dim of 128: 61 sequences of 100 to 1800, plain decoding, 2757 -> 2680 us a step; 64 of 256 to 2048, 5569 -> 5504.
-  const int attn_groups = B * m.n_kv_heads * ((m.n_q_heads / m.n_kv_heads * q + 31) / 32);
-  ra.order = bf && attn_groups > 256 ? (int32_t *)(ws + A.order) : nullptr;
-  ra.pair_from = attn_groups > 512 ? 0 : std::max(1, 256 * B / attn_groups);
-  ra.dev_err = (int32_t *)(ws + A.dev_err); ra.len_upper = len_upper;
-  LAUNCH(K_ROPE, launch_rope_table(ra, r.s));
-  const size_t lb = kv_layer_bytes(m, B, cap);
-  for (int l = 0; l < L && r.st == SF_OK; ++l) {
-    void *kc = (char *)st->tk + l * lb, *vc = (char *)st->tv + l * lb;
-    norm_gemm(r, m, h, hb, c->attn_norm[l], c->wqkv[l], qkv, M, nq + 2 * nkv, d, 0);
-    ra.kc = kc; ra.vc = vc;
-    // bf16: the attention kernel rotates Q and K and appends the block's K, V rows itself
-    if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
-    attention(r, m, qr, kc, vc, st->kv_len, ao, (float *)(ws + A.part_o), (float *)(ws + A.part_ml), B, q, cap,
-              SF_MASK_CAUSAL, len_upper, bf ? qkv : nullptr, ra.table, ra.order);
-    // h += attention . W_O, and h += W_down . act: float sums; bf16 mode also refreshes the bf16 copy
-    GemmExtra ex;
-    ex.res_f32 = 1; ex.y2 = hb;
-    gemm(r, m.dtype, ao, c->wo[l], nullptr, h, h, M, d, nq, 1, 0, 0, 0.f, &ex);
-    norm_swiglu_in(r, m, h, hb, c->ffn_norm[l], c->w_gate_up[l], act, M, F, d);
-    const int mask = hook_mask_of(l + 1);  // the stream after this layer is hooked state(s) `mask`
-    if (mask) { ex.hooks = st->hooks; ex.hook_mask = mask; ex.hook_q = q; ex.hook_qmax = qm; }
-    gemm(r, m.dtype, act, c->w_down[l], nullptr, h, h, M, d, F, 1, 0, 0, 0.f, &ex);
-  }
-  // the LM head serves two norms (this one and the draft's), so no gain is folded into it
-  if (bf) norm(r, m, h, c->tw.final_norm, a, M, 1, 0, 1, 1, nullptr, 1);
-  lm_head_argmax(r, m, bf ? a : h, c->tw.lm_head, logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
-                 (int32_t *)(ws + A.pidx), target_ids, M, c->tw.final_norm);
-  if (r.st == SF_OK) { c->verified_state = st->kv_len; c->verified_k = k; }
-  return r.st;
+  const sf_status v = verify_pass(c, st, k, draft, len_upper, logits, target_ids, stream, {st ? st->B : 0, nullptr, true});
+  if (v == SF_OK) { c->verified_state = st->kv_len; c->verified_k = k; }
+  return v;
 }
 
-sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int32_t len_upper,
-                        int32_t *draft_tokens, float *draft_logits, void *stream) {
-  sf_status v = check_state(c, st, k, true);
+sf_status sf_draft_step(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int32_t len_upper, int32_t *draft_tokens,
+                        float *draft_logits, void *stream) {
+  return draft_pass(c, st, k, mask, len_upper, draft_tokens, draft_logits, stream, {st ? st->B : 0, nullptr, true});
+}
+
+sf_status sf_prefill_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_t *tokens, const int32_t *block_len,
+                          int32_t n_seq, const int32_t *slots, int32_t len_upper, int32_t len_after, int32_t k_draft,
+                          int32_t last, int32_t *target_ids, int32_t *accept_len, int32_t *out_tokens,
+                          int32_t *draft_tokens, void *stream) {
+  sf_status v = check_state(c, st, k, k_draft > 0);
   if (v != SF_OK) return v;
-  if (k == 0) return SF_OK;
-  const bool two_stage = (mask & SF_DRAFT_TWO_STAGE) != 0;
-  mask &= ~SF_DRAFT_TWO_STAGE;
-  if (!draft_tokens || len_upper < 0 || (mask != SF_MASK_CAUSAL && mask != SF_MASK_BIDIR)) return SF_EINVAL;
-  const sf_model_cfg &m = c->dc;
-  const int B = st->B, cap = st->cap, qm = c->max_k + 1, Mh = B * qm, Ms = B * k;
-  if ((long)len_upper + k > cap) return SF_ECAPACITY;
-  if ((v = check_attn_shape(m, k)) != SF_OK) return v;
-  const sf_draft_weights &w = c->dw;
-  if (two_stage && (!w.sa_norm || !w.sa_wqkv || !w.sa_wo)) return SF_ESTATE;
-  if (two_stage && k > TK) return SF_EUNSUPPORTED;
-  const Arena A = plan(c, B, k, cap);
-  char *ws = (char *)st->workspace;
-  const bool bf = m.dtype == SF_BF16;
-  void *a = ws + A.a, *qkv = ws + A.qkv, *qr = ws + A.qr, *ao = ws + A.ao, *act = ws + A.act;
-  void *f4 = ws + A.f4, *x = ws + A.x, *kvc = ws + A.kvc, *xl = ws + A.xl;
-  float *s0 = (float *)(ws + A.s0);                                    // the slot layer's residual stream
-  void *s0b = bf ? (void *)(ws + A.s0b) : (void *)s0;                  // bf16: its copy for the matrix products
-  float *part_o = (float *)(ws + A.part_o), *part_ml = (float *)(ws + A.part_ml);
-  const int d = m.d_model, F = m.d_ffn;
-  const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
-  const size_t es = esize(m.dtype);
+  if (n_seq < 1 || n_seq > st->B || !slots || !block_len || !target_ids || !accept_len || !out_tokens) return SF_EINVAL;
+  if (k_draft < 0 || k_draft > c->max_k || (k_draft > 0 && !draft_tokens) || len_after < 0) return SF_EINVAL;
+  if (last && (long)len_after + k_draft > st->cap) return SF_ECAPACITY;
+  const Subset sub{n_seq, slots, last != 0};
+  if ((v = verify_pass(c, st, k, tokens, len_upper, nullptr, target_ids, stream, sub)) != SF_OK) return v;
+  c->verified_state = nullptr;  // committed right here
+  c->verified_k = -1;
   Run r{c, (hipStream_t)stream};
-  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes;
-  // context rows: Grouped RMSNorm -> W_D -> K,V of the draft attention layer at the rows' positions
-  norm(r, m, st->hooks, w.group_norm, f4, Mh * 4, 4, 1, qm, qm, nullptr);
-  gemm(r, m.dtype, f4, w.w_ds, nullptr, nullptr, x, Mh, d, 4 * d, 0);
-  // K and V rows of wqkv start after the nq query rows (a whole number of packed 32-row blocks)
-  const size_t kv_off = bf ? packed_weight_bytes(nq, d, m.dtype) : (size_t)nq * d * es;
-  norm_gemm(r, m, x, x, w.attn_norm, (const char *)w.wqkv + kv_off, kvc, Mh, 2 * nkv, d, 0);
-  RopeArgs ra{};
-  ra.qkv = kvc; ra.q_out = nullptr; ra.kc = st->dk; ra.vc = st->dv; ra.kv_len = st->kv_len; ra.n_new = st->n_new;
-  ra.table = (float2 *)(ws + A.table);
-  ra.B = B; ra.n_q = qm; ra.Hq = m.n_q_heads; ra.Hkv = m.n_kv_heads; ra.hd = m.head_dim; ra.cap = cap;
-  ra.kv_only = 1; ra.pos_mode = 1; ra.theta = m.rope_theta;
-  // the same launch fills the slots' table (positions kv_len[b] + s) when they sit behind the cached context
-  float2 *slot_table = ra.table + (size_t)Mh * (m.head_dim / 2);
-  if (!two_stage) {
-    ra.table2 = slot_table; ra.n_q2 = k;
-    ra.dev_err = (int32_t *)(ws + A.dev_err); ra.len_upper = len_upper;
-  }
-  LAUNCH(K_ROPE, launch_rope_table(ra, r.s));
-  LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
-  ra.table2 = nullptr; ra.dev_err = nullptr;
-  const void *norm_s = w.attn_norm, *wqkv_s = w.wqkv, *wo_s = w.wo;  // the slot attention's parameters
-  const void *kc_s = st->dk, *vc_s = st->dv;
-  const int32_t *len_s = st->kv_len;
-  int cap_s = cap, len_upper_s = len_upper;
-  if (!two_stage) {
-    // positional FFN on the newest committed row -> k slot states
-    norm(r, m, x, w.pos_norm, xl, B, 1, 2, qm, qm, st->n_new);
-  } else {
-    // The context attention's own output at the newest row (its K/V are in the cache by now):
-    // I_D = X + W_O . attention(RoPE(W_Q . RMS(X)), keys up to and including the row itself).
-    void *x_last = ws + A.x_last, *q1 = ws + A.q1, *qr1 = ws + A.qr1, *ao1 = ws + A.ao1;
-    float *id_last = (float *)(ws + A.id_last);
-    int32_t *len_m1 = (int32_t *)(ws + A.len_m1);
-    LAUNCH(K_EMBED_HOOK, launch_gather_last(x, x_last, st->n_new, st->kv_len, len_m1, B, qm, d, m.dtype, r.s));
-    norm_gemm(r, m, x_last, x_last, w.attn_norm, w.wqkv, q1, B, nq, d, 0);  // the nq query rows lead wqkv
-    RopeArgs rq{};
-    rq.qkv = q1; rq.q_out = qr1; rq.kc = nullptr; rq.vc = nullptr; rq.kv_len = len_m1; rq.n_new = nullptr;
-    rq.table = ra.table; rq.B = B; rq.n_q = 1; rq.Hq = m.n_q_heads; rq.Hkv = 0; rq.hd = m.head_dim; rq.cap = cap;
-    rq.kv_only = 0; rq.pos_mode = 0; rq.theta = m.rope_theta;
-    LAUNCH(K_ROPE, launch_rope_table(rq, r.s));
-    LAUNCH(K_ROPE, launch_rope_kv(rq, m.dtype, r.s));
-    attention(r, m, qr1, st->dk, st->dv, len_m1, ao1, part_o, part_ml, B, 1, cap, SF_MASK_CAUSAL, len_upper);
-    gemm(r, m.dtype, ao1, w.wo, nullptr, x_last, id_last, B, d, nq, 1);  // float row of the stream
-    norm(r, m, id_last, w.pos_norm, xl, B, 1, 3, 1, 1, st->n_new, 1);
-    // the slots attend to each other only: an empty prefix in a one-tile cache of their own
-    norm_s = w.sa_norm; wqkv_s = w.sa_wqkv; wo_s = w.sa_wo;
-    kc_s = ws + A.kc2; vc_s = ws + A.vc2; len_s = (const int32_t *)(ws + A.zeros);
-    cap_s = TK; len_upper_s = 0;
-  }
-  GemmExtra ex;
-  ex.y2 = s0b;
-  gemm(r, m.dtype, xl, w.w_pos, w.b_pos, nullptr, s0, B, k * d, d, 1, 0, 0, 0.f, &ex);
-  // one attention + SwiGLU layer over the slots
-  norm_gemm(r, m, s0, s0b, norm_s, wqkv_s, qkv, Ms, nq + 2 * nkv, d, 0);
-  ra.qkv = qkv; ra.q_out = qr; ra.kc = (void *)kc_s; ra.vc = (void *)vc_s; ra.kv_len = len_s; ra.n_new = nullptr;
-  ra.n_q = k; ra.cap = cap_s; ra.kv_only = 0; ra.pos_mode = 0; ra.table = slot_table;
-  if (two_stage) LAUNCH(K_ROPE, launch_rope_table(ra, r.s));  // slots at positions 0..k-1 of their own tile
-  // bf16: the attention kernel rotates the slots' Q and K and appends their K, V rows itself
-  if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
-  attention(r, m, qr, kc_s, vc_s, len_s, ao, part_o, part_ml, B, k, cap_s, mask, len_upper_s, bf ? qkv : nullptr,
-            ra.table);
-  ex.res_f32 = 1;
-  gemm(r, m.dtype, ao, wo_s, nullptr, s0, s0, Ms, d, nq, 1, 0, 0, 0.f, &ex);
-  norm_swiglu_in(r, m, s0, s0b, w.ffn_norm, w.w_gate_up, act, Ms, F, d);
-  ex.y2 = nullptr;
-  gemm(r, m.dtype, act, w.w_down, nullptr, s0, s0, Ms, d, F, 1, 0, 0, 0.f, &ex);
-  if (bf) norm(r, m, s0, w.out_norm, a, Ms, 1, 0, 1, 1, nullptr, 1);
-  lm_head_argmax(r, m, bf ? a : s0, c->tw.lm_head, draft_logits, (float *)(ws + A.logits), (float *)(ws + A.pmax),
-                 (int32_t *)(ws + A.pidx), draft_tokens, Ms, w.out_norm);
-  return r.st;
+  AcceptArgs a{target_ids, tokens, block_len, accept_len, out_tokens, st->kv_len, st->pending, st->n_new, st->cu_new,
+               n_seq, k};
+  LAUNCH(K_ACCEPT, launch_accept(a, r.s));
+  if (r.st != SF_OK || k_draft == 0) return r.st;
+  return draft_pass(c, st, k_draft, SF_MASK_BIDIR, last ? len_after : 0, draft_tokens, nullptr, stream, sub);
 }
 
 sf_status sf_accept_commit(sf_ctx *c, const sf_state *st, int32_t k, const int32_t *draft, const int32_t *target_ids,

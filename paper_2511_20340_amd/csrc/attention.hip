@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 4 : 2) void attn_bf16_kernel(
     const int32_t *__restrict__ kv_len, bf16_t *__restrict__ O, float *__restrict__ part_o,
     float *__restrict__ part_ml, int n_q, int Hq, int Hkv, int cap, int mode, int chunk_tiles,
     int n_chunks, int n_rt, float scale_log2e, const float2 *__restrict__ table,
-    const int32_t *__restrict__ order) {
+    const int32_t *__restrict__ order, const int32_t *__restrict__ slots) {
   constexpr int KS = HD / 16;       // k-steps of the QK^T product
   constexpr int NT = HD / 32;       // 32-column tiles of the output
   constexpr int TILE_U4 = HD * 4;   // 16-byte units per 32-key tile (32*HD*2/16)
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256, HD == 64 ? 4 : 2) void attn_bf16_kernel(
   const int qi = row_ok ? r / G : 0;    // block index of the row
   const int qh = g * G + (row_ok ? r % G : 0);
 
-  const size_t seq_base = ((size_t)b * Hkv + g) * (size_t)(cap / TK) * TILE_U4;
+  const size_t seq_base = ((size_t)(slots ? slots[b] : b) * Hkv + g) * (size_t)(cap / TK) * TILE_U4;
   const uint4 *Kb = Kc + seq_base + lane;
   const uint4 *Vb = Vc + seq_base + lane;
   int t = t_begin + wave;
@@ -369,15 +369,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
                                                        const float *__restrict__ Vc,
                                                        const int32_t *__restrict__ kv_len, float *__restrict__ O,
                                                        int n_q, int Hq, int Hkv, int hd, int cap, int mode,
-                                                       float scale) {
+                                                       float scale, const int32_t *__restrict__ slots) {
   __shared__ __attribute__((aligned(16))) float sq[256];
   __shared__ float sc[CK], red[8];
   __shared__ f32x4 so[256];
   const int hq = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = hq / (Hq / Hkv);
   const int len = min(kv_len[b], cap - n_q), total = len + (mode == SF_MASK_BIDIR ? n_q : i + 1);
-  const float *K = Kc + ((size_t)b * Hkv + g) * (size_t)cap * hd;
-  const float *V = Vc + ((size_t)b * Hkv + g) * (size_t)cap * hd;
+  const size_t cache = ((size_t)(slots ? slots[b] : b) * Hkv + g) * (size_t)cap * hd;
+  const float *K = Kc + cache, *V = Vc + cache;
   const size_t row = (((size_t)b * n_q + i) * Hq + hq) * hd;
   if (tid < hd) sq[tid] = Q[row + tid];
   __syncthreads();
@@ -477,7 +477,7 @@ hipError_t launch_attention_bf16(const AttnArgs &a, hipStream_t s) {
 #define SF_ATTN_LAUNCH(HD_, FUSE_, ONCE_)                                                                   \
   attn_bf16_kernel<HD_, FUSE_, ONCE_><<<grid, block, lds, s>>>(                                             \
       q, (const uint4 *)a.kc, (const uint4 *)a.vc, a.kv_len, (bf16_t *)a.out, a.part_o, a.part_ml, a.n_q,   \
-      a.Hq, a.Hkv, a.cap, a.mode, a.chunk_tiles, a.n_chunks, n_rt, scale_log2e, a.table, a.order)
+      a.Hq, a.Hkv, a.cap, a.mode, a.chunk_tiles, a.n_chunks, n_rt, scale_log2e, a.table, a.order, a.slots)
 #define SF_ATTN_PICK(HD_)                                                                                   \
   do {                                                                                                      \
     if (n_rt == 1) { if (a.qkv) SF_ATTN_LAUNCH(HD_, 1, 1); else SF_ATTN_LAUNCH(HD_, 0, 1); }                \
@@ -502,7 +502,7 @@ hipError_t launch_attention_combine(const AttnArgs &a, hipStream_t s) {
 hipError_t launch_attention_f32(const AttnArgs &a, hipStream_t s) {
   attn_f32_kernel<<<dim3(a.Hq, a.n_q, a.B), 256, 0, s>>>((const float *)a.q, (const float *)a.kc, (const float *)a.vc,
                                                          a.kv_len, (float *)a.out, a.n_q, a.Hq, a.Hkv, a.hd, a.cap,
-                                                         a.mode, 1.f / sqrtf((float)a.hd));
+                                                         a.mode, 1.f / sqrtf((float)a.hd), a.slots);
   return hipGetLastError();
 }
 

@@ -167,7 +167,8 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const T *__restrict__ QKV,
                                                       const int32_t *__restrict__ kv_len,
                                                       const int32_t *__restrict__ n_new,
                                                       const float2 *__restrict__ table, int n_q, int Hq, int Hkv,
-                                                      int hd, int cap, int kv_only, int pos_mode) {
+                                                      int hd, int cap, int kv_only, int pos_mode,
+                                                      const int32_t *__restrict__ slots) {
   const int row = blockIdx.x, b = row / n_q, i = row % n_q;
   const int half = hd >> 1;
   const int nq_cols = kv_only ? 0 : Hq * hd, nkv = Hkv * hd;
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const T *__restrict__ QKV,
     Elem<T>::st(Qo + (size_t)row * nq_cols + hh * hd + e + half, q1);
   }
   if (!valid) return;
-  const size_t tile = pos / TK;
+  const size_t tile = pos / TK, slot = slots ? slots[b] : b;
   const int a_in = pos % TK;
   for (int x = threadIdx.x; x < Hkv * half; x += 256) {
     const int g = x / half, e = x % half;
@@ -200,13 +201,13 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(const T *__restrict__ QKV,
     const float v0 = Elem<T>::ld(src + nq_cols + nkv + g * hd + e);
     const float v1 = Elem<T>::ld(src + nq_cols + nkv + g * hd + e + half);
     if (sizeof(T) == 2) {
-      const size_t base = (((size_t)b * Hkv + g) * (cap / TK) + tile) * (size_t)(TK * hd);
+      const size_t base = ((slot * Hkv + g) * (cap / TK) + tile) * (size_t)(TK * hd);
       Elem<T>::st(Kc + base + k_tile_off(a_in, e), k0);
       Elem<T>::st(Kc + base + k_tile_off(a_in, e + half), k1);
       Elem<T>::st(Vc + base + v_tile_off(a_in, e, hd), v0);
       Elem<T>::st(Vc + base + v_tile_off(a_in, e + half, hd), v1);
     } else {
-      const size_t base = (((size_t)b * Hkv + g) * cap + pos) * (size_t)hd;
+      const size_t base = ((slot * Hkv + g) * cap + pos) * (size_t)hd;
       Elem<T>::st(Kc + base + e, k0);
       Elem<T>::st(Kc + base + e + half, k1);
       Elem<T>::st(Vc + base + e, v0);
@@ -296,7 +297,7 @@ template <typename T>
 hipError_t rope_kv_t(const RopeArgs &a, hipStream_t s) {
   const int M = a.B * a.n_q;
   rope_kv_kernel<T><<<M, 256, 0, s>>>((const T *)a.qkv, (T *)a.q_out, (T *)a.kc, (T *)a.vc, a.kv_len, a.n_new,
-                                      a.table, a.n_q, a.Hq, a.Hkv, a.hd, a.cap, a.kv_only, a.pos_mode);
+                                      a.table, a.n_q, a.Hq, a.Hkv, a.hd, a.cap, a.kv_only, a.pos_mode, a.slots);
   return hipGetLastError();
 }
 

@@ -80,6 +80,7 @@ struct AttnArgs {
   const void *qkv;
   const float2 *table;
   const int32_t *order;  // bf16 only, optional [B]: a permutation of the sequences, workgroups of order[0] start first
+  const int32_t *slots;  // optional [B]: sequence b's keys and values are those of cache slot slots[b]
   const void *kc, *vc;
   const int32_t *kv_len;
   void *out;
@@ -180,6 +181,7 @@ struct RopeArgs {
   float2 *table;         // [M][hd/2] cos,sin scratch
   float2 *table2 = nullptr;  // optional second table of the same launch: n_q2 rows per sequence at kv_len[b] + r
   int n_q2 = 0;
+  const int32_t *slots = nullptr;  // optional [B]: sequence b appends to cache slot slots[b]
   int32_t *order;        // optional [B]: filled with the sequences in descending kv_len order ...
   int pair_from;         // ... but from this place on (0: nowhere) in ascending order
   // optional: a sticky word that collects SF_DEVERR_* bits when a device-side length contradicts what the

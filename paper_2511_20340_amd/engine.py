@@ -438,19 +438,67 @@ class Engine:
             return _prefill_blocks(self, prompts, q, self.max_k)
         helper = Engine(self.cfg, self.B, self.cap, q - 1, device=self.dev, share_caches=self)
         helper.bind_shared(self, with_draft=self._D is not None)
-        first = _prefill_blocks(helper, prompts, q, max(self.max_k, 1))
+        # row j of the helper is prompt order[j]; its K/V stay in the prompt's own cache slot
+        lens = [len(p) for p in prompts]
+        if len(lens) == self.B and min(lens) > 0:
+            order = sorted(range(self.B), key=lambda b: -((lens[b] + q - 1) // q))
+            slots = _prefill_packed(helper, [prompts[b] for b in order], order, q, max(self.max_k, 1))
+        else:
+            slots = torch.arange(self.B, device=self.dev)
+            _prefill_blocks(helper, prompts, q, max(self.max_k, 1))
         # hand-over: committed lengths, pending tokens, and every sequence's newest committed row of hooks
-        self.kv_len.copy_(helper.kv_len)
-        self.pending.copy_(helper.pending)
+        self.kv_len[slots] = helper.kv_len
+        self.pending[slots] = helper.pending
         last = (helper.n_new.to(torch.int64) - 1).clamp_(min=0)
         rows = helper.hooks[torch.arange(self.B, device=self.dev), last]          # [B, 4, d]
         self.hooks.zero_()
-        self.hooks[:, 0] = rows
-        self.n_new.copy_((helper.n_new > 0).to(torch.int32))
+        self.hooks[slots, 0] = rows
+        self.n_new[slots] = (helper.n_new > 0).to(torch.int32)
         self.len_upper = helper.len_upper
         torch.cuda.current_stream().synchronize()
         helper.close()
-        return first
+        return self.pending.clone()
+
+
+def _prefill_packed(eng, prompts, order, q, k_draft):
+    """Chunked prefill in blocks of q tokens, right-aligned as in _prefill_blocks, of prompts in descending number of blocks:
+    each block runs over the prompts that have started (the first n rows), in one sf_prefill_step, and nothing is read back
+    in between.  order[j]: the cache slot of row j.  Returns the slots on the device."""
+    lens = np.array([len(p) for p in prompts], np.int64)
+    nblk = (lens + q - 1) // q
+    total = int(nblk[0])
+    # row j's tokens end with the last block: a short first block, padded behind (the pad rows are not committed)
+    toks = np.zeros((total, eng.B, q), np.int32)
+    size = np.zeros((total, eng.B), np.int32)
+    for j, p in enumerate(prompts):
+        first = int(lens[j] - (nblk[j] - 1) * q)
+        start = total - int(nblk[j])
+        toks[start, j, :first] = p[:first]
+        size[start, j] = first
+        toks[start + 1:, j] = np.asarray(p[first:], np.int32).reshape(-1, q)
+        size[start + 1:, j] = q
+    active = (nblk[None, :] >= total - np.arange(total)[:, None]).sum(1)
+    upper = size.cumsum(0).max(1)
+    d_first = torch.from_numpy(np.ascontiguousarray(toks[:, :, 0])).to(eng.dev)
+    d_rest = torch.from_numpy(np.ascontiguousarray(toks[:, :, 1:])).to(eng.dev)
+    d_size = torch.from_numpy(size).to(eng.dev)
+    slots = torch.tensor(order, dtype=torch.int32, device=eng.dev)
+    i32 = dict(dtype=torch.int32, device=eng.dev)
+    ids, out = torch.zeros(eng.B, q, **i32), torch.empty(eng.B, q, **i32)
+    acc, draft = torch.empty(eng.B, **i32), torch.empty(eng.B, k_draft, **i32)
+    eng.kv_len.zero_()
+    eng.n_new.zero_()
+    before = 0
+    for step in range(total):
+        n = int(active[step])
+        eng.pending.copy_(d_first[step])
+        sfb.check(eng.lib.sf_prefill_step(eng.ctx, C.byref(eng.st), q - 1, _ptr(d_rest[step]), _ptr(d_size[step]), n,
+                                          _ptr(slots), before, int(upper[step]), k_draft if eng._D is not None else 0,
+                                          int(step == total - 1), _ptr(ids), _ptr(acc), _ptr(out), _ptr(draft), _stream()),
+                  "sf_prefill_step", eng.ctx)
+        before = int(upper[step])
+    eng.len_upper = before
+    return slots.to(torch.int64)
 
 
 def _prefill_blocks(eng, prompts, q, k_draft):
@@ -465,7 +513,6 @@ def _prefill_blocks(eng, prompts, q, k_draft):
     for step in range(total):
         toks = np.zeros((eng.B, q), np.int32)
         force = np.zeros(eng.B, np.int32)
-        nxt = np.zeros(eng.B, np.int32)
         for b, p in enumerate(prompts):
             if step < total - nblk[b]:
                 continue                      # this sequence starts later
@@ -474,18 +521,12 @@ def _prefill_blocks(eng, prompts, q, k_draft):
             toks[b, :len(seg)] = seg
             force[b] = len(seg)
             done[b] += len(seg)
-            nxt[b] = p[done[b]] if done[b] < lens[b] else -1
         eng.pending.copy_(torch.from_numpy(toks[:, 0].copy()))
         draft = torch.from_numpy(toks[:, 1:].copy()).to(eng.dev)
         fl = torch.from_numpy(force).to(eng.dev)
         _, ids = eng.sf_verify_step(k, draft, logits=False)
         eng.sf_accept_commit(k, draft, ids, force_len=fl)
         eng.len_upper = int(done.max())
-        if step < total - 1:
-            # pending of a finished block is the next prompt token, not the target's choice
-            pend = eng.pending.cpu().numpy()
-            pend[nxt >= 0] = nxt[nxt >= 0]
-            eng.pending.copy_(torch.from_numpy(pend))
         if k_draft > 0 and eng._D is not None:
             eng.sf_draft_step(k_draft)
     return eng.pending.clone()
