@@ -2,6 +2,7 @@
 // schedulers (draft / verify / accept) that enqueue the HIP kernels on the caller's stream.
 #include <math.h>
 #include <string.h>
+#include <algorithm>
 #include <new>
 #include <vector>
 #include "sf_internal.h"
@@ -248,13 +249,14 @@ void norm_swiglu_in(Run &r, const sf_model_cfg &m, const void *x, const void *xb
 void attention(Run &r, const sf_model_cfg &m, const void *q, const void *kc, const void *vc, const int32_t *kv_len,
                void *out, float *part_o, float *part_ml, int B, int n_q, int cap, int mode, int len_upper,
                const void *qkv = nullptr, const float2 *table = nullptr, const int32_t *order = nullptr,
-               const int32_t *slots = nullptr) {
+               const int32_t *slots = nullptr, int plan_B = 0) {
   if (r.st != SF_OK) return;
   AttnArgs a{};
   a.q = q; a.qkv = qkv; a.table = table; a.order = order; a.slots = slots; a.kc = kc; a.vc = vc; a.kv_len = kv_len; a.out = out; a.part_o = part_o; a.part_ml = part_ml;
   a.B = B; a.n_q = n_q; a.Hq = m.n_q_heads; a.Hkv = m.n_kv_heads; a.hd = m.head_dim; a.cap = cap; a.mode = mode;
   const int n_rt = (m.n_q_heads / m.n_kv_heads * n_q + 31) / 32;
-  a.chunk_tiles = r.c->tune_chunk > 0 ? r.c->tune_chunk : attn_chunk_tiles(B * m.n_kv_heads * n_rt, len_upper + n_q);
+  // a part of the batch keeps the whole batch's chunks (plan_B)
+  a.chunk_tiles = r.c->tune_chunk > 0 ? r.c->tune_chunk : attn_chunk_tiles(std::max(plan_B, B) * m.n_kv_heads * n_rt, len_upper + n_q);
   const int n_tiles = (len_upper + n_q + TK - 1) / TK;
   a.n_chunks = (n_tiles + a.chunk_tiles - 1) / a.chunk_tiles;
   LAUNCH(K_ATTN, m.dtype == SF_BF16 ? launch_attention_bf16(a, r.s) : launch_attention_f32(a, r.s));
@@ -340,7 +342,7 @@ sf_status verify_pass(sf_ctx *c, const sf_state *st, int32_t k, const int32_t *d
     // bf16: the attention kernel rotates Q and K and appends the block's K, V rows itself
     if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
     attention(r, m, qr, kc, vc, st->kv_len, ao, (float *)(ws + A.part_o), (float *)(ws + A.part_ml), B, q, cap,
-              SF_MASK_CAUSAL, len_upper, bf ? qkv : nullptr, ra.table, ra.order, sub.slots);
+              SF_MASK_CAUSAL, len_upper, bf ? qkv : nullptr, ra.table, ra.order, sub.slots, st->B);
     // h += attention . W_O, and h += W_down . act: float sums; bf16 mode also refreshes the bf16 copy
     GemmExtra ex;
     ex.res_f32 = 1; ex.y2 = hb;
@@ -429,7 +431,7 @@ sf_status draft_pass(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int
     rq.kv_only = 0; rq.pos_mode = 0; rq.theta = m.rope_theta;
     LAUNCH(K_ROPE, launch_rope_table(rq, r.s));
     LAUNCH(K_ROPE, launch_rope_kv(rq, m.dtype, r.s));
-    attention(r, m, qr1, st->dk, st->dv, len_m1, ao1, part_o, part_ml, B, 1, cap, SF_MASK_CAUSAL, len_upper);
+    attention(r, m, qr1, st->dk, st->dv, len_m1, ao1, part_o, part_ml, B, 1, cap, SF_MASK_CAUSAL, len_upper, nullptr, nullptr, nullptr, nullptr, st->B);
     gemm(r, m.dtype, ao1, w.wo, nullptr, x_last, id_last, B, d, nq, 1);  // float row of the stream
     norm(r, m, id_last, w.pos_norm, xl, B, 1, 3, 1, 1, st->n_new, 1);
     // the slots attend to each other only: an empty prefix in a one-tile cache of their own
@@ -448,7 +450,7 @@ sf_status draft_pass(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int
   // bf16: the attention kernel rotates the slots' Q and K and appends their K, V rows itself
   if (!bf) LAUNCH(K_ROPE, launch_rope_kv(ra, m.dtype, r.s));
   attention(r, m, qr, kc_s, vc_s, len_s, ao, part_o, part_ml, B, k, cap_s, mask, len_upper_s, bf ? qkv : nullptr,
-            ra.table, nullptr, two_stage ? nullptr : sub.slots);
+            ra.table, nullptr, two_stage ? nullptr : sub.slots, st->B);
   ex.res_f32 = 1;
   gemm(r, m.dtype, ao, wo_s, nullptr, s0, s0, Ms, d, nq, 1, 0, 0, 0.f, &ex);
   norm_swiglu_in(r, m, s0, s0b, w.ffn_norm, w.w_gate_up, act, Ms, F, d);
