@@ -195,7 +195,14 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
 #pragma unroll
   for (int a = 0; a < AHEAD; ++a) read_a(0, a);
   __builtin_amdgcn_s_waitcnt(0xc07f);
-  asm volatile("s_nop 7" ::);  // the zeroed accumulators are settled
+  // the accumulators are zeroed before this point, and settled behind it
+  static_for<TM * TN>([&](auto i_c) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_c)::value;
+    f32x4 &c = acc[i / TN][i % TN];
+    if constexpr (i < IN_ACC) asm volatile("" : "+a"(c));
+    else asm volatile("" : "+v"(c));
+  });
+  asm volatile("s_nop 7" ::);
   __builtin_amdgcn_sched_barrier(0);
   for (int i = kt0; i < kt1; ++i) {
     k_step(std::integral_constant<int, 0>{});
