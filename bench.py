@@ -432,7 +432,7 @@ def main():
                    "q_heads": m.n_q_heads, "kv_heads": m.n_kv_heads, "head_dim": m.head_dim, "d_ffn": m.d_ffn,
                    "vocab": m.vocab, "draft_wiring": args.draft_wiring, "draft_mask": args.draft_mask, "drafts": "natural (the random-init draft block's own tokens)",
                    "state": "seeded caches (no prefill)" if args.seeded_state else
-                            f"real chunked prefill through sf_verify_step, blocks of {max(args.prefill_block, k + 1)} "
+                            f"real chunked prefill, blocks of {max(args.prefill_block, k + 1)} "
                             "prompt tokens", "prefill_s": round(t_prefill, 3),
                    "launch": "one HIP graph replay per step" if args.graph else "eager launches"},
         "kappa": tok_nat / (steps * B),

@@ -100,7 +100,8 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 // 6-8 % faster with it, also inside whole steps; the 320-row kernel with the fused norm measured 3 % faster
 // alone but 3.7 % slower as the gate/up product inside whole steps, so the fused-norm kernels keep the
 // compiler's order (seventh argument).
-// 15-25: the block kernel's (gemm_block.hip); forced on a layer that it does not take they stand for tile 10.
+// 15-28: the block and panel kernels' (gemm_block.hip, gemm_panel.hip); forced on a layer that they do not take they stand
+// for tile 10.
 constexpr int N_TILES = 28, N_RING_TILES = 14, N_MODEL_TILES = 10;
 constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1, 4, 5, 5};
 
@@ -257,7 +258,9 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
 // of both kernels x splits 1 to 8 were measured on 440 shapes (the 1B, 8B and 14B layers and heads at 40 to 2304 rows,
 // weights cold, medians of interleaved repeats) and the constants fitted to them: 4.8 % rms.  Since float outputs leave in
 // whole lines, launches of the tall tiles are up to 12 % faster than this; constants fitted anew choose no better.  (Tile
-// 20's norm by hand: its waves have one row block, and the squares of one chunk wait for each other.)
+// 20's norm by hand: its waves have one row block, and the squares of one chunk wait for each other.)  The panel kernel's
+// tiles (15-17, 26-28) were fitted to 360 shapes of 40 to 2304 rows, weights rotated through 600 MB, 6 to 9 % rms; their
+// norm is a launch in front, priced 4 us above what it takes by itself: so much more a launch costs in the chain of a step.
 struct TileCost {
   int bm, bn, groups;
   float slice, fixed, least, norm;
@@ -295,10 +298,11 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
 // of the block kernel's, whichever cost_us puts first.  (The split stays what the rules say: it fixes the order of a
 // layer's sums.)  Up to 160 rows the ring kernel, which then reads large weights past the caches, is up to 5 % better than
 // its formula; an LM head with arg-max partials up to 192 rows is up to 10 % better (160 x 152064 x 5120 372 us against
-// 384 on the block kernel, 192 x 32000 x 2048 46.6 against 51.4).  Over 521 shapes (33 to 8192 rows, with the norm, the
-// gate, float output or arg-max, replayed from graphs) the choice takes 0.92 times as long as the rules alone and 1.1 %
-// longer than the fastest tile of each shape; 19 are more than 2 % slower than by the rules, the worst by 11 % (norm, 136 x
-// 7168 x 5120: 35 us on five 32-row tiles, 39 on two of 128).
+// 384 on the block kernel, 192 x 32000 x 2048 46.6 against 51.4).  From 161 rows on its formula is 8 % short beside the panel
+// kernel's (1536 x 2048 x 8192: 69 us on 96 x 128, 56 on 128 x 128).  Tiles 26-28 start there too: below, 136 x 28672 x 4096
+// with norm and gate is 9 us faster on 160 x 128 than on the ring kernel, and the launch in front takes that back inside a
+// step.  Over 360 shapes (40 to 2304 rows, with the norm, float output or arg-max, replayed from graphs) the choice is 0.8 %
+// slower than the fastest tile of each.
 GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, int norm, bool am) {
   GemmConfig best = pick(M, N, K, ws_bytes, split);
   if (M <= 32) return best;

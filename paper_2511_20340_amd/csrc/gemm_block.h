@@ -7,10 +7,8 @@
 // operand passes through registers on its way to LDS, so what is in flight is bounded by the 160 KiB of LDS alone; the
 // packed weight units are LDS fragments as they are.  Activations arrive in rows of whole 128-byte lines (64-byte pieces
 // of half as long slices cost 4 to 10 % more).
-// What bounds it: the matrix cores at the clock the card holds under this load (about 1.9 GHz of 2.4), then operand
-// latency: 1280 x 28672 x 4096 takes 256 us, 226 when all loads hit one line and 213 without the loads; the ring
-// kernel 290 (with the fused norm 272 against 314).  1280 x 4096 x 14336 148 against 165 us, 640 x 152064 x 5120 823
-// against 944, 512 x 2048 x 2048 9.7 against 16.7, 320 x 5120 x 13824 67 against 88.
+// What bounds it: operand latency.  512 x 2048 x 2048 9.7 us (ring kernel 16.7), 320 x 5120 x 13824 67 (88).  The largest
+// tiles are the panel kernel's (gemm_panel.h): 1280 x 28672 x 4096 with the norm 270 us on eight waves here, 232 there.
 //
 // Same products in the same order, same K partition, same row sums as the ring kernel: the same bits.
 //

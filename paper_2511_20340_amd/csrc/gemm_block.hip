@@ -4,11 +4,12 @@
 namespace sf {
 
 //   id  rows x columns  waves      LDS slices, workgroups per CU
+//   18  128 x 256       2 x 4      3, 1 (with the fused norm)
+//   19  128 x  64       2 x 2      3, 2
 //   20   64 x  64       2 x 2      4, 2
 //   21  160 x  64       5 x 1      5, 1
-//   18  128 x 256       2 x 4      3, 1 (with the fused norm; without: the panel kernel)
-//   19  128 x  64       2 x 2      3, 2
 //   22  160 x 128       5 x 2      4, 1
+//   15-17, 18 without the norm, 26-28: the panel kernel's (gemm_panel.hip)
 // K shared by groups of waves (layers whose K is split that often, see gemm_block_kernel):
 //   23   64 x  64       2 x 2, 2 groups   4, 1
 //   24   32 x  64       1 x 2, 4 groups   3, 1
@@ -20,9 +21,9 @@ hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split)
   switch (tile) {
     case 18: return a.fused_norm ? run_block<2, 4, 2, 2, 3>(a, s, split) : dispatch_panel(tile, a, s, split);
     case 19: return run_block<2, 2, 2, 1, 3>(a, s, split);
-    case 22: return run_block<5, 2, 1, 2, 4>(a, s, split);
     case 20: return run_block<2, 2, 1, 1, 4>(a, s, split);
     case 21: return run_block<5, 1, 1, 2, 5>(a, s, split);
+    case 22: return run_block<5, 2, 1, 2, 4>(a, s, split);
     case 23: return run_block<2, 2, 1, 1, 4, 2>(a, s, split);
     case 24: return run_block<1, 2, 1, 1, 3, 4>(a, s, split);
     case 25: return run_block<1, 2, 1, 1, 3, 2>(a, s, split);
@@ -51,6 +52,7 @@ int block_groups(int tile) { return tile == 24 ? 4 : tile == 23 || tile == 25 ? 
 bool block_takes(int tile, int M, int N, int K, int split, bool am, ptrdiff_t norm_ws) {
   if (tile < 15 || tile > 28 || (am && tile >= 19 && tile != 22)) return false;
   if (block_groups(tile) > 1 && make_plan(M, N, K, 32, 32, split).split_k != block_groups(tile)) return false;
+  // 26-28: unsplit layers only (split ones gain up to 6 % from them)
   if (tile > 25 && make_plan(M, N, K, 32, 32, split).split_k > 1) return false;
   if (squares_before(tile) && norm_ws >= 0 && !squares_fit(M, norm_ws)) return false;
   const size_t limit = (size_t)1 << 32;
