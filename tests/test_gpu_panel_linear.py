@@ -92,11 +92,11 @@ def test_a_norm_without_workspace_runs_on_tiles_that_need_none():
 
 
 @pytest.mark.parametrize("tile", ROWS)
-@pytest.mark.parametrize("split", [1, 2])
-def test_residual_stream_in_a_step(tile, split):
+@pytest.mark.parametrize("split,vocab", [(1, 1032), (2, 1032), (1, 1001)])
+def test_residual_stream_in_a_step(tile, split, vocab):
     """A whole step forced onto the tile: norm, gate, float residual, bf16 copy, hooked copies, logits and arg-max; more rows
-    than the tile has, and not a multiple."""
-    shape, B, k, cap = synth.ModelShape("t", 2, 512, 4, 2, 128, 544, 1032, "bf16"), 67, 4, 64
+    than the tile has, and not a multiple; a vocabulary whose rows of logits are off 16 bytes."""
+    shape, B, k, cap = synth.ModelShape("t", 2, 512, 4, 2, 128, 544, vocab, "bf16"), 67, 4, 64
     weights = synth.target_weights(shape, 5, 0.05)
     toks = synth.rng(63, tile).integers(0, shape.vocab, (B, k + 1)).astype(np.int32)
     eng = Engine(shape.cfg(), B, cap, k)
@@ -111,5 +111,34 @@ def test_residual_stream_in_a_step(tile, split):
     try:
         for got, ref in zip(step(tile), step(RING_TILE)):
             assert torch.equal(got, ref)
+    finally:
+        eng.sf_tune_linear(0, 0)
+
+
+@pytest.mark.parametrize("tile", [15, 16, 17, 18])
+@pytest.mark.parametrize("N", [1032, 264])
+def test_argmax(tile, N):
+    """LM heads with ties everywhere, a NaN row, and a row of -inf: choices and stored logits."""
+    M, K = 90, 192
+    g = synth.rng(64, tile + N)
+    x = g.integers(-2, 3, (M, K)).astype(np.float32)     # integers: exact sums, ties everywhere
+    w = g.integers(-1, 2, (N, K)).astype(np.float32)
+    x[5, 0], x[7] = np.nan, 0.0
+    x[9], w[:, 3] = 0.0, 1.0
+    x[9, 3] = -np.inf                                    # every logit of the row is -inf
+    eng = engine()
+    xd, wd = dev(x, "bf16"), dev(w, "bf16")
+    try:
+        out = []
+        for t in (RING_TILE, tile):
+            eng.sf_tune_linear(t, 1)
+            ids, logits = eng.sf_op_linear_argmax(xd, wd, want_logits=True)
+            out.append((ids.clone(), logits.clone(), eng.sf_op_linear_argmax(xd, wd).clone()))
+        (i0, l0, j0), (i1, l1, j1) = out
+        assert torch.equal(i0, i1) and torch.equal(i1, j1) and torch.equal(j0, i0)
+        assert torch.equal(l0.nan_to_num(), l1.nan_to_num()) and torch.equal(torch.isnan(l0), torch.isnan(l1))
+        rows = [r for r in range(M) if r not in (5, 9)]
+        np.testing.assert_array_equal(i1.cpu().numpy()[rows], sfo.linear(x[rows], w).argmax(-1))
+        assert int(i1[9]) == 0 and int(i1[5]) == 0
     finally:
         eng.sf_tune_linear(0, 0)
