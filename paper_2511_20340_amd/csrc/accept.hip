@@ -105,6 +105,9 @@ __global__ __launch_bounds__(256) void accept_kernel(const int32_t *__restrict__
   const int q = k + 1;
   const int per = (B + 255) / 256;
   const int b0 = threadIdx.x * per, b1 = min(B, b0 + per);
+  // blocks of many tokens (prefill): all threads write them (one thread per sequence took 12 us for 8 blocks of 64); a decoding
+  // block's few go out from the thread that has them, without waiting for the accept lengths
+  const bool shared = q > 16;
   int32_t local = 0;
   for (int b = b0; b < b1; ++b) {
     const int32_t *p = target_ids + (size_t)b * q;
@@ -115,6 +118,8 @@ __global__ __launch_bounds__(256) void accept_kernel(const int32_t *__restrict__
       a = 1;
       for (int n = 0; n < k && draft[b * k + n] == p[n]; ++n) a = n + 2;
     }
+    if (!shared)
+      for (int i = 0; i < q; ++i) out_tokens[b * q + i] = i < a ? p[i] : -1;
     accept_len[b] = a;
     if (a > 0) pending[b] = p[a - 1];
     kv_len[b] += a;
@@ -123,8 +128,8 @@ __global__ __launch_bounds__(256) void accept_kernel(const int32_t *__restrict__
   }
   scan[threadIdx.x] = local;
   __syncthreads();
-  // all threads write the tokens (one thread per sequence took 12 us for 8 blocks of 64)
-  for (int x = threadIdx.x; x < B * q; x += 256) out_tokens[x] = x % q < accept_len[x / q] ? target_ids[x] : -1;
+  if (shared)
+    for (int x = threadIdx.x; x < B * q; x += 256) out_tokens[x] = x % q < accept_len[x / q] ? target_ids[x] : -1;
   for (int o = 1; o < 256; o <<= 1) {  // inclusive Hillis-Steele scan
     const int32_t v = threadIdx.x >= o ? scan[threadIdx.x - o] : 0;
     __syncthreads();

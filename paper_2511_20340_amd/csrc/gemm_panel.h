@@ -34,10 +34,10 @@ struct PanelShape {
   static constexpr int NW = WM * WN, BM = WM * TM * 16, BN = WN * TN * 16;
   static constexpr int A_UNITS = BM / 8, UNITS = (BM + BN) / 8, PER = UNITS / NW;  // 1 KiB each; PER: loads per wave
   static constexpr int A_SLICE = A_UNITS * UNIT, SLICE = UNITS * UNIT;
-  // after the loop the same LDS holds the row factors, the sums of squares by chunk (or the arg-max partials of the WN
-  // columns of waves), and per wave pieces of 16 rows
+  // after the loop the same LDS holds the row factors, the arg-max partials of the WN columns of waves, and per wave pieces
+  // of 16 rows
   static constexpr int ROW = TN * 16 + 4, PIECE = 16 * ROW * 4, PIECES = 2;
-  static constexpr size_t rows = (size_t)BM * 9 * 4;
+  static constexpr size_t rows = (size_t)BM * (1 + 2 * WN) * 4;
   static constexpr size_t after = rows + (size_t)NW * PIECES * PIECE, loop = STAGES * (size_t)SLICE;
   static constexpr size_t lds = loop > after ? loop : after;
   static constexpr bool PAIR = lds <= 80 * 1024;  // two workgroups on a compute unit
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 
-  float *const sS = reinterpret_cast<float *>(smem), *const chunk = sS + BM;
+  float *const sS = reinterpret_cast<float *>(smem);
   if (split_k == 1) {  // one factor per row: of the fused norm, or 1
     for (int r = tid; r < BM; r += 64 * NW) sS[r] = ssq ? 1.0f / sqrtf(ssq[min(m0 + r, M - 1)] / (float)K + eps) : 1.f;
     __syncthreads();
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   if (e.am_val) {
     // Arg-max partials of this workgroup's columns: a lane walks its columns in ascending order (a NaN is never greater),
     // the four lanes of a row and the WN waves compare value, then column.  Columns past N never take part.
-    float *s_val = chunk;                                        // [WN][BM]
+    float *s_val = sS + BM;                                      // [WN][BM]
     int32_t *s_idx = reinterpret_cast<int32_t *>(s_val + WN * BM);  // [WN][BM]
     auto better = [](float v, int32_t i, float bv, int32_t bi) __attribute__((always_inline)) {
       return i != INT32_MAX && (bi == INT32_MAX || v > bv || (v == bv && i < bi));
