@@ -235,8 +235,9 @@ sf_status sf_pack_weight(const sf_ctx *ctx, const void *w, void *packed, int32_t
 
 /* y[M][N] = x[M][K] . w[N][K]^T (+ bias[N]) (+ residual[M][N]); x, bias, residual: dev elem; w: packed;
  * fp32 accumulation; y: dev elem, or float when out_f32 != 0.  K % 8 == 0, N % 8 == 0.
- * residual may alias y.  workspace (dev, 256-byte aligned, may be NULL): lets skinny shapes split the
- * K dimension over several workgroups (their partial sums; nothing is kept in it between calls).
+ * residual may alias y.  workspace (dev, 256-byte aligned, may be NULL): lets layers with few workgroups split
+ * the K dimension over more of them; it then holds their partial sums, and is written by no other launch (nothing
+ * is kept in it between calls).
  * sf_linear_workspace_bytes gives the size to pass. */
 size_t sf_linear_workspace_bytes(const sf_ctx *ctx, int32_t M);
 sf_status sf_op_linear(const sf_ctx *ctx, const void *x, const void *w, const void *bias,
@@ -245,7 +246,7 @@ sf_status sf_op_linear(const sf_ctx *ctx, const void *x, const void *w, const vo
 /* Fused y = RMSNorm(x; gain, eps of the target configuration) . w^T, SF_BF16 only (SF_EUNSUPPORTED
  * otherwise): what the decoder layers run in place of a norm kernel followed by a linear kernel.  w must
  * have been packed with col_gain = gain; the kernel streams the raw x, accumulates every row's sum of
- * squares on the way, and scales its fp32 accumulators by the row factor 1/sqrt(mean(x^2)+eps), which
+ * squares on the way (the steps' widest layers and split ones by a launch in front, in the same order), and scales its fp32 accumulators by the row factor 1/sqrt(mean(x^2)+eps), which
  * commutes with the K sum; the normalised activations never reach HBM.  x: dev bf16 [M][K]; other
  * arguments as sf_op_linear. */
 sf_status sf_op_rmsnorm_linear(const sf_ctx *ctx, const void *x, const void *w, void *y, int32_t M, int32_t N,

@@ -31,7 +31,8 @@ enum {
   SF_LINEAR_GLU = 1,       /* the SwiGLU gate (N = 2F)                      */
   SF_LINEAR_NORM = 2,      /* the fused RMSNorm                             */
   SF_LINEAR_ARGMAX = 4,    /* arg-max partials (LM head)                    */
-  SF_LINEAR_UNALIGNED = 8  /* x does not start on a 16-byte boundary        */
+  SF_LINEAR_UNALIGNED = 8, /* x does not start on a 16-byte boundary        */
+  SF_LINEAR_OP = 16        /* a public operation, whose workspace may be shared between streams; without it a step's layer */
 };
 sf_status sf_linear_choice(int32_t M, int32_t plan_M, int32_t N, int32_t K, size_t workspace_bytes, int32_t flags,
                            int32_t *kernel, int32_t *tile, int32_t *split_k);

@@ -10,7 +10,7 @@ SF_OK, SF_EINVAL, SF_ECAPACITY, SF_ESTATE, SF_EHIP, SF_EUNSUPPORTED = range(6)
 SF_BF16, SF_F32 = 0, 1
 SF_MASK_CAUSAL, SF_MASK_BIDIR = 0, 1
 SF_KERNEL_RING, SF_KERNEL_BLOCK, SF_KERNEL_STREAM = range(3)
-SF_LINEAR_GLU, SF_LINEAR_NORM, SF_LINEAR_ARGMAX, SF_LINEAR_UNALIGNED = 1, 2, 4, 8
+SF_LINEAR_GLU, SF_LINEAR_NORM, SF_LINEAR_ARGMAX, SF_LINEAR_UNALIGNED, SF_LINEAR_OP = 1, 2, 4, 8, 16
 SF_DRAFT_TWO_STAGE = 16   # OR-ed into sf_draft_step's mask
 KERNEL_CLASSES = ["linear", "attention", "attention_combine", "rmsnorm", "rope_kv_append", "silu_mul",
                   "embed_hook", "argmax", "accept"]

@@ -131,6 +131,7 @@ struct Run {
   sf_status st = SF_OK;
   void *gemm_ws = nullptr;
   size_t gemm_ws_bytes = 0;
+  int own_ws = 0;     // gemm_ws belongs to a state, whose calls are on one stream; a public operation's may be shared
   int plan_rows = 0;  // rows the linear layers' K partition is chosen for (0: the launch's own M)
   // a stale error left by an earlier, unrelated HIP call of the process must not be blamed on us
   Run(const sf_ctx *ctx, hipStream_t stream) : c(ctx), s(stream) { (void)hipGetLastError(); }
@@ -177,7 +178,7 @@ void gemm(Run &r, int dtype, const void *x, const void *w, const void *bias, con
   GemmArgs g{x, w, bias, res, y, M, N, K, out_f32, glu, r.gemm_ws, r.gemm_ws_bytes};
   g.plan_M = r.plan_rows;
   g.tile = r.c->tune_tile; g.split = r.c->tune_split;
-  g.fused_norm = fused_norm; g.norm_eps = norm_eps;
+  g.fused_norm = fused_norm; g.norm_eps = norm_eps; g.own_ws = r.own_ws;
   if (ex) {
     g.hooks = ex->hooks; g.hook_mask = ex->hook_mask; g.hook_q = ex->hook_q; g.hook_qmax = ex->hook_qmax;
     if (dtype != SF_BF16) g.gain_f32 = ex->gain_f32;
@@ -307,7 +308,7 @@ sf_status verify_pass(sf_ctx *c, const sf_state *st, int32_t k, const int32_t *d
   const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
   const bool bf = m.dtype == SF_BF16;
   Run r{c, (hipStream_t)stream};
-  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes;
+  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes; r.own_ws = 1;
   // the target's logits for a position must not depend on how many draft positions are verified
   // with it: every k of this state uses the K partition chosen for the largest block
   r.plan_rows = st->B * qm;
@@ -387,7 +388,7 @@ sf_status draft_pass(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int
   const int nq = m.n_q_heads * m.head_dim, nkv = m.n_kv_heads * m.head_dim;
   const size_t es = esize(m.dtype);
   Run r{c, (hipStream_t)stream};
-  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes;
+  r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes; r.own_ws = 1;
   r.plan_rows = B < st->B ? st->B * qm : 0;  // a part of the batch keeps the whole batch's order of sums
   // context rows: Grouped RMSNorm -> W_D -> K,V of the draft attention layer at the rows' positions
   norm(r, m, st->hooks, w.group_norm, f4, Mh * 4, 4, 1, qm, qm, nullptr);
@@ -710,7 +711,7 @@ sf_status sf_linear_choice(int32_t M, int32_t plan_M, int32_t N, int32_t K, size
   a.x = (const void *)(uintptr_t)(flags & SF_LINEAR_UNALIGNED ? 2 : 0);
   a.M = M; a.N = N; a.K = K; a.plan_M = plan_M;
   a.ws = workspace_bytes ? &set : nullptr; a.ws_bytes = workspace_bytes;
-  a.glu = (flags & SF_LINEAR_GLU) != 0; a.fused_norm = (flags & SF_LINEAR_NORM) != 0;
+  a.glu = (flags & SF_LINEAR_GLU) != 0; a.fused_norm = (flags & SF_LINEAR_NORM) != 0; a.own_ws = !(flags & SF_LINEAR_OP);
   a.am_val = flags & SF_LINEAR_ARGMAX ? &set : nullptr;
   a.tile = *tile; a.split = *split_k;
   const GemmChoice c = gemm_choose(a);

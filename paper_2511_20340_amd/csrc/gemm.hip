@@ -100,10 +100,10 @@ __global__ void pack_weight_kernel(const bf16_t *__restrict__ W, uint4 *__restri
 // 6-8 % faster with it, also inside whole steps; the 320-row kernel with the fused norm measured 3 % faster
 // alone but 3.7 % slower as the gate/up product inside whole steps, so the fused-norm kernels keep the
 // compiler's order (seventh argument).
-// 15-28: the block and panel kernels' (gemm_block.hip, gemm_panel.hip); forced on a layer that they do not take they stand
+// 15-31: the block and panel kernels' (gemm_block.hip, gemm_panel.hip); forced on a layer that they do not take they stand
 // for tile 10.
-constexpr int N_TILES = 28, N_RING_TILES = 14, N_MODEL_TILES = 10;
-constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1, 4, 5, 5};
+constexpr int N_TILES = 31, N_RING_TILES = 14, N_MODEL_TILES = 10;
+constexpr int TILE_TM[N_TILES + 1] = {0, 1, 2, 3, 4, 5, 2, 3, 4, 5, 5, 10, 8, 7, 6, 10, 8, 6, 4, 4, 2, 5, 5, 2, 1, 1, 4, 5, 5, 10, 8, 6};
 
 // the block kernel's direct loads move 16 bytes at a time; the ring kernel takes rows at any address
 bool rows_aligned(const GemmArgs &a) { return (uintptr_t)a.x % 16 == 0; }
@@ -281,6 +281,7 @@ constexpr TileCost TILE_COST[N_TILES + 1] = {
     {64, 64, 2, 0.469f, 0.2f, 0.63f, 0.083f}, {32, 64, 4, 0.737f, 0.0f, 0.52f, 0.089f},
     {32, 64, 2, 0.348f, 0.1f, 0.95f, 0.038f}, {128, 128, 1, 0.526f, 1.1f, 0.69f, 8.5f},
     {160, 128, 1, 0.486f, 1.9f, 1.63f, 7.8f}, {160, 128, 1, 0.509f, 4.3f, 0.61f, 7.0f},
+    {320, 256, 1, 1.691f, 2.6f, 0.86f, 0.230f}, {256, 256, 1, 1.317f, 3.2f, 0.84f, 0.232f}, {192, 256, 1, 1.027f, 3.7f, 0.84f, 0.143f},
 };
 double cost_us(int M, int N, int K, GemmConfig c, int norm) {
   const TileCost &t = TILE_COST[c.tile];
@@ -302,13 +303,16 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
 // kernel's (1536 x 2048 x 8192: 69 us on 96 x 128, 56 on 128 x 128).  Tiles 26-28 start there too: below, 136 x 28672 x 4096
 // with norm and gate is 9 us faster on 160 x 128 than on the ring kernel, and the launch in front takes that back inside a
 // step.  Over 360 shapes (40 to 2304 rows, with the norm, float output or arg-max, replayed from graphs) the choice is 0.8 %
-// slower than the fastest tile of each.
-GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, int norm, bool am) {
+// slower than the fastest tile of each.  A norm whose row sums have nowhere to go (norm_ws, as for block_takes) leaves the
+// panel kernel out of an unsplit layer: there 29-31 stand in for 15-17, and the ring kernel's formula holds.
+GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, ptrdiff_t norm_ws, bool am) {
+  const int norm = norm_ws >= 0;
+  const bool no_panel = norm && make_plan(M, N, K, 32, 32, split).split_k == 1 && !squares_fit(M, norm_ws);
   GemmConfig best = pick(M, N, K, ws_bytes, split);
   if (M <= 32) return best;
-  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : 1.08);
+  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : no_panel ? 1.0 : 1.08);
   for (int tile = N_RING_TILES + 1; tile <= N_TILES; ++tile) {
-    if ((tile > 25 && M <= 160) || !block_takes(tile, M, N, K, split, am, norm ? (ptrdiff_t)ws_bytes : -1)) continue;
+    if ((tile > 28 ? !no_panel : tile > 25 && M <= 160) || !block_takes(tile, M, N, K, split, am, norm_ws)) continue;
     const Plan p = make_plan(M, N, K, TILE_COST[tile].bm, TILE_COST[tile].bn, split);
     if (block_groups(tile) == 1 && !plan_fits(p, TILE_COST[tile].bm, (const void *)1, ws_bytes)) continue;
     const double us = cost_us(M, N, K, {tile, split}, norm);
@@ -370,13 +374,13 @@ GemmChoice gemm_choose(const GemmArgs &a) {
     const int split = am ? 1 : gemm_heuristic(a.M, std::max(a.plan_M, a.M), a.N, a.K, ws_bytes).split;
     const int tiles = am ? 0 : gemm_stream_tiles(a.M, a.N, a.K, split, a.glu);
     if (tiles) return {GEMM_STREAM, tiles, split};
-    c = rows_aligned(a) ? pick_any(a.M, a.N, a.K, ws_bytes, split, a.fused_norm, am) : pick(a.M, a.N, a.K, ws_bytes, split);
+    c = rows_aligned(a) ? pick_any(a.M, a.N, a.K, ws_bytes, split, gemm_norm_bytes(a), am) : pick(a.M, a.N, a.K, ws_bytes, split);
   } else if (c.tile <= 0 || c.split <= 0) {
     const GemmConfig h = gemm_heuristic(a.M, a.plan_M > 0 ? a.plan_M : a.M, a.N, a.K, ws_bytes);
     if (c.split <= 0) c.split = h.split;
     if (c.tile <= 0) c.tile = c.split == h.split ? h.tile : pick(a.M, a.N, a.K, ws_bytes, c.split).tile;
   }
-  if (c.tile > N_RING_TILES && (!block_takes(c.tile, a.M, a.N, a.K, c.split, am, a.fused_norm ? (ptrdiff_t)ws_bytes : -1) || !rows_aligned(a))) c.tile = 10;
+  if (c.tile > N_RING_TILES && (!block_takes(c.tile, a.M, a.N, a.K, c.split, am, gemm_norm_bytes(a)) || !rows_aligned(a))) c.tile = 10;
   return {c.tile > N_RING_TILES ? GEMM_BLOCK : GEMM_RING, c.tile, c.split};
 }
 

@@ -253,7 +253,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void gemm_block_kernel(const bf1
 #endif
 }
 
-template <int WM, int WN, int TM, int TN, int STAGES, int KG = 1>
+// NORM_ALONE: a tile that runs with the fused norm only; the other form is not built
+template <int WM, int WN, int TM, int TN, int STAGES, int KG = 1, bool NORM_ALONE = false>
 hipError_t ensure_block_lds() {
   using S = BlockShape<WM, WN, TM, TN, STAGES, KG>;
   constexpr int cap = (int)S::lds;
@@ -263,15 +264,17 @@ hipError_t ensure_block_lds() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (raised[dev]) return hipSuccess;
   auto raise = [](const void *f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, cap); };
-  hipError_t err = raise(reinterpret_cast<const void *>(&gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 0>));
+  hipError_t err = hipSuccess;
+  if constexpr (!NORM_ALONE) err = raise(reinterpret_cast<const void *>(&gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 0>));
   if (err == hipSuccess) err = raise(reinterpret_cast<const void *>(&gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 1>));
   if (err == hipSuccess) raised[dev] = true;
   return err;
 }
 
-template <int WM, int WN, int TM, int TN, int STAGES, int KG = 1>
+template <int WM, int WN, int TM, int TN, int STAGES, int KG = 1, bool NORM_ALONE = false>
 hipError_t run_block(const GemmArgs &a, hipStream_t s, int split) {
   using S = BlockShape<WM, WN, TM, TN, STAGES, KG>;
+  if (NORM_ALONE && !a.fused_norm) return hipErrorInvalidValue;
   const Plan p = make_plan(a.M, a.N, a.K, S::BM, S::BN, split);
   if (KG > 1 ? p.split_k != KG : !plan_fits(p, S::BM, a.ws, a.ws_bytes)) return hipErrorInvalidValue;
   const bool two = KG == 1 && p.split_k > 1;  // a second launch adds the partial tiles
@@ -281,14 +284,16 @@ hipError_t run_block(const GemmArgs &a, hipStream_t s, int split) {
   if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;
   if (a.am_val && a.am_parts_out) *a.am_parts_out = p.tiles_n;
   const Epilogue e = make_epilogue(a);
-  const hipError_t set = ensure_block_lds<WM, WN, TM, TN, STAGES, KG>();
+  const hipError_t set = ensure_block_lds<WM, WN, TM, TN, STAGES, KG, NORM_ALONE>();
   if (set != hipSuccess) return set;
   auto launch = [&](auto kernel) {
     kernel<<<groups * XCDS * p.tiles_m, 64 * S::NW * KG, S::lds, s>>>(
         (const bf16_t *)a.x, (const uint4 *)a.w, e, a.M, a.N, a.K, p.tiles_m, p.tiles_n, p.split_k, p.kt_per_split, partial,
         a.norm_eps, ssq_part);
   };
-  launch(a.fused_norm ? &gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 1> : &gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 0>);
+  if (a.fused_norm) launch(&gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 1>);
+  if constexpr (!NORM_ALONE)
+    if (!a.fused_norm) launch(&gemm_block_kernel<WM, WN, TM, TN, STAGES, KG, 0>);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess || !two) return err;
   return launch_split_finish(partial, a.fused_norm ? ssq_part : nullptr, e, p.split_k, a, s);

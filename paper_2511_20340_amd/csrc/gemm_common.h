@@ -157,7 +157,10 @@ hipError_t launch_gemm_stream(const GemmArgs &a, int tiles, int split, hipStream
 // adds the partial tiles of a split layer and applies the epilogue (gemm.hip)
 hipError_t launch_split_finish(const float *partial, const float *ssq_part, const Epilogue &e, int split,
                                const GemmArgs &a, hipStream_t s);
-// the fused norm's row sums of squares by a launch of their own: ssq[split][M] in the workspace (gemm_panel.hip)
+// the fused norm's row sums of squares by a launch of their own: ssq[split][M] in the workspace (gemm_panel.hip).
+// Unsplit, only in a workspace that is the launch's own: the caller of a public operation may share one between streams.
+// (A tile forced by the tuning call runs whatever it needs.)  -1: no norm
+inline ptrdiff_t gemm_norm_bytes(const GemmArgs &a) { return !a.fused_norm ? -1 : a.ws && (a.own_ws || a.tile > 0) ? (ptrdiff_t)a.ws_bytes : 0; }
 inline bool squares_fit(int M, size_t ws_bytes) { return (size_t)M * sizeof(float) <= GEMM_SSQ_BYTES && ws_bytes >= GEMM_SSQ_BYTES; }
 hipError_t launch_row_squares(const GemmArgs &a, int split_k, int kt_per_split, float *ssq, hipStream_t s);
 // the tile configurations (gemm_tiles_*.hip)
@@ -166,13 +169,13 @@ hipError_t dispatch_wide(int tile, const GemmArgs &a, hipStream_t s, int split);
 hipError_t dispatch_tall(int tile, const GemmArgs &a, hipStream_t s, int split);    // 11-14
 hipError_t prepare_tall();  // their function attributes, once per device
 // the block kernel's (gemm_block.hip)
-hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-28
+hipError_t dispatch_block(int tile, const GemmArgs &a, hipStream_t s, int split);  // 15-31
 hipError_t prepare_block();
 hipError_t dispatch_panel(int tile, const GemmArgs &a, hipStream_t s, int split);  // those of them on the panel kernel
 hipError_t dispatch_panel_narrow(int tile, const GemmArgs &a, hipStream_t s, int split);
 hipError_t prepare_panel();
 hipError_t prepare_panel_narrow();
-inline bool squares_before(int tile) { return (tile >= 15 && tile <= 17) || tile >= 26; }  // a norm's row sums: a launch of their own
+inline bool squares_before(int tile) { return (tile >= 15 && tile <= 17) || (tile >= 26 && tile <= 28); }  // a norm's row sums: a launch of their own
 int block_groups(int tile);  // groups of waves that share a split K inside a workgroup (1: none)
 bool block_takes(int tile, int M, int N, int K, int split, bool am, ptrdiff_t norm_ws);  // whether that tile can run such a layer
 

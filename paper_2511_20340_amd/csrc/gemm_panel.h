@@ -452,8 +452,8 @@ template <int WM, int WN, int TM, int TN, int STAGES>
 hipError_t run_panel(const GemmArgs &a, hipStream_t s, int split) {
   using S = PanelShape<WM, WN, TM, TN, STAGES>;
   const Plan p = make_plan(a.M, a.N, a.K, S::BM, S::BN, split);
-  if (!plan_fits(p, S::BM, a.ws, a.ws_bytes) || (a.fused_norm && !squares_fit(a.M, a.ws_bytes))) return hipErrorInvalidValue;
   const bool two = p.split_k > 1;  // a second launch adds the partial tiles
+  if (!plan_fits(p, S::BM, a.ws, a.ws_bytes) || (a.fused_norm && !two && !squares_fit(a.M, gemm_norm_bytes(a)))) return hipErrorInvalidValue;
   const int groups = (p.tiles_n * p.split_k + XCDS - 1) / XCDS;
   float *partial = two ? (float *)((char *)a.ws + GEMM_SSQ_BYTES) : nullptr;
   if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;

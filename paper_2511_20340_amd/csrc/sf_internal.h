@@ -112,6 +112,7 @@ struct GemmArgs {
   // folded into w's columns at pack time; the kernel supplies the row factor 1/sqrt(mean(x^2)+eps)
   int fused_norm = 0;
   float norm_eps = 0.f;
+  int own_ws = 0;  // nobody else uses the workspace meanwhile: an unsplit norm's row sums may go through it
   // fp32 only: the gain vector [K] of an RMSNorm applied to the rows of x on their way in (with norm_eps)
   const void *gain_f32 = nullptr;
   // bf16 only, the residual stream: residual (and with out_f32 the output) is float [M][N]; y2, when

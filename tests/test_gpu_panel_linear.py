@@ -1,6 +1,8 @@
 """The panel kernel (four waves, 16 x 16 tiles, written-out order): what its dispatch adds to the block kernel's tests, against
 the CPU oracle and the ring kernel's bits -- its own tiles 26 and 27, every tile at its edges, the row sums' own launch, rows
 and outputs off 16 bytes, and the float residual stream with its copies inside a step."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -142,3 +144,30 @@ def test_argmax(tile, N):
         assert int(i1[9]) == 0 and int(i1[5]) == 0
     finally:
         eng.sf_tune_linear(0, 0)
+
+
+@pytest.mark.parametrize("tile,M,N,K", [(29, 576, 28672, 512), (30, 1280, 20480, 512), (31, 320, 24576, 1024)])
+def test_a_public_norm_leaves_the_workspace_alone(tile, M, N, K):
+    """Unsplit, sf_op_rmsnorm_linear writes nothing into its workspace, which streams may share; with it, without it and on the
+    ring kernel: the same bits."""
+    assert linear_choice(M, N, K, sfb.SF_LINEAR_NORM | sfb.SF_LINEAR_OP) == (sfb.SF_KERNEL_BLOCK, tile, 1)
+    eng = engine()
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn(M, K, generator=gen, device="cuda").bfloat16()
+    w = (torch.randn(N, K, generator=gen, device="cuda") * 0.05).bfloat16()
+    gain = (1 + 0.5 * torch.randn(K, generator=gen, device="cuda")).bfloat16()
+    packed = (eng.sf_pack_weight(w, gain=gain), N)
+    eng.linear_workspace(M)
+    eng._lin_ws.fill_(0xA5)
+    got = eng.sf_op_rmsnorm_linear(x, gain, None, out_f32=True, packed=packed)
+    assert bool((eng._lin_ws == 0xA5).all())
+    bare = torch.empty_like(got)
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    sfb.check(eng.lib.sf_op_rmsnorm_linear(eng.ctx, ptr(x), ptr(packed[0]), ptr(bare), M, N, K, 1, None, 0,
+                                           C.c_void_p(torch.cuda.current_stream().cuda_stream)), "sf_op_rmsnorm_linear")
+    eng.sf_tune_linear(RING_TILE, 1)
+    want = eng.sf_op_rmsnorm_linear(x, gain, None, out_f32=True, packed=packed)
+    eng.sf_tune_linear(0, 0)
+    assert torch.equal(got, want) and torch.equal(bare, want)
+    ref = torch.nn.functional.rms_norm(x.float(), (K,), eps=1e-6) @ (w.float() * gain.float()).bfloat16().float().t()
+    assert float((got - ref).abs().max() / ref.abs().max()) < 1e-5

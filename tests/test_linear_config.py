@@ -197,3 +197,26 @@ def test_chosen_configurations_can_run(ws):
                     assert (1 << 20) + tiles * parts * rows[tile] * cols[tile] * 4 <= ws, (M, N, K, flags)
                 if kernel == sfb.SF_KERNEL_BLOCK:
                     assert K % 64 == 0 and tile >= 15
+
+
+OP_NORM = sfb.SF_LINEAR_NORM | sfb.SF_LINEAR_OP
+
+
+@pytest.mark.parametrize("ws", [0, WS])
+def test_a_public_norm_keeps_its_row_sums_out_of_the_workspace(ws):
+    """sf_op_rmsnorm_linear may share its workspace between streams as long as no K is split: its row sums of squares stay in
+    the kernel (any tile but 15-17, 26-28), which costs the wide layers no tile of their size."""
+    for N, K in SHAPES + [(512, 1000), (4104, 2056), (2048, 16384)]:
+        for M in (33, 136, 161, 200, 320, 500, 640, 896, 1024, 1280, 2048, 3000):
+            kernel, tile, split = linear_choice(M, N, K, OP_NORM, ws=ws)
+            parts = -(-((K + 63) // 64) // -(-((K + 63) // 64) // min(split, (K + 63) // 64)))
+            assert parts > 1 or kernel != sfb.SF_KERNEL_BLOCK or tile not in (15, 16, 17, 26, 27, 28), (M, N, K)
+    for (M, N, K), tile in {(640, 27648, 5120): 29, (1280, 28672, 4096): 29, (320, 28672, 4096): 31, (1024, 28672, 4096): 30,
+                            (896, 27648, 5120): 30, (768, 28672, 4096): 31}.items():
+        assert linear_choice(M, N, K, OP_NORM, ws=ws)[:2] == (sfb.SF_KERNEL_BLOCK, tile), (M, N, K)
+    # a step's sums have the state's own workspace: as many rows as it has room for
+    rows = (1 << 20) // 4
+    assert linear_choice(rows, 3072, 2048, sfb.SF_LINEAR_NORM)[1] in (15, 16, 17, 26, 27, 28)
+    assert linear_choice(rows + 1, 3072, 2048, sfb.SF_LINEAR_NORM)[1] == 29
+    # split: beside the parts of the sums, in the workspace anyway
+    assert linear_choice(1280, 4096, 14336, OP_NORM) == (sfb.SF_KERNEL_BLOCK, 17, 2)
