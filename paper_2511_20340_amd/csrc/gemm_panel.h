@@ -315,12 +315,18 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     });
     return;
   }
-  // how_c: PLAIN rows; FULL: bias, the float residual stream (requested as many pieces ahead as registers allow: y may
-  // be the residual, a lane's own elements), bf16 copy, hooked copies; ANY: any types and addresses, in a loop that is not unrolled
-  enum { PLAIN, FULL, ANY };
+  // how_c: PLAIN rows; FULL, FULL_BF: bias, a float or bf16 residual (requested as many pieces ahead as registers allow: y may
+  // be the residual, a lane's own elements), bf16 copy, hooked copies; ANY: any types and addresses, in a loop that is not
+  // unrolled and waits for every residual (1280 x 28672 x 4096, bf16 with bias and residual: 373 us that way, FULL_BF 250;
+  // without either 245)
+  enum { PLAIN, FULL, FULL_BF, ANY };
   auto outputs = [&](auto w_c, auto how_c, auto store) __attribute__((always_inline)) {
     constexpr int W = decltype(w_c)::value, PR = TN * 16 / W, T = (16 * PR + 63) / 64;  // units per row; units per lane
     constexpr int how = decltype(how_c)::value;
+    constexpr bool ahead = how == FULL || how == FULL_BF;
+    typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
+    typedef std::conditional_t<how == FULL_BF, words, f32x4> res_t;
+    typedef std::conditional_t<how == FULL_BF, bf16_t, float> res_e;
     auto place = [&](int a, int t, int &r, int &row, int &col) __attribute__((always_inline)) {
       const int u = t * 64 + lane;
       r = u / PR;
@@ -328,17 +334,17 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       col = col0 + (u - r * PR) * W;
     };
     constexpr int DEEP = 24 / T < 1 ? 1 : 24 / T, RING = TM < DEEP ? TM : DEEP;  // pieces of residual rows in flight
-    f32x4 res[how == FULL ? RING : 1][how == FULL ? T : 1];
+    res_t res[ahead ? RING : 1][ahead ? T : 1];
     auto request = [&](int to, int a) __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         int r, row, col;
         place(a, t, r, row, col);
-        res[to][t] = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(e.residual) +
+        res[to][t] = *reinterpret_cast<const res_t *>(reinterpret_cast<const res_e *>(e.residual) +
                                                       (size_t)min(row, M - 1) * N + min(col, N - W));
       }
     };
-    auto piece = [&](int a, int t, const float *p, f32x4 &own) __attribute__((always_inline)) {
+    auto piece = [&](int a, int t, const float *p, res_t &own) __attribute__((always_inline)) {
       int r, row, col;
       place(a, t, r, row, col);
       if ((16 * PR) % 64 != 0 && r >= 16) return;
@@ -346,7 +352,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       load_n(p + r * S::ROW + (col - col0), v, 1);
       if (row < M && col < N) store((wm * TM + a) * 16 + r, row, col, v, own);
     };
-    if (how == FULL && e.residual) {
+    if (ahead && e.residual) {
 #pragma unroll
       for (int a = 0; a < RING; ++a) request(a, a);
     }
@@ -363,8 +369,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
         for (int t = 0; t < T; ++t) piece(a, t, p, res[0][0]);
       } else {
 #pragma unroll
-        for (int t = 0; t < T; ++t) piece(a, t, p, res[how == FULL ? a % RING : 0][how == FULL ? t : 0]);
-        if constexpr (how == FULL && a + RING < TM) {
+        for (int t = 0; t < T; ++t) piece(a, t, p, res[ahead ? a % RING : 0][ahead ? t : 0]);
+        if constexpr (ahead && a + RING < TM) {
           if (e.residual) request(a % RING, a + RING);
         }
       }
@@ -375,12 +381,13 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   typedef std::integral_constant<int, 8> eight;
   typedef std::integral_constant<int, PLAIN> plain;
   typedef std::integral_constant<int, FULL> full;
+  typedef std::integral_constant<int, FULL_BF> full_bf;
   typedef std::integral_constant<int, ANY> any;
   if (split_k > 1) {
     outputs(four{}, plain{}, [&](int, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
       store_n(partial + ((size_t)ks * M + row) * N + col, v, 1);
     });
-  } else if (!e.vec || (e.residual && !e.res_f32) || (!e.out_f32 && (e.bias || e.residual || e.y2 || e.hooks))) {
+  } else if (!e.vec || (!e.out_f32 && (e.y2 || e.hooks || (e.residual && e.res_f32)))) {
     outputs(four{}, any{}, [&](int in_tile, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
       const float f = sS[in_tile];
       float x[4];
@@ -399,7 +406,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       }
       store_row(e, row, col, N, v);
     });
-  } else if (!e.out_f32) {
+  } else if (!e.out_f32 && !e.bias && !e.residual) {
     outputs(eight{}, plain{}, [&](int in_tile, int row, int col, float (&v)[8], f32x4 &) __attribute__((always_inline)) {
       const float f = sS[in_tile];
 #pragma unroll
@@ -414,22 +421,29 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       store_n(reinterpret_cast<float *>(e.y) + (size_t)row * N + col, v, 1);
     });
   } else {
-    outputs(four{}, full{}, [&](int in_tile, int row, int col, float (&v)[4], f32x4 &res) __attribute__((always_inline)) {
+    auto all = [&](int in_tile, int row, int col, auto &v, auto &res) __attribute__((always_inline)) {
+      constexpr int W = sizeof(v) / sizeof(float);
       const float f = sS[in_tile];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] *= f;
+      for (int i = 0; i < W; ++i) v[i] *= f;
       if (e.bias) {
-        float bv[4];
+        float bv[W];
         load_n(e.bias + col, bv, 1);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] += bv[i];
+        for (int i = 0; i < W; ++i) v[i] += bv[i];
       }
       if (e.residual) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] += res[i];
+        for (int i = 0; i < W; ++i) {
+          if constexpr (std::is_same_v<std::remove_reference_t<decltype(res)>, f32x4>) v[i] += res[i];
+          else v[i] += __uint_as_float(i & 1 ? res[i >> 1] & 0xffff0000u : res[i >> 1] << 16);
+        }
       }
       store_row(e, row, col, N, v);
-    });
+    };
+    if (!e.out_f32) outputs(eight{}, full_bf{}, all);
+    else if (e.residual && !e.res_f32) outputs(four{}, full_bf{}, all);
+    else outputs(four{}, full{}, all);
   }
 #endif
 }
