@@ -41,7 +41,7 @@ struct PanelShape {
   static constexpr size_t after = rows + (size_t)NW * PIECES * PIECE, loop = STAGES * (size_t)SLICE;
   static constexpr size_t lds = loop > after ? loop : after;
   static constexpr bool PAIR = lds <= 80 * 1024;  // two workgroups on a compute unit
-  static_assert(lds <= 160 * 1024 && TN % 2 == 0 && WN <= 4, "LDS of a compute unit; whole 32-column blocks per wave");
+  static_assert(lds <= 160 * 1024 && TN % 4 == 0 && WN <= 4, "LDS of a compute unit; whole 32-column blocks per wave");
   static_assert(UNITS % NW == 0, "loads in flight are counted: every wave has as many");
   static_assert(TM * TN <= 80, "IN_ACC tiles in accumulation registers, the rest in vector registers");
 };
@@ -49,7 +49,8 @@ struct PanelShape {
 #ifdef __HIP_DEVICE_COMPILE__
 // c += w . x.  Written out because the compiler, given all accumulation registers to fill, moves tiles about in the loop.
 // It knows what the statement reads and writes, but not how long a product takes: the loop is led in and followed by
-// enough idle states.
+// enough idle states, tied to the tiles so that no copy of one slips past them.  What the compiler made of it is looked at
+// by a test of the built library.
 template <bool ACC>
 __device__ __forceinline__ void product(f32x4 &c, const bf16x8 &w, const bf16x8 &x) {
   if constexpr (ACC) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
@@ -195,21 +196,35 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
 #pragma unroll
   for (int a = 0; a < AHEAD; ++a) read_a(0, a);
   __builtin_amdgcn_s_waitcnt(0xc07f);
-  // the accumulators are zeroed before this point, and settled behind it
-  static_for<TM * TN>([&](auto i_c) __attribute__((always_inline)) {
-    constexpr int i = decltype(i_c)::value;
-    f32x4 &c = acc[i / TN][i % TN];
-    if constexpr (i < IN_ACC) asm volatile("" : "+a"(c));
-    else asm volatile("" : "+v"(c));
-  });
+  auto pin_tiles = [&]() __attribute__((always_inline)) {
+    static_for<TM * TN>([&](auto i_c) __attribute__((always_inline)) {
+      constexpr int i = decltype(i_c)::value;
+      f32x4 &c = acc[i / TN][i % TN];
+      if constexpr (i < IN_ACC) asm volatile("" : "+a"(c));
+      else asm volatile("" : "+v"(c));
+    });
+  };
+  pin_tiles();  // the accumulators are zeroed before this point, and settled behind it
   asm volatile("s_nop 7" ::);
   __builtin_amdgcn_sched_barrier(0);
   for (int i = kt0; i < kt1; ++i) {
     k_step(std::integral_constant<int, 0>{});
     k_step(std::integral_constant<int, 1>{});
   }
-  // nothing may land in LDS any more, the epilogue reuses it; the last products are done
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15\n\ts_barrier" ::: "memory");
+  // the last products are done: the idle states hold the newest tiles (products finish in order, those before them are done
+  // by then), and no tile is read ahead of them
+  {
+    constexpr int L = TM * TN;
+    f32x4 &n1 = acc[TM - 1][TN - 1], &n2 = acc[TM - 1][TN - 2], &n3 = acc[TM - 1][TN - 3], &n4 = acc[TM - 1][TN - 4];
+    static_assert(L <= IN_ACC || L >= IN_ACC + 4, "the newest four tiles are in one kind of registers");
+    if constexpr (L <= IN_ACC)
+      asm volatile("s_nop 15\n\ts_nop 15" : "+a"(n1), "+a"(n2), "+a"(n3), "+a"(n4));
+    else
+      asm volatile("s_nop 15\n\ts_nop 15" : "+v"(n1), "+v"(n2), "+v"(n3), "+v"(n4));
+  }
+  pin_tiles();
+  // nothing may land in LDS any more, the epilogue reuses it
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 
   float *const sS = reinterpret_cast<float *>(smem);
