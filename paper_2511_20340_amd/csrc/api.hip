@@ -133,6 +133,7 @@ struct Run {
   size_t gemm_ws_bytes = 0;
   int own_ws = 0;     // gemm_ws belongs to a state, whose calls are on one stream; a public operation's may be shared
   int plan_rows = 0;  // rows the linear layers' K partition is chosen for (0: the launch's own M)
+  int part = 1, whole = 1;  // sequences of the pass and of the batch: a part of a batch plans for the whole batch's rows
   // a stale error left by an earlier, unrelated HIP call of the process must not be blamed on us
   Run(const sf_ctx *ctx, hipStream_t stream) : c(ctx), s(stream) { (void)hipGetLastError(); }
   bool ok(hipError_t e) {
@@ -176,7 +177,7 @@ void gemm(Run &r, int dtype, const void *x, const void *w, const void *bias, con
           int K, int out_f32, int glu = 0, int fused_norm = 0, float norm_eps = 0.f, const GemmExtra *ex = nullptr) {
   if (r.st != SF_OK) return;
   GemmArgs g{x, w, bias, res, y, M, N, K, out_f32, glu, r.gemm_ws, r.gemm_ws_bytes};
-  g.plan_M = r.plan_rows;
+  g.plan_M = r.plan_rows ? r.plan_rows : M / r.part * r.whole;
   g.tile = r.c->tune_tile; g.split = r.c->tune_split;
   g.fused_norm = fused_norm; g.norm_eps = norm_eps; g.own_ws = r.own_ws;
   if (ex) {
@@ -389,7 +390,7 @@ sf_status draft_pass(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int
   const size_t es = esize(m.dtype);
   Run r{c, (hipStream_t)stream};
   r.gemm_ws = ws + A.gemm_ws; r.gemm_ws_bytes = A.gemm_ws_bytes; r.own_ws = 1;
-  r.plan_rows = B < st->B ? st->B * qm : 0;  // a part of the batch keeps the whole batch's order of sums
+  r.part = B; r.whole = st->B;  // every layer's rows are B times something
   // context rows: Grouped RMSNorm -> W_D -> K,V of the draft attention layer at the rows' positions
   norm(r, m, st->hooks, w.group_norm, f4, Mh * 4, 4, 1, qm, qm, nullptr);
   gemm(r, m.dtype, f4, w.w_ds, nullptr, nullptr, x, Mh, d, 4 * d, 0);
