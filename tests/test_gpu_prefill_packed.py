@@ -77,6 +77,32 @@ WIDE = synth.ModelShape("t", 2, 1024, 8, 1, 64, 4096, 1032, "bf16")
 HALF, ALL, BLOCK = 32, 64, 16
 
 
+def test_bits_of_the_whole_batch_where_its_plan_matters():
+    d, F = WIDE.d_model, WIDE.d_ffn
+    for N, K in ((d, F), (d, 4 * d)):
+        assert linear_choice(HALF * BLOCK, N, K)[2] == 4 and linear_choice(ALL * BLOCK, N, K)[2] == 1
+    assert (8 * BLOCK + 31) // 32 * HALF == 128                  # attention workgroups per key chunk
+    k, cap = 4, 704
+    lens = [(600 + 13 * i) % 60 + 600 for i in range(HALF)] + [5 + i for i in range(ALL - HALF)]
+    lens = [lens[(i * 27) % ALL] for i in range(ALL)]             # long and short ones mixed
+    tw, dw = synth.target_weights(WIDE, 17, 0.05), synth.draft_weights(WIDE, k, 17, 0.05)
+    eng, ref = (E.Engine(WIDE.cfg(), ALL, cap, k) for _ in range(2))
+    eng.bind(tw, dw)
+    ref.bind_shared(eng, with_draft=True)
+    prompts = synth.prompts(lens, WIDE.vocab, 19)
+    first = eng.prefill(prompts, block=BLOCK)
+    helper = E.Engine(ref.cfg, ALL, cap, BLOCK - 1, share_caches=ref)
+    helper.bind_shared(ref, with_draft=True)
+    want = E._prefill_blocks(helper, prompts, BLOCK, k)
+    torch.cuda.synchronize()
+    assert torch.equal(first, want) and eng.kv_len.tolist() == lens
+    for name in ("tk", "tv", "dk", "dv"):
+        a, b = getattr(eng, name), getattr(ref, name)
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+    rows = helper.hooks[torch.arange(ALL), (helper.n_new.long() - 1).cpu()]
+    assert torch.equal(eng.hooks[:, 0], rows)
+
+
 @pytest.mark.parametrize("n,k_draft", [(HALF, 2), (HALF, 4), (24, 1), (1, 4)])
 def test_last_block_over_a_part_of_the_batch(n, k_draft):
     """sf_prefill_step(last) over the first n rows leaves those sequences, in their cache slots, what the three steps over the
