@@ -560,6 +560,7 @@ sf_status sf_prefill_step(sf_ctx *c, const sf_state *st, int32_t k, const int32_
   if (v != SF_OK) return v;
   if (n_seq < 1 || n_seq > st->B || !slots || !block_len || !target_ids || !accept_len || !out_tokens) return SF_EINVAL;
   if (k_draft < 0 || k_draft > c->max_k || (k_draft > 0 && !draft_tokens) || len_after < 0) return SF_EINVAL;
+  if (k_draft > k && (v = check_state(c, st, k_draft, true)) != SF_OK) return v;  // room for the draft too, before the commit
   if (last && (long)len_after + k_draft > st->cap) return SF_ECAPACITY;
   const Subset sub{n_seq, slots, last != 0};
   if ((v = verify_pass(c, st, k, tokens, len_upper, nullptr, target_ids, stream, sub)) != SF_OK) return v;

@@ -156,3 +156,43 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(sfb, "LIB_PATH", "/nonexistent/libspecformer.so")
     with pytest.raises(RuntimeError, match="no CPU fallback"):
         sfb.lib()
+
+
+def test_prefill_step_validates_before_launching_anything():
+    """Nothing may be committed by a call that is refused: every argument, the draft step's too, is looked at first."""
+    L = sfb.lib()
+    fake = 0x10000
+    st, ctx = create(cfg(), cfg(n_layers=1))
+    assert st == sfb.SF_OK
+    tw, dw, s = sfb.TargetWeights(), sfb.DraftWeights(), sfb.State()
+    arr = (C.c_void_p * 2)(fake, fake)
+    for n, _ in sfb.TargetWeights._fields_:
+        setattr(tw, n, arr if n not in ("embed", "lm_head", "final_norm") else fake)
+    for n, _ in sfb.DraftWeights._fields_:
+        setattr(dw, n, None if n.startswith("sa_") else fake)
+    for n in ("tk", "tv", "dk", "dv", "kv_len", "pending", "hooks", "n_new", "cu_new"):
+        setattr(s, n, fake)
+    s.B, s.cap, s.workspace, s.workspace_bytes = 4, 128, fake, L.sf_workspace_bytes(ctx, 4, 4, 128)
+
+    def call(**kw):
+        a = dict(k=4, tokens=fake, block_len=fake, n_seq=4, slots=fake, upper=0, after=5, k_draft=4, last=1, ids=fake, acc=fake,
+                 out=fake, draft=fake)
+        a.update(kw)
+        return L.sf_prefill_step(ctx, C.byref(s), a["k"], a["tokens"], a["block_len"], a["n_seq"], a["slots"], a["upper"],
+                                 a["after"], a["k_draft"], a["last"], a["ids"], a["acc"], a["out"], a["draft"], None)
+    assert call() == sfb.SF_ESTATE                                        # not bound
+    assert L.sf_bind(ctx, C.byref(tw), None) == sfb.SF_OK
+    assert call() == sfb.SF_ESTATE                                        # no draft weights to follow with
+    assert L.sf_bind(ctx, C.byref(tw), C.byref(dw)) == sfb.SF_OK
+    for bad in (dict(n_seq=0), dict(n_seq=5), dict(k=-1), dict(k=5), dict(k_draft=-1), dict(k_draft=5), dict(after=-1),
+                dict(upper=-1), dict(tokens=None), dict(block_len=None), dict(slots=None), dict(ids=None), dict(acc=None),
+                dict(out=None), dict(draft=None)):
+        assert call(**bad) == sfb.SF_EINVAL, bad
+    assert call(upper=124) == sfb.SF_ECAPACITY                            # 124 + 5 > 128: the block
+    assert call(upper=120, after=125) == sfb.SF_ECAPACITY                 # 125 + 4 > 128: the draft slots behind it
+    # room for the block's buffers, not for the longer draft's
+    s.workspace_bytes = L.sf_workspace_bytes(ctx, 4, 1, 128)
+    assert s.workspace_bytes < L.sf_workspace_bytes(ctx, 4, 4, 128)
+    assert call(k=1, k_draft=4) == sfb.SF_ECAPACITY
+    assert L.sf_last_hip_error(ctx) == 0                                  # nothing was launched
+    L.sf_destroy(ctx)
