@@ -433,7 +433,8 @@ sf_status draft_pass(sf_ctx *c, const sf_state *st, int32_t k, int32_t mask, int
     rq.kv_only = 0; rq.pos_mode = 0; rq.theta = m.rope_theta;
     LAUNCH(K_ROPE, launch_rope_table(rq, r.s));
     LAUNCH(K_ROPE, launch_rope_kv(rq, m.dtype, r.s));
-    attention(r, m, qr1, st->dk, st->dv, len_m1, ao1, part_o, part_ml, B, 1, cap, SF_MASK_CAUSAL, len_upper, nullptr, nullptr, nullptr, nullptr, st->B);
+    attention(r, m, qr1, st->dk, st->dv, len_m1, ao1, part_o, part_ml, B, 1, cap, SF_MASK_CAUSAL, len_upper, nullptr, nullptr,
+              nullptr, sub.slots, st->B);
     gemm(r, m.dtype, ao1, w.wo, nullptr, x_last, id_last, B, d, nq, 1);  // float row of the stream
     norm(r, m, id_last, w.pos_norm, xl, B, 1, 3, 1, 1, st->n_new, 1);
     // the slots attend to each other only: an empty prefix in a one-tile cache of their own
