@@ -23,21 +23,26 @@ def planted_logits(B, k, V, seed, match_p):
     return lg, draft.astype(np.int32)
 
 
-@pytest.mark.parametrize("B,k,V", [(64, 4, 4096), (256, 6, 1000), (5, 1, 77), (1, 0, 512), (700, 2, 64)])
+# blocks of up to 16 tokens: each thread writes its sequences' tokens; longer ones: all threads write all of them
+@pytest.mark.parametrize("B,k,V", [(64, 4, 4096), (256, 6, 1000), (5, 1, 77), (1, 0, 512), (700, 2, 64),
+                                   (70, 15, 96), (2, 16, 96), (300, 16, 64), (33, 63, 64), (257, 127, 32)])
 @pytest.mark.parametrize("forced", [False, True])
 def test_accept_commit_bit_exact(B, k, V, forced):
     shape = synth.ModelShape("t", 1, 64, 2, 2, 64, 64, V, "bf16")
-    lg, draft = planted_logits(B, k, V, B + k, 0.7)
+    cap = 64 if k < 14 else 192
+    lg, draft = planted_logits(B, k, V, B + k, 0.7 if k < 14 else 0.97)
     lg[0, 0, [3, V - 1]] = 30.0                                   # a tie: lowest index wins
     g = synth.rng(3, 3)
     len0 = g.integers(0, 50, B).astype(np.int32)
     pend0 = g.integers(0, V, B).astype(np.int32)
     force = g.integers(0, k + 2, B).astype(np.int32) if forced else None
-    orc = sfo.Oracle(shape.cfg(), synth.target_weights(shape, 1), None, B, 64, k + 1)
+    if forced and B > 1:    # none and the whole block among them
+        force[0], force[-1] = 0, k + 1
+    orc = sfo.Oracle(shape.cfg(), synth.target_weights(shape, 1), None, B, cap, k + 1)
     orc.kv_len[:] = len0; orc.pending[:] = pend0
     acc_o, out_o = orc.accept_commit(k, draft, lg, force_len=force)
 
-    eng = engine_only(shape, B, 64, k)
+    eng = engine_only(shape, B, cap, k)
     eng.bind(synth.target_weights(shape, 1))
     eng.set_state(kv_len=len0, pending=pend0, n_new=np.zeros(B, np.int32))
     d = torch.from_numpy(draft).cuda()
