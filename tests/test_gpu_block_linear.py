@@ -117,7 +117,7 @@ def test_block_gate(M, F, K):
 @pytest.mark.parametrize("split", [1, 2, 4])
 def test_block_gate_with_the_norm(split):
     """Gate and up projection as a step runs them, with the fused norm, every layer of the step forced onto each tile."""
-    shape, B, k, cap = synth.ModelShape("t", 1, 512, 4, 2, 128, 544, 1032, "bf16"), 15, 4, 64
+    shape, B, k, cap = synth.ModelShape("t", 1, 512, 4, 2, 128, 640, 1032, "bf16"), 15, 4, 64
     weights = synth.target_weights(shape, 3, 0.05)
     g = synth.rng(55, split)
     toks = g.integers(0, shape.vocab, (B, k + 1)).astype(np.int32)
@@ -135,6 +135,7 @@ def test_block_gate_with_the_norm(split):
         for tile in BLOCK_TILES:
             if block_runs(tile, B * (k + 1), 2 * shape.d_ffn, shape.d_model, split, sfb.SF_LINEAR_GLU | sfb.SF_LINEAR_NORM):
                 ran += 1
+                assert block_runs(tile, B * (k + 1), shape.d_model, shape.d_ffn, split)      # the down projection too
                 for got, ref in zip(step(tile), want):
                     assert torch.equal(got, ref), tile
     finally:

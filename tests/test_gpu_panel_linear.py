@@ -93,12 +93,21 @@ def test_a_norm_without_workspace_runs_on_tiles_that_need_none():
     assert linear_choice(M, N, K, ws=0)[:2] == (sfb.SF_KERNEL_BLOCK, 15)
 
 
-@pytest.mark.parametrize("tile", ROWS)
-@pytest.mark.parametrize("split,vocab", [(1, 1032), (2, 1032), (1, 1001)])
-def test_residual_stream_in_a_step(tile, split, vocab):
+# d_ffn 544: K of the down projection is no whole number of slices, so that layer stays with the ring kernel beside the others
+@pytest.mark.parametrize("tile,split,vocab,d_ffn", [(t, s, v, f) for t in ROWS for s, v, f in
+                                                    ((1, 1032, 576), (1, 1001, 576), (2, 1032, 576), (1, 1032, 544))
+                                                    if s == 1 or t < 26])        # 26-28: unsplit layers only
+def test_residual_stream_in_a_step(tile, split, vocab, d_ffn):
     """A whole step forced onto the tile: norm, gate, float residual, bf16 copy, hooked copies, logits and arg-max; more rows
     than the tile has, and not a multiple; a vocabulary whose rows of logits are off 16 bytes."""
-    shape, B, k, cap = synth.ModelShape("t", 2, 512, 4, 2, 128, 544, vocab, "bf16"), 67, 4, 64
+    shape, B, k, cap = synth.ModelShape("t", 2, 512, 4, 2, 128, d_ffn, vocab, "bf16"), 67, 4, 64
+    M, d = B * (k + 1), shape.d_model
+    for name, N, K, flags in [("qkv", 1024, d, sfb.SF_LINEAR_NORM), ("o", d, 512, 0), ("down", d, d_ffn, 0),
+                              ("gate and up", 2 * d_ffn, d, sfb.SF_LINEAR_GLU | sfb.SF_LINEAR_NORM),
+                              ("head", vocab, d, sfb.SF_LINEAR_ARGMAX)]:
+        ring = (name == "head" and tile >= 26) or (name == "down" and d_ffn % 64)
+        assert linear_choice(M, N, K, flags, tile=tile, split=split)[:2] == \
+            ((sfb.SF_KERNEL_RING, 10) if ring else (sfb.SF_KERNEL_BLOCK, tile)), name
     weights = synth.target_weights(shape, 5, 0.05)
     toks = synth.rng(63, tile).integers(0, shape.vocab, (B, k + 1)).astype(np.int32)
     eng = Engine(shape.cfg(), B, cap, k)
