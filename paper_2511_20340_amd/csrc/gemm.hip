@@ -252,15 +252,17 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
 }
 
 // What a launch of a layer takes on MI355X, in us; the measured side of the choice below.  A compute unit works through its
-// workgroups one after the other (`least`: how many it takes to keep it busy), each a fixed part and a part per 64
-// positions of K (with the fused norm a little more); the weights have to come from memory, which overlaps a good half of
-// the shorter of the two; a split adds the second launch and its partial rows, unless groups of waves share it.  The tiles
-// of both kernels x splits 1 to 8 were measured on 440 shapes (the 1B, 8B and 14B layers and heads at 40 to 2304 rows,
-// weights cold, medians of interleaved repeats) and the constants fitted to them: 4.8 % rms.  Since float outputs leave in
-// whole lines, launches of the tall tiles are up to 12 % faster than this; constants fitted anew choose no better.  (Tile
+// workgroups one after the other (`least`: so many count where fewer do not keep it busy), each a fixed part and a part per
+// 64 positions of K (with the fused norm a little more); the weights have to come from memory, which overlaps a good half of
+// the shorter of the two; a split adds the second launch and its partial rows, unless groups of waves share it.  The ring
+// and block kernels' tiles x splits 1 to 8 were measured on 440 shapes (the 1B, 8B and 14B layers and heads at 40 to 2304
+// rows, weights cold, medians of interleaved repeats) and the constants fitted to them: 4.8 % rms.  Since float outputs leave
+// in whole lines, launches of the tall tiles are up to 12 % faster than this; constants fitted anew choose no better.  (Tile
 // 20's norm by hand: its waves have one row block, and the squares of one chunk wait for each other.)  The panel kernel's
 // tiles (15-17, 26-28) were fitted to 360 shapes of 40 to 2304 rows, weights rotated through 600 MB, 6 to 9 % rms; their
 // norm is a launch in front, priced 4 us above what it takes by itself: so much more a launch costs in the chain of a step.
+// Tile 18 has one row for both kernels: the constants are the block kernel's, which it runs on with the norm; without it the
+// panel kernel's times are 0.82 to 1.07 of the formula's (13 shapes of 192 to 2048 rows, 7 % rms).
 struct TileCost {
   int bm, bn, groups;
   float slice, fixed, least, norm;
@@ -270,18 +272,18 @@ constexpr TileCost TILE_COST[N_TILES + 1] = {
     {32, 128, 1, 0.241f, 1.2f, 1.19f, 0.000f}, {64, 128, 1, 0.304f, 2.0f, 1.27f, 0.018f},
     {96, 128, 1, 0.385f, 3.2f, 1.11f, 0.034f}, {128, 128, 1, 0.493f, 2.9f, 1.09f, 0.045f},
     {160, 128, 1, 0.636f, 3.0f, 1.06f, 0.044f}, {64, 256, 1, 0.540f, 2.7f, 1.10f, 0.002f},
-    {96, 256, 1, 0.708f, 5.7f, 0.96f, 0.026f}, {128, 256, 1, 0.849f, 4.1f, 0.94f, 0.044f},
-    {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f}, {160, 256, 1, 1.105f, 4.5f, 0.96f, 0.086f},
-    {320, 256, 1, 2.072f, 2.4f, 0.96f, 0.333f}, {256, 256, 1, 1.593f, 3.3f, 0.94f, 0.302f},
-    {224, 256, 1, 1.560f, 4.4f, 0.95f, 0.095f}, {192, 256, 1, 1.167f, 6.0f, 0.92f, 0.096f},
-    {320, 256, 1, 1.403f, 11.3f, 0.85f, 6.2f}, {256, 256, 1, 1.238f, 8.9f, 0.11f, 7.0f},
-    {192, 256, 1, 1.071f, 7.1f, 0.97f, 7.2f}, {128, 256, 1, 0.744f, 4.5f, 0.90f, 0.081f},
+    {96, 256, 1, 0.708f, 5.7f, 1.00f, 0.026f}, {128, 256, 1, 0.849f, 4.1f, 1.00f, 0.044f},
+    {160, 256, 1, 1.105f, 4.5f, 1.00f, 0.086f}, {160, 256, 1, 1.105f, 4.5f, 1.00f, 0.086f},
+    {320, 256, 1, 2.072f, 2.4f, 1.00f, 0.333f}, {256, 256, 1, 1.593f, 3.3f, 1.00f, 0.302f},
+    {224, 256, 1, 1.560f, 4.4f, 1.00f, 0.095f}, {192, 256, 1, 1.167f, 6.0f, 1.00f, 0.096f},
+    {320, 256, 1, 1.403f, 11.3f, 1.00f, 6.2f}, {256, 256, 1, 1.238f, 8.9f, 1.00f, 7.0f},
+    {192, 256, 1, 1.071f, 7.1f, 1.00f, 7.2f}, {128, 256, 1, 0.744f, 4.5f, 1.00f, 0.081f},
     {128, 64, 1, 0.293f, 1.7f, 1.12f, 0.041f}, {64, 64, 1, 0.199f, 1.1f, 1.12f, 0.140f},
-    {160, 64, 1, 0.392f, 3.2f, 0.97f, 0.081f}, {160, 128, 1, 0.548f, 4.9f, 0.91f, 0.117f},
-    {64, 64, 2, 0.469f, 0.2f, 0.63f, 0.083f}, {32, 64, 4, 0.737f, 0.0f, 0.52f, 0.089f},
-    {32, 64, 2, 0.348f, 0.1f, 0.95f, 0.038f}, {128, 128, 1, 0.526f, 1.1f, 0.69f, 8.5f},
-    {160, 128, 1, 0.486f, 1.9f, 1.63f, 7.8f}, {160, 128, 1, 0.509f, 4.3f, 0.61f, 7.0f},
-    {320, 256, 1, 1.691f, 2.6f, 0.86f, 0.230f}, {256, 256, 1, 1.317f, 3.2f, 0.84f, 0.232f}, {192, 256, 1, 1.027f, 3.7f, 0.84f, 0.143f},
+    {160, 64, 1, 0.392f, 3.2f, 1.00f, 0.081f}, {160, 128, 1, 0.548f, 4.9f, 1.00f, 0.117f},
+    {64, 64, 2, 0.469f, 0.2f, 1.00f, 0.083f}, {32, 64, 4, 0.737f, 0.0f, 1.00f, 0.089f},
+    {32, 64, 2, 0.348f, 0.1f, 1.00f, 0.038f}, {128, 128, 1, 0.526f, 1.1f, 1.00f, 8.5f},
+    {160, 128, 1, 0.486f, 1.9f, 1.63f, 7.8f}, {160, 128, 1, 0.509f, 4.3f, 1.00f, 7.0f},
+    {320, 256, 1, 1.691f, 2.6f, 1.00f, 0.230f}, {256, 256, 1, 1.317f, 3.2f, 1.00f, 0.232f}, {192, 256, 1, 1.027f, 3.7f, 1.00f, 0.143f},
 };
 double cost_us(int M, int N, int K, GemmConfig c, int norm) {
   const TileCost &t = TILE_COST[c.tile];

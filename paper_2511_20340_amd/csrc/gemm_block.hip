@@ -55,9 +55,10 @@ hipError_t prepare_block() {
 
 int block_groups(int tile) { return tile == 24 ? 4 : tile == 23 || tile == 25 ? 2 : 1; }
 
-// Whole slices of K; 32-bit byte offsets into both operands; arg-max partials are kept per 128 columns at the finest; a
-// tile with groups takes the layers whose K is split that often; with the norm the panel kernel's row sums of squares go
-// through memory: norm_ws bytes of the workspace (gemm_norm_bytes; -1: no norm), or, split, beside the partial tiles.
+// Whole slices of K; 32-bit byte offsets into both operands; arg-max partials are kept per 128 columns at the finest, and
+// 26-28 are built without them (heads of many rows choose 15-18); a tile with groups takes the layers whose K is split that
+// often; with the norm the panel kernel's row sums of squares go through memory: norm_ws bytes of the workspace
+// (gemm_norm_bytes; -1: no norm), or, split, beside the partial tiles.
 bool block_takes(int tile, int M, int N, int K, int split, bool am, ptrdiff_t norm_ws) {
   if (tile < 15 || tile > 31 || (am && tile >= 19 && tile != 22)) return false;
   const int parts = make_plan(M, N, K, 32, 32, split).split_k;

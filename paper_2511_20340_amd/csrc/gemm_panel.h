@@ -41,6 +41,7 @@ struct PanelShape {
   static constexpr size_t after = rows + (size_t)NW * PIECES * PIECE, loop = STAGES * (size_t)SLICE;
   static constexpr size_t lds = loop > after ? loop : after;
   static constexpr bool PAIR = lds <= 80 * 1024;  // two workgroups on a compute unit
+  static constexpr bool HEAD = TN >= 8;           // takes LM heads: the narrow tiles are built without the arg-max
   static_assert(lds <= 160 * 1024 && TN % 4 == 0 && WN <= 4, "LDS of a compute unit; whole 32-column blocks per wave");
   static_assert(UNITS % NW == 0, "loads in flight are counted: every wave has as many");
   static_assert(TM * TN <= 80, "IN_ACC tiles in accumulation registers, the rest in vector registers");
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   }
 
   const int col0 = n0 + wn * TN * 16;
-  if (e.am_val) {
+  if (S::HEAD && e.am_val) {
     // Arg-max partials of this workgroup's columns: a lane walks its columns in ascending order (a NaN is never greater),
     // the four lanes of a row and the WN waves compare value, then column.  Columns past N never take part.
     float *s_val = sS + BM;                                      // [WN][BM]
@@ -485,7 +486,7 @@ hipError_t run_panel(const GemmArgs &a, hipStream_t s, int split) {
   if (!plan_fits(p, S::BM, a.ws, a.ws_bytes) || (a.fused_norm && !two && !squares_fit(a.M, gemm_norm_bytes(a)))) return hipErrorInvalidValue;
   const int groups = (p.tiles_n * p.split_k + XCDS - 1) / XCDS;
   float *partial = two ? (float *)((char *)a.ws + GEMM_SSQ_BYTES) : nullptr;
-  if (a.am_val && (p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;
+  if (a.am_val && (!S::HEAD || p.split_k != 1 || a.am_stride < p.tiles_n || a.fused_norm)) return hipErrorInvalidValue;
   if (a.am_val && a.am_parts_out) *a.am_parts_out = p.tiles_n;
   const Epilogue e = make_epilogue(a);
   hipError_t err = ensure_panel_lds<WM, WN, TM, TN, STAGES>();
