@@ -226,7 +226,7 @@ sf_status sf_op_attention(const sf_ctx *ctx, const void *q, const void *kc, cons
  * 16 so that the linear kernel's epilogue can form silu(gate)*up in registers.
  * col_gain (dev elem [K], or NULL): SF_BF16 only -- the gain vector of the RMSNorm whose output this
  * layer consumes, folded into the weight's columns (w[n][k] * col_gain[k], rounded to bf16 once).  The
- * decoder's norm + linear pairs run as ONE kernel on such weights (see sf_op_rmsnorm_linear), which is
+ * decoder's norm + linear pairs run without a norm kernel on such weights (see sf_op_rmsnorm_linear), which is
  * why, in SF_BF16 mode, the weight structs below want wqkv, w_gate_up and sa_wqkv packed with their
  * norm's gains; SF_F32 mode ignores col_gain and applies the gains in its norm kernel. */
 size_t sf_packed_weight_bytes(const sf_ctx *ctx, int32_t N, int32_t K);

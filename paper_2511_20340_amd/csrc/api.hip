@@ -229,9 +229,9 @@ void norm(Run &r, const sf_model_cfg &m, const void *x, const void *gain, void *
   LAUNCH(K_NORM, launch_rmsnorm(n, m.dtype, r.s));
 }
 
-// y = RMSNorm(x; gain) . w^T, one kernel.  bf16: w was packed with the gain folded into its columns, the linear
-// kernel takes the raw rows, sums their squares while staging them and scales its accumulators by the row
-// factor.  fp32: the linear kernel multiplies the rows by the gain as they arrive.
+// y = RMSNorm(x; gain) . w^T.  bf16: w was packed with the gain folded into its columns, the linear kernel takes the raw
+// rows, sums their squares while staging them (the panel kernel: a launch in front does) and scales its accumulators by the
+// row factor.  fp32: the linear kernel multiplies the rows by the gain as they arrive.
 // x: the rows in fp32 mode; xb: their bf16 copy in bf16 mode (rows of the residual stream are kept as float
 // plus a bf16 copy for exactly this use).
 void norm_gemm(Run &r, const sf_model_cfg &m, const void *x, const void *xb, const void *gain, const void *w, void *y,

@@ -8,7 +8,7 @@
 // packed weight units are LDS fragments as they are.  Activations arrive in rows of whole 128-byte lines (64-byte pieces
 // of half as long slices cost 4 to 10 % more).
 // What bounds it: operand latency.  512 x 2048 x 2048 9.7 us (ring kernel 16.7), 320 x 5120 x 13824 67 (88).  The largest
-// tiles are the panel kernel's (gemm_panel.h): 1280 x 28672 x 4096 with the norm 270 us on eight waves here, 232 there.
+// tiles are the panel kernel's (gemm_panel.h): 1280 x 28672 x 4096 with the norm 272 us on eight waves here, 238 there.
 //
 // Same products in the same order, same K partition, same row sums as the ring kernel: the same bits.
 //

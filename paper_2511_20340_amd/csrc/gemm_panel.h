@@ -80,7 +80,8 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   const int xcd = id % XCDS, j = id / XCDS;
   // The units of an XCD and the row tiles that share a unit's weights: those side by side, or, where a compute unit holds
   // two workgroups, all units of one row tile first, so that the second half of a not quite full round spreads evenly
-  // (320 x 28672 x 4096 on 160 x 128: 86 -> 75 us; with one to a compute unit 1280 x 28672 x 4096 takes 241 us that way, 222).
+  // (320 x 28672 x 4096 on 160 x 128 with two: 97 us side by side, 93 this way; 1280 x 28672 x 4096 on 320 x 256 with one
+  // takes 247 us this way, 230 side by side; single unsplit launches on one card, bf16 out, weights rotated).
   const int per = (tiles_n * split_k + XCDS - 1) / XCDS;
   const int tm = S::PAIR ? j / per : j % tiles_m, unit = (S::PAIR ? j % per : j / tiles_m) * XCDS + xcd;
   if (unit >= tiles_n * split_k) return;

@@ -428,11 +428,13 @@ class Engine:
 
     # ---- prefill: chunked verify with forced acceptance --------------------------------------
     def prefill(self, prompts, block=None):
-        """Feeds every prompt through sf_verify_step in blocks of `block` tokens (default max_k+1) with forced
-        commits, right-aligned so that all sequences finish with the last block, and runs sf_draft_step after
-        every block so the draft cache follows.  A block longer than max_k+1 runs on a helper engine created
-        for that block length (same weights, same caches); its final lengths, pending tokens and newest hooked
-        rows are then handed to this engine.  Returns the first emitted token of every sequence (device)."""
+        """Feeds every prompt through the target in blocks of `block` tokens (default max_k+1) with forced commits,
+        right-aligned so that all sequences finish with the last block, the draft cache following.  Blocks of up to
+        max_k+1 tokens run sf_verify_step, sf_accept_commit and sf_draft_step over the whole batch.  A longer block runs
+        on a helper engine created for that block length (same weights, same caches): one sf_prefill_step per block over
+        the prompts that have started, or, where a prompt is empty, the three steps over the whole batch; its final lengths,
+        pending tokens and newest hooked rows are then handed to this engine.  Returns the first emitted token of every
+        sequence (device)."""
         q = self.max_k + 1 if block is None else int(block)
         if q <= self.max_k + 1:
             return _prefill_blocks(self, prompts, q, self.max_k)
