@@ -12,7 +12,8 @@ extern "C" {
 
 /* Force the linear kernels' tile configuration (1..sf_linear_num_tiles()) and split-K factor for every
  * later launch of this context; 0 = automatic choice.  A forced pair whose partial tiles do not fit the
- * workspace makes the launch fail with SF_EHIP. host. */
+ * workspace makes the launch fail with SF_EHIP.  Tiles 15-17 and 26-28 leave a fused norm's row sums of squares in the workspace,
+ * public operations included. host. */
 sf_status sf_tune_linear(sf_ctx *ctx, int32_t tile, int32_t split_k);
 int32_t sf_linear_num_tiles(void);
 /* The K split of a bf16 linear layer of M rows whose weight [N][K] is also used with up to plan_M >= M rows, and the ring

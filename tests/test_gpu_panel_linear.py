@@ -155,6 +155,43 @@ def test_argmax(tile, N):
         eng.sf_tune_linear(0, 0)
 
 
+@pytest.mark.parametrize("tile,rows", [(29, 320), (30, 256), (31, 192)])
+def test_norm_tiles_of_eight_waves(tile, rows):
+    """Tiles 29-31 at their edges: the norm into floats and bf16, and the gated norm inside a step; the ring kernel's bits.  One
+    slice of K (every load past it repeats the last), two, as many as are kept in LDS and one more."""
+    eng = engine()
+    try:
+        for M, N, K in [(rows - 1, 256, 64), (rows, 264, 128), (rows + 1, 504, 192), (2 * rows, 8, 576)]:
+            assert linear_choice(M, N, K, sfb.SF_LINEAR_NORM | sfb.SF_LINEAR_OP, tile=tile, split=1) == (sfb.SF_KERNEL_BLOCK, tile, 1)
+            assert linear_choice(M, N, K, tile=tile, split=1) == (sfb.SF_KERNEL_RING, 10, 1)      # without the norm
+            g = synth.rng(66, tile + M)
+            x = synth.to_bf16_values(g.standard_normal((M, K), dtype=np.float32))
+            w = synth.to_bf16_values(g.standard_normal((N, K), dtype=np.float32) * 0.05)
+            gain = synth.to_bf16_values(1.0 + 0.5 * g.standard_normal(K, dtype=np.float32))
+            xd, gd = dev(x, "bf16"), dev(gain, "bf16")
+            folded = (eng.sf_pack_weight(dev(w, "bf16"), gain=gd), N)
+
+            def outputs(t):
+                eng.sf_tune_linear(t, 1)
+                return [eng.sf_op_rmsnorm_linear(xd, gd, None, out_f32=f, packed=folded) for f in (True, False)]
+            want = outputs(RING_TILE)
+            assert rel_err(to_np(want[0]), sfo.linear(sfo.rmsnorm(x, gain, 1e-6), w)) < 5e-3   # the gain is rounded in once
+            for got, ref in zip(outputs(tile), want):
+                assert torch.equal(got, ref), (M, N, K)
+    finally:
+        eng.sf_tune_linear(0, 0)
+    shape, B, k = synth.ModelShape("t", 1, 512, 4, 2, 128, 544, 1032, "bf16"), 67, 4
+    eng = Engine(shape.cfg(), B, 64, k)
+    eng.bind(synth.target_weights(shape, 5, 0.05), None)
+    toks = synth.rng(67, tile).integers(0, shape.vocab, (B, k + 1)).astype(np.int32)
+    out = []
+    for t in (RING_TILE, tile):
+        eng.sf_tune_linear(t, 1)
+        eng.set_state(kv_len=np.full(B, 2, np.int32), pending=toks[:, 0], n_new=np.ones(B, np.int32))
+        out.append([t.clone() for t in eng.sf_verify_step(k, torch.from_numpy(toks[:, 1:].copy()).cuda())])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
 @pytest.mark.parametrize("tile,M,N,K", [(29, 576, 28672, 512), (30, 1280, 20480, 512), (31, 320, 24576, 1024)])
 def test_a_public_norm_leaves_the_workspace_alone(tile, M, N, K):
     """Unsplit, sf_op_rmsnorm_linear writes nothing into its workspace, which streams may share; with it, without it and on the
