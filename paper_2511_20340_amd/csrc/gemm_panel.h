@@ -65,6 +65,37 @@ __device__ __forceinline__ f32x4 finished(f32x4 &c) {
 }
 #endif
 
+// store_row for whole units of W columns at any address, without a branch on the alignment (vector stores need none; a branch per
+// unit holds up the stores behind it: float outputs with a residual 7 % slower)
+template <int W>
+__device__ __forceinline__ void store_at(bf16_t *p, const float (&v)[W]) {
+  typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
+  typedef words words_at __attribute__((aligned(2)));
+  words w;
+#pragma unroll
+  for (int i = 0; i < W / 2; ++i) w[i] = pack2bf(v[2 * i], v[2 * i + 1]);
+  *reinterpret_cast<words_at *>(p) = w;
+}
+template <int W>
+__device__ __forceinline__ void store_at(float *p, const float (&v)[W]) {
+  typedef f32x4 f32x4_at __attribute__((aligned(4)));
+#pragma unroll
+  for (int j = 0; j < W; j += 4) *reinterpret_cast<f32x4_at *>(p + j) = f32x4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+}
+template <int W>
+__device__ __forceinline__ void store_row_at(const Epilogue &e, int row, int col, int N, const float (&r)[W]) {
+  const size_t o = (size_t)row * N + col;
+  if (e.out_f32) store_at(reinterpret_cast<float *>(e.y) + o, r);
+  else store_at(reinterpret_cast<bf16_t *>(e.y) + o, r);
+  if (e.y2) store_at(e.y2 + o, r);
+  if (e.hooks) {
+    const size_t hrow = ((size_t)(row / e.hook_q) * e.hook_qmax + row % e.hook_q) * 4;
+#pragma unroll
+    for (int g = 1; g < 4; ++g)
+      if (e.hook_mask >> g & 1) store_at(e.hooks + (hrow + g) * N + col, r);
+  }
+}
+
 template <int WM, int WN, int TM, int TN, int STAGES>
 __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_t *__restrict__ A, const uint4 *__restrict__ Wp,
                                                                      const Epilogue e, int M, int N, int K, int tiles_m,
@@ -333,9 +364,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     return;
   }
   // how_c: PLAIN rows; FULL, FULL_BF: bias, a float or bf16 residual (requested as many pieces ahead as registers allow: y may
-  // be the residual, a lane's own elements), bf16 copy, hooked copies; ANY: any types and addresses, in a loop that is not
-  // unrolled and waits for every residual (1280 x 28672 x 4096, bf16 with bias and residual: 373 us that way, FULL_BF 250;
-  // without either 245)
+  // be the residual, a lane's own elements; at any address), bf16 copy, hooked copies; ANY: rows that end within the W, any
+  // types, in a loop that is not unrolled and waits for every residual (1280 x 28672 x 4096, bf16 with bias and residual: 373
+  // us that way, FULL_BF 250; without either 245)
   enum { PLAIN, FULL, FULL_BF, ANY };
   auto outputs = [&](auto w_c, auto how_c, auto store) __attribute__((always_inline)) {
     constexpr int W = decltype(w_c)::value, PR = TN * 16 / W, T = (16 * PR + 63) / 64;  // units per row; units per lane
@@ -344,6 +375,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
     typedef std::conditional_t<how == FULL_BF, words, f32x4> res_t;
     typedef std::conditional_t<how == FULL_BF, bf16_t, float> res_e;
+    typedef res_t __attribute__((aligned(sizeof(res_e)))) res_at;
     auto place = [&](int a, int t, int &r, int &row, int &col) __attribute__((always_inline)) {
       const int u = t * 64 + lane;
       r = u / PR;
@@ -357,7 +389,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       for (int t = 0; t < T; ++t) {
         int r, row, col;
         place(a, t, r, row, col);
-        res[to][t] = *reinterpret_cast<const res_t *>(reinterpret_cast<const res_e *>(e.residual) +
+        res[to][t] = *reinterpret_cast<const res_at *>(reinterpret_cast<const res_e *>(e.residual) +
                                                       (size_t)min(row, M - 1) * N + min(col, N - W));
       }
     };
@@ -404,7 +436,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     outputs(four{}, plain{}, [&](int, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
       store_n(partial + ((size_t)ks * M + row) * N + col, v, 1);
     });
-  } else if (!e.vec || (!e.out_f32 && (e.y2 || e.hooks || (e.residual && e.res_f32)))) {
+  } else if (N % 8 != 0 || (!e.out_f32 && (e.y2 || e.hooks || (e.residual && e.res_f32)))) {
     outputs(four{}, any{}, [&](int in_tile, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
       const float f = sS[in_tile];
       float x[4];
@@ -423,14 +455,14 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       }
       store_row(e, row, col, N, v);
     });
-  } else if (!e.out_f32 && !e.bias && !e.residual) {
+  } else if (e.vec && !e.out_f32 && !e.bias && !e.residual) {
     outputs(eight{}, plain{}, [&](int in_tile, int row, int col, float (&v)[8], f32x4 &) __attribute__((always_inline)) {
       const float f = sS[in_tile];
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] *= f;
       store_n(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * N + col, v, 1);
     });
-  } else if (!e.bias && !e.residual && !e.y2 && !e.hooks) {
+  } else if (e.vec && !e.bias && !e.residual && !e.y2 && !e.hooks) {
     outputs(four{}, plain{}, [&](int in_tile, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
       const float f = sS[in_tile];
 #pragma unroll
@@ -443,20 +475,24 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       const float f = sS[in_tile];
 #pragma unroll
       for (int i = 0; i < W; ++i) v[i] *= f;
+      typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
+      typedef words words_at __attribute__((aligned(2)));
+      auto bf = [](const words &w, int i) __attribute__((always_inline)) {
+        return __uint_as_float(i & 1 ? w[i >> 1] & 0xffff0000u : w[i >> 1] << 16);
+      };
       if (e.bias) {
-        float bv[W];
-        load_n(e.bias + col, bv, 1);
+        const words bv = *reinterpret_cast<const words_at *>(e.bias + col);
 #pragma unroll
-        for (int i = 0; i < W; ++i) v[i] += bv[i];
+        for (int i = 0; i < W; ++i) v[i] += bf(bv, i);
       }
       if (e.residual) {
 #pragma unroll
         for (int i = 0; i < W; ++i) {
           if constexpr (std::is_same_v<std::remove_reference_t<decltype(res)>, f32x4>) v[i] += res[i];
-          else v[i] += __uint_as_float(i & 1 ? res[i >> 1] & 0xffff0000u : res[i >> 1] << 16);
+          else v[i] += bf(res, i);
         }
       }
-      store_row(e, row, col, N, v);
+      store_row_at(e, row, col, N, v);
     };
     if (!e.out_f32) outputs(eight{}, full_bf{}, all);
     else if (e.residual && !e.res_f32) outputs(four{}, full_bf{}, all);

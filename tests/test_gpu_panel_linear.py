@@ -222,8 +222,8 @@ def test_a_public_norm_leaves_the_workspace_alone(tile, M, N, K):
 # one row tile and a row, columns with a remainder; and rows that leave the last wave's pieces empty
 @pytest.mark.parametrize("tile", ROWS)
 def test_bias_and_residual(tile):
-    """Bias and a bf16 residual, alone and together, into bf16 (the residual's own buffer too) and into floats: the oracle's
-    values, the ring kernel's bits."""
+    """Bias and a bf16 residual, alone and together, into bf16 (the residual's own buffer too) and into floats, all on and all off
+    16 bytes: the oracle's values, the ring kernel's bits, nothing written beside the output."""
     eng, K = engine(), 128
     for M, N in [(ROWS[tile] + 1, COLS[tile] + 8), (ROWS[tile] // 2 + 17, 2 * COLS[tile])]:
         g = synth.rng(65, tile + M)
@@ -233,32 +233,45 @@ def test_bias_and_residual(tile):
         res = synth.to_bf16_values(g.standard_normal((M, N), dtype=np.float32))
         xd, wd, bd, rd = dev(x, "bf16"), dev(w, "bf16"), dev(bias, "bf16"), dev(res, "bf16")
         packed = (eng.sf_pack_weight(wd), N)
+        off = lambda t: torch.cat([t.flatten()[:1], t.flatten()])[1:].view(t.shape)
 
         def outputs(t):
             eng.sf_tune_linear(t, 1)
             out = [eng.sf_op_linear(xd, None, bias=b, residual=r, out_f32=f, packed=packed)
                    for f in (False, True) for b, r in ((bd, None), (None, rd), (bd, rd))]
             own = rd.clone()
-            return out + [eng.sf_op_linear(xd, None, bias=bd, residual=own, y=own, packed=packed)]
+            out.append(eng.sf_op_linear(xd, None, bias=bd, residual=own, y=own, packed=packed))
+            for f in (False, True):                   # one element off: 2 bytes, float outputs 4
+                for b, r in ((None, None), (bd, None), (bd, rd)):
+                    b, r = b if b is None else off(b), r if r is None else off(r)
+                    y = torch.full((M * N + 2,), 7.0, device="cuda", dtype=torch.float32 if f else torch.bfloat16)
+                    eng.sf_op_linear(xd, None, bias=b, residual=r, out_f32=f, y=y[1:-1].view(M, N), packed=packed)
+                    out.append(y)
+            return out
         try:
             assert linear_choice(M, N, K, tile=tile, split=1) == (sfb.SF_KERNEL_BLOCK, tile, 1)
             want = outputs(RING_TILE)
             assert rel_err(to_np(want[5]), sfo.linear(x, w) + bias + res) < 1e-5
-            for i, (got, ref) in enumerate(zip(outputs(tile), want)):
-                assert torch.equal(got, ref), (M, N, i)
+            got = outputs(tile)
+            for i, (a, b) in enumerate(zip(got, want)):
+                assert torch.equal(a, b), (M, N, i)
+            for i, aligned in ((8, 0), (9, 2), (11, 3), (12, 5)):
+                assert torch.equal(got[i][1:-1].view(M, N), got[aligned]) and got[i][0] == got[i][-1] == 7.0, (M, N, i)
         finally:
             eng.sf_tune_linear(0, 0)
 
 
-def test_a_bf16_residual_costs_little():
+@pytest.mark.parametrize("off", [0, 1])
+def test_a_bf16_residual_costs_little(off):
     """Bias and residual are requested ahead of their use: with them a wide layer takes hardly longer (measured 1.02 of the
-    time, 1.5 to 1.7 where every residual is waited for)."""
+    time, 1.06 off 16 bytes; 1.5 to 1.7 where every residual is waited for)."""
     M, N, K = 1280, 28672, 4096
     assert linear_choice(M, N, K)[1] == 15
     eng = engine()
     x = torch.randn(M, K, device="cuda").bfloat16()
     packed = (eng.sf_pack_weight((torch.randn(N, K, device="cuda") * 0.05).bfloat16()), N)
-    bias, res, y = (torch.randn(*s, device="cuda").bfloat16() for s in ((N,), (M, N), (M, N)))
+    bias, res, y = (torch.randn(n + 1, device="cuda").bfloat16()[off:off + n] for n in (N, M * N, M * N))
+    res, y = res.view(M, N), y.view(M, N)
 
     def time(**more):
         a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
