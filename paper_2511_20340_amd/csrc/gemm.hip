@@ -261,6 +261,9 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
 // 20's norm by hand: its waves have one row block, and the squares of one chunk wait for each other.)  The panel kernel's
 // tiles (15-17, 26-28) were fitted to 360 shapes of 40 to 2304 rows, weights rotated through 600 MB, 6 to 9 % rms; their
 // norm is a launch in front, priced 4 us above what it takes by itself: so much more a launch costs in the chain of a step.
+// All of these have K >= 2048.  On 420 shapes of 2 to 16 slices of K (170 to 3000 rows, 1024 to 16384 columns) the prices hold
+// but for tile 26 and the tall ring tiles, which have another line there (cost_us); with it the choice is 1.1 % slower than
+// the fastest tile of each, 5 % without (900 x 16384 x 128 took 20.2 us for 13.5).
 // Tile 18 has one row for both kernels: the constants are the block kernel's, which it runs on with the norm; without it the
 // panel kernel's times are 0.82 to 1.07 of the formula's (13 shapes of 192 to 2048 rows, 7 % rms).
 struct TileCost {
@@ -291,7 +294,10 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
   const int tiles_m = (M + t.bm - 1) / t.bm, units = (N + t.bn - 1) / t.bn * (t.groups > 1 ? 1 : split);
   const int per_cu = ((units + XCDS - 1) / XCDS * tiles_m + 31) / 32;  // 32 compute units in the busiest XCD
   const bool before = squares_before(c.tile);  // a launch in front
-  const double cu = std::max((double)per_cu, (double)t.least) * ((t.slice + (norm && !before ? t.norm : 0.f)) * kps + t.fixed);
+  double wg = (t.slice + (norm && !before ? t.norm : 0.f)) * kps + t.fixed;
+  if (kps < 16 && c.tile == 26) wg = std::max(wg, 0.326 * kps + 4.2);         // filling four slices, and the epilogue
+  if (kps < 16 && c.tile >= 11 && c.tile <= 14) wg += std::max(0.0, 9.5 - t.fixed);
+  const double cu = std::max((double)per_cu, (double)t.least) * wg;
   const double mem = (double)N * K * 2 / 7.22e6;
   const double second = split > 1 && t.groups == 1 ? 2.5 + (double)M * N * 4 * split / 2.27e6 : 0.0;
   return 1.4 + std::max(cu, mem) + 0.44 * std::min(cu, mem) + second + (norm && before ? t.norm : 0.f);
