@@ -363,11 +363,16 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     });
     return;
   }
-  // how_c: PLAIN rows; FULL, FULL_BF: bias, a float or bf16 residual (requested as many pieces ahead as registers allow: y may
-  // be the residual, a lane's own elements; at any address), bf16 copy, hooked copies; ANY: rows that end within the W, any
+  // how_c: PLAIN rows, a bias; FULL, FULL_BF: also a float or bf16 residual (requested as many pieces ahead as registers allow: y
+  // may be the residual, a lane's own elements; at any address), bf16 copy, hooked copies; ANY: rows that end within the W, any
   // types, in a loop that is not unrolled and waits for every residual (1280 x 28672 x 4096, bf16 with bias and residual: 373
-  // us that way, FULL_BF 250; without either 245)
+  // us that way, FULL_BF 250; without either 245).  A lane's units are in the same columns of every row, so it reads its bias
+  // once, ahead (read for every unit, 1024 x 16384 x 256 with a bias took 21.8 us; 16.6 this way, 17.0
+  // without one)
   enum { PLAIN, FULL, FULL_BF, ANY };
+  auto bf_of = [](const auto &w, int i) __attribute__((always_inline)) {  // value i of packed bf16
+    return __uint_as_float(i & 1 ? w[i >> 1] & 0xffff0000u : w[i >> 1] << 16);
+  };
   auto outputs = [&](auto w_c, auto how_c, auto store) __attribute__((always_inline)) {
     constexpr int W = decltype(w_c)::value, PR = TN * 16 / W, T = (16 * PR + 63) / 64;  // units per row; units per lane
     constexpr int how = decltype(how_c)::value;
@@ -384,6 +389,12 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
     };
     constexpr int DEEP = 24 / T < 1 ? 1 : 24 / T, RING = TM < DEEP ? TM : DEEP;  // pieces of residual rows in flight
     res_t res[ahead ? RING : 1][ahead ? T : 1];
+    static_assert(64 % PR == 0, "one bias per lane");
+    words bias = {};
+    if (how != ANY && e.bias) {
+      typedef words __attribute__((aligned(2))) words_at;
+      bias = *reinterpret_cast<const words_at *>(e.bias + min(col0 + lane % PR * W, N - W));
+    }
     auto request = [&](int to, int a) __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < T; ++t) {
@@ -399,7 +410,11 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       if ((16 * PR) % 64 != 0 && r >= 16) return;
       float v[W];
       load_n(p + r * S::ROW + (col - col0), v, 1);
-      if (row < M && col < N) store((wm * TM + a) * 16 + r, row, col, v, own);
+      if (row < M && col < N) {
+        if constexpr (ahead) store((wm * TM + a) * 16 + r, row, col, v, own, bias);
+        else if constexpr (how == PLAIN) store((wm * TM + a) * 16 + r, row, col, v, bias);
+        else store((wm * TM + a) * 16 + r, row, col, v);
+      }
     };
     if (ahead && e.residual) {
 #pragma unroll
@@ -433,11 +448,11 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
   typedef std::integral_constant<int, FULL_BF> full_bf;
   typedef std::integral_constant<int, ANY> any;
   if (split_k > 1) {
-    outputs(four{}, plain{}, [&](int, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
+    outputs(four{}, plain{}, [&](int, int row, int col, float (&v)[4], const auto &) __attribute__((always_inline)) {
       store_n(partial + ((size_t)ks * M + row) * N + col, v, 1);
     });
   } else if (N % 8 != 0 || (!e.out_f32 && (e.y2 || e.hooks || (e.residual && e.res_f32)))) {
-    outputs(four{}, any{}, [&](int in_tile, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
+    outputs(four{}, any{}, [&](int in_tile, int row, int col, float (&v)[4]) __attribute__((always_inline)) {
       const float f = sS[in_tile];
       float x[4];
 #pragma unroll
@@ -455,48 +470,78 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_panel_kernel(const bf16_
       }
       store_row(e, row, col, N, v);
     });
-  } else if (e.vec && !e.out_f32 && !e.bias && !e.residual) {
-    outputs(eight{}, plain{}, [&](int in_tile, int row, int col, float (&v)[8], f32x4 &) __attribute__((always_inline)) {
-      const float f = sS[in_tile];
+  } else if (e.vec && !e.out_f32 && !e.residual) {
+    auto rows = [&](auto with) __attribute__((always_inline)) {  // two loops: a branch per unit costs 1 to 2 % without a bias
+      outputs(eight{}, plain{}, [&](int in_tile, int row, int col, float (&v)[8], const auto &bias) __attribute__((always_inline)) {
+        const float f = sS[in_tile];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] *= f;
-      store_n(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * N + col, v, 1);
-    });
+        for (int i = 0; i < 8; ++i) v[i] *= f;
+        if constexpr (decltype(with)::value) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] += bf_of(bias, i);
+        }
+        store_n(reinterpret_cast<bf16_t *>(e.y) + (size_t)row * N + col, v, 1);
+      });
+    };
+    if (e.bias) rows(std::true_type{});
+    else rows(std::false_type{});
   } else if (e.vec && !e.bias && !e.residual && !e.y2 && !e.hooks) {
-    outputs(four{}, plain{}, [&](int in_tile, int row, int col, float (&v)[4], f32x4 &) __attribute__((always_inline)) {
+    outputs(four{}, plain{}, [&](int in_tile, int row, int col, float (&v)[4], const auto &) __attribute__((always_inline)) {
       const float f = sS[in_tile];
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] *= f;
       store_n(reinterpret_cast<float *>(e.y) + (size_t)row * N + col, v, 1);
     });
   } else {
-    auto all = [&](int in_tile, int row, int col, auto &v, auto &res) __attribute__((always_inline)) {
+    auto all = [&](int in_tile, int row, int col, auto &v, auto &res, const auto &bias) __attribute__((always_inline)) {
       constexpr int W = sizeof(v) / sizeof(float);
       const float f = sS[in_tile];
 #pragma unroll
       for (int i = 0; i < W; ++i) v[i] *= f;
-      typedef uint32_t words __attribute__((ext_vector_type(W / 2)));
-      typedef words words_at __attribute__((aligned(2)));
-      auto bf = [](const words &w, int i) __attribute__((always_inline)) {
-        return __uint_as_float(i & 1 ? w[i >> 1] & 0xffff0000u : w[i >> 1] << 16);
-      };
       if (e.bias) {
-        const words bv = *reinterpret_cast<const words_at *>(e.bias + col);
 #pragma unroll
-        for (int i = 0; i < W; ++i) v[i] += bf(bv, i);
+        for (int i = 0; i < W; ++i) v[i] += bf_of(bias, i);
       }
       if (e.residual) {
 #pragma unroll
         for (int i = 0; i < W; ++i) {
           if constexpr (std::is_same_v<std::remove_reference_t<decltype(res)>, f32x4>) v[i] += res[i];
-          else v[i] += bf(res, i);
+          else v[i] += bf_of(res, i);
         }
       }
       store_row_at(e, row, col, N, v);
     };
-    if (!e.out_f32) outputs(eight{}, full_bf{}, all);
-    else if (e.residual && !e.res_f32) outputs(four{}, full_bf{}, all);
-    else outputs(four{}, full{}, all);
+    // a bf16 residual and nothing else but a bias: written out for either (with the branches of `all`, 2048 x 16384 x 256 into bf16
+    // with both takes 42 us; 36 this way)
+    auto sums = [&](auto w_c, auto with) __attribute__((always_inline)) {
+      constexpr int W = decltype(w_c)::value;
+      typedef std::conditional_t<W == 8, bf16_t, float> out_t;
+      outputs(w_c, full_bf{}, [&](int in_tile, int row, int col, float (&v)[W], auto &res, const auto &bias) __attribute__((always_inline)) {
+        const float f = sS[in_tile];
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+          v[i] *= f;
+          if constexpr (decltype(with)::value) v[i] += bf_of(bias, i);
+          v[i] += bf_of(res, i);
+        }
+        store_at(reinterpret_cast<out_t *>(e.y) + (size_t)row * N + col, v);
+      });
+    };
+    if (e.residual && !e.res_f32 && !e.y2 && !e.hooks) {
+      if (e.out_f32) {
+        if (e.bias) sums(four{}, std::true_type{});
+        else sums(four{}, std::false_type{});
+      } else {
+        if (e.bias) sums(eight{}, std::true_type{});
+        else sums(eight{}, std::false_type{});
+      }
+    } else if (!e.out_f32) {
+      outputs(eight{}, full_bf{}, all);
+    } else if (e.residual && !e.res_f32) {
+      outputs(four{}, full_bf{}, all);
+    } else {
+      outputs(four{}, full{}, all);
+    }
   }
 #endif
 }
