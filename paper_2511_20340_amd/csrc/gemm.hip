@@ -264,6 +264,8 @@ GemmConfig pick(int M, int N, int K, size_t ws_bytes, int fixed_split) {
 // All of these have K >= 2048.  On 420 shapes of 2 to 16 slices of K (170 to 3000 rows, 1024 to 16384 columns) the prices hold
 // but for tile 26 and the tall ring tiles, which have another line there (cost_us); with it the choice is 1.1 % slower than
 // the fastest tile of each, 5 % without (900 x 16384 x 128 took 20.2 us for 13.5).
+// Tiles 29-31 have one too: 483 x 9136 x 64 with the norm takes 14.1 us on tile 29, 9.0 on 18 (up to 4 us more than the line
+// says, as tile 18 is there, which keeps its price: beside the ring kernel's, short as well, it holds).
 // Tile 18 has one row for both kernels: the constants are the block kernel's, which it runs on with the norm; without it the
 // panel kernel's times are 0.82 to 1.07 of the formula's (13 shapes of 192 to 2048 rows, 7 % rms).
 struct TileCost {
@@ -297,6 +299,7 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
   double wg = (t.slice + (norm && !before ? t.norm : 0.f)) * kps + t.fixed;
   if (kps < 16 && c.tile == 26) wg = std::max(wg, 0.326 * kps + 4.2);         // filling four slices, and the epilogue
   if (kps < 16 && c.tile >= 11 && c.tile <= 14) wg += std::max(0.0, 9.5 - t.fixed);
+  if (kps < 16 && c.tile >= 29) wg += 1.5 + 0.025 * t.bm - t.fixed;
   const double cu = std::max((double)per_cu, (double)t.least) * wg;
   const double mem = (double)N * K * 2 / 7.22e6;
   const double second = split > 1 && t.groups == 1 ? 2.5 + (double)M * N * 4 * split / 2.27e6 : 0.0;
@@ -312,13 +315,14 @@ double cost_us(int M, int N, int K, GemmConfig c, int norm) {
 // with norm and gate is 9 us faster on 160 x 128 than on the ring kernel, and the launch in front takes that back inside a
 // step.  Over 360 shapes (40 to 2304 rows, with the norm, float output or arg-max, replayed from graphs) the choice is 0.8 %
 // slower than the fastest tile of each.  A norm whose row sums have nowhere to go (norm_ws, as for block_takes) leaves the
-// panel kernel out of an unsplit layer: there 29-31 stand in for 15-17, and the ring kernel's formula holds.
+// panel kernel out of an unsplit layer: there 29-31 stand in for 15-17, and the ring kernel's formula is short by as much
+// (without the 8 %, 716 x 5168 x 192 takes 11.2 us on tile 8, 9.1 on 22; 306 x 14536 x 960 20.9 on tile 5, 18.6 on 22).
 GemmConfig pick_any(int M, int N, int K, size_t ws_bytes, int split, ptrdiff_t norm_ws, bool am) {
   const int norm = norm_ws >= 0;
   const bool no_panel = norm && make_plan(M, N, K, 32, 32, split).split_k == 1 && !squares_fit(M, norm_ws);
   GemmConfig best = pick(M, N, K, ws_bytes, split);
   if (M <= 32) return best;
-  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : no_panel ? 1.0 : 1.08);
+  double best_us = cost_us(M, N, K, best, norm) * (am && M <= 192 ? 0.9 : M <= 160 ? 0.95 : 1.08);
   for (int tile = N_RING_TILES + 1; tile <= N_TILES; ++tile) {
     if ((tile > 28 ? !no_panel : tile > 25 && M <= 160) || !block_takes(tile, M, N, K, split, am, norm_ws)) continue;
     const Plan p = make_plan(M, N, K, TILE_COST[tile].bm, TILE_COST[tile].bn, split);

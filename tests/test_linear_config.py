@@ -235,3 +235,17 @@ def test_short_k_is_priced_by_its_own_measurements():
     does at K >= 2048, where the constants come from.  At most one of these shapes misses the tiles measured near its best."""
     miss = [s for s, ok in SHORT_K_NEAR_BEST.items() if linear_choice(*s)[1] not in ok]
     assert len(miss) <= 1, miss
+
+
+# the same for a public norm, whose tiles are the ring kernel's, 18-25 and 29-31 (measured without a workspace, one card)
+PUBLIC_NORM_NEAR_BEST = {
+    (483, 9136, 64): {18}, (654, 5360, 64): {18}, (175, 14224, 64): {19}, (189, 9608, 128): {20}, (520, 6288, 192): {22},
+    (714, 23328, 192): {31}, (856, 11672, 320): {31}, (1635, 16984, 448): {30}, (306, 14536, 960): {22}, (1060, 8696, 4160): {31},
+    (359, 5312, 4160): {19}, (1080, 14624, 4736): {29},
+}
+
+
+def test_a_public_norm_is_priced_by_its_own_measurements():
+    """At most one of these shapes misses the tiles measured within 5 % of its best."""
+    miss = [s for s, ok in PUBLIC_NORM_NEAR_BEST.items() if linear_choice(*s, OP_NORM, ws=0)[1] not in ok]
+    assert len(miss) <= 1, miss
